@@ -181,7 +181,7 @@ Layout make_resnet_layout(const lsgd_config* c) {
     if (i % 2 == 0) r.cv[i].act = take(sz);
     if (i % 2 == 0 && i > 0) r.cv[i].mbits = take(sz / 32);
     maxact = std::max(maxact, std::max(sz, K * B * q.H * q.W * q.Cin * 4));
-    maxpart = std::max(maxpart, (size_t)lsgd::conv_wgrad_splits(c->B_loc, q.Ho, q.Wo) *
+    maxpart = std::max(maxpart, (size_t)lsgd::conv_wgrad_splits(c->K, c->B_loc, q.Ho, q.Wo) *
                                     K * 9 * q.Cin * q.Cout * 4);
     maxbn = std::max(maxbn, K * lsgd::bn_chunks(c->B_loc * q.Ho * q.Wo) * q.Cout * 2 * 8);
     // the forward convolutions' statistics: one partial per 256 output rows
@@ -207,7 +207,7 @@ Layout make_resnet_layout(const lsgd_config* c) {
   r.wpart = take(maxpart);
   // the stem's weight-gradient partials apart: the main stream forms them
   // while the side stream may still use wpart
-  r.wpart0 = take((size_t)lsgd::conv_wgrad_splits(c->B_loc, r.cv[0].Ho, r.cv[0].Wo) * K * 9 *
+  r.wpart0 = take((size_t)lsgd::conv_wgrad_splits(c->K, c->B_loc, r.cv[0].Ho, r.cv[0].Wo) * K * 9 *
                   r.cv[0].Cin * r.cv[0].Cout * 4);
   l.total = t;
   return l;
@@ -902,7 +902,7 @@ lsgd_status do_local_step_resnet(lsgd_ctx* c, float lr, float* d_loss) {
     g.out = part;
     LSGD_LAUNCH_ON(c, ws, "conv_wgrad", lsgd::launch_conv(lsgd::CONV_WGRAD_MODE, g, ws));
     LSGD_LAUNCH_ON(c, ws, "conv_wupdate",
-                   lsgd::launch_conv_wupdate(part, lsgd::conv_wgrad_splits(B, q.Ho, q.Wo),
+                   lsgd::launch_conv_wupdate(part, lsgd::conv_wgrad_splits(K, B, q.Ho, q.Wo),
                                              K, 9 * q.Cin * q.Cout, W + q.offW, U + q.offW,
                                              Ps, lr, cf.momentum, cf.weight_decay,
                                              upd_mode(cf), ws));

@@ -192,7 +192,7 @@ enum { CONV_FWD_MODE = 0, CONV_DGRAD_MODE = 1, CONV_WGRAD_MODE = 2 };
 // bit 2 the sums with the activation mask (bs_hb). A launch takes one of them,
 // or the shortcut with one kind of sums.
 int conv_dgrad_epilogues(const ConvGeom& q);
-int conv_wgrad_splits(int Bt, int Ho, int Wo);
+int conv_wgrad_splits(int G, int Bt, int Ho, int Wo);
 // Whether the forward convolution of q writes its output's BN statistics
 // (per 256-row chunk, [G][R/256][Cout][2] doubles: sum, sum of squares) when
 // q.stats is set; the caller then finalises with launch_bn_finalize_chunks.

@@ -1946,16 +1946,22 @@ bool conv_fwd_stats(const ConvGeom& q) {
   return rows_shape(q, CONV_FWD) && ((long long)q.Bt * q.Ho * q.Wo) % 256 == 0;
 }
 
-// Splits of a weight gradient over the batch: a power of two that divides
-// the batch (the stem's kernel takes whole images per split). The band
-// kernel of the 16- and 8-wide stages takes 32 and 16 splits (about two and
-// one workgroups per compute unit at 16 replicas, each with whole bands);
-// the others at most 64 with at least 1024 positions per split.
-int conv_wgrad_splits(int Bt, int Ho, int Wo) {
+// Splits of a weight gradient over the batch of each of G replicas: a power
+// of two (the update kernel's instances). At 16 or more replicas 64 for the
+// 32-wide stage and 32 / 16 for the 16- / 8-wide ones (about four, two and one
+// workgroups per compute unit at 16 replicas); with fewer replicas up to 64,
+// while the launch has no more workgroups than it has at 16. Every split keeps
+// at least one 64-position band (1024 positions of the 32-wide stage); the
+// split need not divide the batch: split s takes bands (images, in the stem)
+// [s per, (s + 1) per), per rounded up. (A rule that asked for dividing splits
+// left a batch of 90 with two of them, six workgroups for three replicas: 13.6
+// ms for a local step of that case, against 2.2 ms.)
+int conv_wgrad_splits(int G, int Bt, int Ho, int Wo) {
   const int rows = Bt * Ho * Wo;
-  const int cap = Wo == 16 ? 32 : Wo == 8 ? 16 : 64;
+  int cap = Wo == 16 ? 32 : Wo == 8 ? 16 : 64;
+  for (const int wgs = 16 * cap; cap < 64 && (long long)G * 2 * cap <= wgs;) cap *= 2;
   int s = 1;
-  while (s < cap && rows / (2 * s) >= (Wo <= 16 ? 64 : 1024) && Bt % (2 * s) == 0) s *= 2;
+  while (s < cap && rows / (2 * s) >= (Wo <= 16 ? 64 : 1024)) s *= 2;
   return s;
 }
 
@@ -2027,8 +2033,7 @@ hipError_t launch_conv(int mode, const ConvGeom& q, hipStream_t st) {
                : mode == CONV_DGRAD ? q.Bt * q.H * q.W : 9 * q.Cin;
   const int Ng = mode == CONV_DGRAD ? q.Cin : q.Cout;
   if (mode == CONV_WGRAD) {
-    c.splits = conv_wgrad_splits(q.Bt, q.Ho, q.Wo);
-    const int rows = q.Bt * q.Ho * q.Wo;
+    c.splits = conv_wgrad_splits(q.G, q.Bt, q.Ho, q.Wo);
     const bool halo = q.Cin == 16 && q.Cout == 16 && q.stride == 1 && q.W == 32 &&
                       q.Wo == 32 && q.H == q.Ho && q.H % 8 == 0 && !q.rowmap &&
                       ((uintptr_t)q.x & 15) == 0 && ((uintptr_t)q.dy & 15) == 0 &&
@@ -2039,7 +2044,7 @@ hipError_t launch_conv(int mode, const ConvGeom& q, hipStream_t st) {
       return hipGetLastError();
     }
     if (stem_shape(q)) {
-      c.mchunk = rows / c.splits;  // whole images per split
+      c.mchunk = (q.Bt + c.splits - 1) / c.splits * q.Ho * q.Wo;  // whole images per split
       hipLaunchKernelGGL(k_conv_wgrad_stem, dim3((unsigned)(q.G * c.splits)), dim3(kT), 0,
                          st, c);
       return hipGetLastError();
