@@ -89,18 +89,21 @@ def test_resnet20_batch_not_a_multiple_of_four():
     assert e <= 1e-5
 
 
-@pytest.mark.parametrize("K,B,seed", [(3, 13, 0x5EED0015), (1, 37, 0x5EED0017)])
+@pytest.mark.parametrize("K,B,seed", [(3, 33, 0x5EED0015), (1, 37, 0x5EED0017)])
 def test_resnet20_weight_gradient_splits_that_do_not_divide_the_batch(K, B, seed):
     """Odd batches at few replicas: the last weight-gradient splits get fewer
-    bands (images) than the others, or none. Every replica after each of two
-    steps; a 1e-7 perturbation of the initial weights moves the oracle's
-    replicas by 3.4e-7 over them at these seeds."""
+    bands (images) than the others, or none. Every replica after one step: a
+    left-out band would move it by more than 1e-4, while five 1e-7
+    perturbations of the initial weights move the oracle's replicas by at most
+    4.2e-7 and 1.6e-6 here (a second step, or a batch of 13, by up to 1.6e-5:
+    with few images a ReLU or a small batch variance amplifies rounding beyond
+    the 1e-5 bar)."""
     base = wk.get("resnet20")
     w = base.scaled(K=K, N=4096, B_loc=B, sample_seed=seed)
     X, y = wk.dataset(base)
     X, y = np.ascontiguousarray(X[:4096]), np.ascontiguousarray(y[:4096])
     print(f"resnet20 K={K} B={B}", flush=True)
-    _, _, worst = _compare(w, X, y, wk.initial_weights(w), 2, list(range(K)), 1e-5, 1e-4)
+    _, _, worst = _compare(w, X, y, wk.initial_weights(w), 1, list(range(K)), 1e-5, 1e-4)
     print(f"resnet20 K={K} B={B}: worst step error {worst:.3e}", flush=True)
 
 
