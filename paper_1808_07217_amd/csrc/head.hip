@@ -2,15 +2,14 @@
 // the loss: the mean mini-batch cross-entropy whose gradient is the bracket of
 // eq. 2 in the paper.
 //
-// k_head_fwd: one wavefront per sample row b of replica k. Lanes stride over
-//   the D inputs to form the C logits, reduced across the wave by a fixed xor
-//   butterfly; then softmax cross-entropy (stable form), dZ = (p - onehot)/B,
-//   and, below the top layer, the input gradient dA[d] = sum_c dZ[c] W[d][c]
-//   masked by the ReLU derivative (A > 0).
+// k_head_fwd: one workgroup per few sample rows of a replica: its four waves
+//   split the D inputs, then softmax cross-entropy (stable form), dZ = (p -
+//   onehot)/B, and, below the top layer, the input gradient dA[d] = sum_c
+//   dZ[c] W[d][c] masked by the ReLU derivative (A > 0).
 // k_head_wgrad: one workgroup per (replica, 64 inputs d): dW[d][c] =
-//   sum_b A[b][d] dZ[b][c] in ascending b, fused with the momentum-SGD update;
-//   workgroup 0 of each replica also updates the bias (sum_b dZ[b][c]) and
-//   reduces the per-row losses in ascending b.
+//   sum_b A[b][d] dZ[b][c], fused with the momentum-SGD update; workgroup 0 of
+//   each replica also updates the bias (sum_b dZ[b][c]) and reduces the
+//   per-row losses.
 #include "kernels.h"
 
 namespace lsgd {
@@ -35,26 +34,6 @@ __device__ __forceinline__ float round_like(float v, const bf16_t*) {
   return bf16_to_f32(f32_to_bf16(v));
 }
 
-// dst[i] = src[base + i] for i < n by the 256 threads of the workgroup, eight
-// loads in flight per thread before the LDS stores.
-template <typename T>
-__device__ __forceinline__ void stage(float* dst, const T* src, long long base,
-                                      int n) {
-  for (int i0 = 0; i0 < n; i0 += 8 * 256) {
-    float v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int i = i0 + u * 256 + (int)threadIdx.x;
-      v[u] = i < n ? ld(src, base + i) : 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int i = i0 + u * 256 + (int)threadIdx.x;
-      if (i < n) dst[i] = v[u];
-    }
-  }
-}
-
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -69,342 +48,286 @@ __device__ __forceinline__ void sgd_step(float& w, float& u, float grad,
   w = __builtin_fmaf(-h.lr, d, w);
 }
 
-// Rows of W_L staged in LDS per pass: W chunk [DCH][C] plus nothing else.
-template <int CMAX>
-constexpr int head_chunk() { return CMAX <= 16 ? 1024 : 512; }
+// The CM classes of one row of W_L from p on, in vector loads at any element
+// alignment. Classes past the real count are whatever follows the row (the
+// bias or padding lies behind the last one): the callers drop what they form
+// from them.
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+template <int CM>
+__device__ __forceinline__ void load_row(const float* p, float (&w)[CM]) {
+#pragma unroll
+  for (int c = 0; c < CM; c += 4) {
+    const v4f_any t = *(const v4f_any*)(p + c);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[c + e] = t[e];
+  }
+}
+template <int CM>
+__device__ __forceinline__ void load_row(const bf16_t* p, float (&w)[CM]) {
+#pragma unroll
+  for (int c = 0; c < CM; c += 4) {
+    const u32x2_any t = *(const u32x2_any*)(p + c);
+    w[c] = __uint_as_float(t.x << 16);
+    w[c + 1] = __uint_as_float(t.x & 0xffff0000u);
+    w[c + 2] = __uint_as_float(t.y << 16);
+    w[c + 3] = __uint_as_float(t.y & 0xffff0000u);
+  }
+}
 
-template <typename T, int CMAX, bool GATHER>
+// Sums of v[0 .. N) over a wavefront (N / 32 whole): five exchanges that each
+// halve what a lane keeps (lanes with the exchanged bit set keep the upper
+// half), then one plain exchange; v[0 .. N/32) of lane l are the sums from
+// index first(l) on. 63 N / 64 + N / 32 exchanges instead of the 6 N of a
+// butterfly per value.
+template <int N, int OFF>
+__device__ __forceinline__ void scatter_sum(float* v, int lane, int& first) {
+  if constexpr (OFF == 1) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] += __shfl_xor(v[i], 1, 64);
+  } else {
+    const bool up = (lane & OFF) != 0;
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+      const float give = up ? v[i] : v[i + N / 2], keep = up ? v[i + N / 2] : v[i];
+      v[i] = keep + __shfl_xor(give, OFF, 64);
+    }
+    if (up) first += N / 2;
+    scatter_sum<N / 2, OFF / 2>(v, lane, first);
+  }
+}
+
+// Rows per workgroup of k_head_fwd: R x CM partial logits per lane.
+template <int CM>
+constexpr int head_rows() { return CM <= 16 ? 8 : 4; }
+
+// Logits, loss, dZ and the input gradient of R rows of replica k. The four
+// waves take inputs d = 256 i + 64 wave + lane: a lane reads the rows' values
+// and its row of W_L straight from memory, four strides in flight, and keeps R
+// x CM partial logits; the waves' sums are added in order. Bound by the rows'
+// bytes and, for small D, by its chain of three memory round trips. 3072
+// gathered inputs, 16 x 128 rows, 10 classes: 50 us with W_L staged through
+// LDS and two rows per wave, now 14.9 us; 5 x 50 rows of 100 inputs: 16
+// us, now 8.5.
+template <typename T, int CM, bool GATHER>
 __global__ __launch_bounds__(256) void k_head_fwd(HeadArgs h) {
-  constexpr int RPW = 2;             // sample rows per wavefront
-  constexpr int DCH = head_chunk<CMAX>();
-  __shared__ float Ws[DCH * CMAX];
-  const int k = blockIdx.y;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  constexpr int R = head_rows<CM>(), N = R * CM;
+  constexpr int LPR = CM <= 16 ? 16 : 32;  // softmax lanes per row
+  static_assert(N % 32 == 0 && R * LPR <= 256, "exchange and softmax shapes");
+  __shared__ float zs[4][N];
+  __shared__ __attribute__((aligned(16))) float dzs[N];
+  const int k = blockIdx.y, row0 = blockIdx.x * R;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
   const int D = h.D, C = h.C;
   const T* Wg = (const T*)h.W + (long long)k * h.sW;
-  const T* arow[RPW];
-  long long rr[RPW];
-  bool live[RPW];
+  const T* arow[R];
 #pragma unroll
-  for (int q = 0; q < RPW; ++q) {
-    const int row = (blockIdx.x * 4 + wave) * RPW + q;
-    live[q] = row < h.B;
-    rr[q] = (long long)k * h.B + (live[q] ? row : 0);
-    arow[q] = GATHER ? (const T*)h.A + (long long)h.rowmap[rr[q]] * D
-                     : (const T*)h.A + (long long)k * h.sA +
-                           (long long)(live[q] ? row : 0) * D;
+  for (int q = 0; q < R; ++q) {
+    const int row = min(row0 + q, h.B - 1);
+    arow[q] = GATHER ? (const T*)h.A + (long long)h.rowmap[(long long)k * h.B + row] * D
+                     : (const T*)h.A + (long long)k * h.sA + (long long)row * D;
   }
+  // softmax thread t: row t / LPR, class t % LPR; its label on its way
+  const int sq = (int)threadIdx.x / LPR, sc = (int)threadIdx.x % LPR;
+  const bool smx = sq < R;
+  const long long srr = (long long)k * h.B + min(row0 + sq, h.B - 1);
+  const int lab = smx ? h.y[h.rowmap[srr]] : 0;
+  const float bias = smx && sc < C ? h.bias[(long long)k * h.sBias + sc] : 0.f;
 
-  float z[RPW][CMAX];
+  float z[N];
 #pragma unroll
-  for (int q = 0; q < RPW; ++q)
+  for (int i = 0; i < N; ++i) z[i] = 0.f;
+  for (int d0 = wave * 64 + lane; d0 - lane < D; d0 += 1024) {
+    float av[4][R], w[4][CM];
 #pragma unroll
-    for (int c = 0; c < CMAX; ++c) z[q][c] = 0.f;
-  for (int d0 = 0; d0 < D; d0 += DCH) {
-    const int nd = min(DCH, D - d0);
-    __syncthreads();
-    stage(Ws, Wg, (long long)d0 * C, nd * C);
-    __syncthreads();
-    // four strides of 64 per pass: all loads first, then the FMAs
-    for (int db = 0; db < nd; db += 256) {
-      float av[4][RPW];
+    for (int u = 0; u < 4; ++u) {
+      const int d = min(d0 + 256 * u, D - 1);
+      load_row<CM>(Wg + (long long)d * C, w[u]);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int d = db + u * 64 + lane;
+      for (int q = 0; q < R; ++q) av[u][q] = ld(arow[q], d);
+    }
 #pragma unroll
-        for (int q = 0; q < RPW; ++q) av[u][q] = d < nd ? ld(arow[q], d0 + d) : 0.f;
-      }
+    for (int u = 0; u < 4; ++u) {
+      const bool in = d0 + 256 * u < D;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int d = db + u * 64 + lane;
-        if (d >= nd) continue;
+      for (int q = 0; q < R; ++q) {
+        const float x = in ? av[u][q] : 0.f;
 #pragma unroll
-        for (int c = 0; c < CMAX; ++c) {
-          if (c >= C) continue;
-          const float wdc = Ws[d * C + c];
-#pragma unroll
-          for (int q = 0; q < RPW; ++q) z[q][c] = __builtin_fmaf(av[u][q], wdc, z[q][c]);
+        for (int c = 0; c < CM; ++c) {
+          const float wc = in ? w[u][c] : 0.f;
+          z[q * CM + c] = __builtin_fmaf(x, wc, z[q * CM + c]);
         }
       }
     }
   }
-  const float* bias = h.bias + (long long)k * h.sBias;
-  const float invB = 1.0f / (float)h.B;
-  float dz[RPW][CMAX];
+  int first = 0;
+  scatter_sum<N, 32>(z, lane, first);
+  if ((lane & 1) == 0) {
 #pragma unroll
-  for (int q = 0; q < RPW; ++q) {
-#pragma unroll
-    for (int c = 0; c < CMAX; ++c)
-      if (c < C) z[q][c] = wave_sum(z[q][c]) + bias[c];
-    // softmax cross-entropy, identical in every lane
-    const int lab = h.y[h.rowmap[rr[q]]];
-    float m = z[q][0];
-#pragma unroll
-    for (int c = 1; c < CMAX; ++c)
-      if (c < C) m = fmaxf(m, z[q][c]);
-    float s = 0.f, rest = 0.f, zy = 0.f;
-#pragma unroll
-    for (int c = 0; c < CMAX; ++c)
-      if (c < C) {
-        const float e = __expf(z[q][c] - m);
-        s += e;
-        if (c != lab) rest += e;
-        else zy = z[q][c];
-      }
-    const float loss = zy >= m ? log1pf(rest) : (m - zy) + logf(s);
-    const float inv_s = 1.0f / s;
-    float mine = 0.f;
-#pragma unroll
-    for (int c = 0; c < CMAX; ++c) {
-      dz[q][c] = 0.f;
-      if (c < C) {
-        const float p = __expf(z[q][c] - m) * inv_s;
-        dz[q][c] = round_like((p - (c == lab ? 1.f : 0.f)) * invB, (const T*)nullptr);
-        if (c == lane) mine = dz[q][c];
-      }
-    }
-    if (live[q]) {
-      if (lane < C) st((T*)h.dZ, rr[q] * C + lane, mine);
-      if (lane == 0) h.rowloss[rr[q]] = loss;
-    }
+    for (int i = 0; i < N / 32; ++i) zs[wave][first + i] = z[i];
   }
-
-  if (!h.dZprev) return;  // uniform over the workgroup
-  // input gradient of the top layer, ReLU-masked: needs W_L again
-  for (int d0 = 0; d0 < D; d0 += DCH) {
-    const int nd = min(DCH, D - d0);
-    if (D > DCH) {  // the chunk in LDS is not the whole of W_L
-      __syncthreads();
-      stage(Ws, Wg, (long long)d0 * C, nd * C);
-      __syncthreads();
-    }
-    for (int db = 0; db < nd; db += 256) {
-      float mk[4][RPW];  // the ReLU mask operand, loaded up front
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int d = db + u * 64 + lane;
-#pragma unroll
-        for (int q = 0; q < RPW; ++q)
-          mk[u][q] = d < nd && live[q] ? ld(arow[q], d0 + d) : 0.f;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int d = db + u * 64 + lane;
-        if (d >= nd) continue;
-        float v[RPW];
-#pragma unroll
-        for (int q = 0; q < RPW; ++q) v[q] = 0.f;
-#pragma unroll
-        for (int c = 0; c < CMAX; ++c) {
-          if (c >= C) continue;
-          const float wdc = Ws[d * C + c];
-#pragma unroll
-          for (int q = 0; q < RPW; ++q) v[q] = __builtin_fmaf(dz[q][c], wdc, v[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < RPW; ++q)
-          if (live[q])
-            st((T*)h.dZprev + rr[q] * D, d0 + d,
-               (h.nomask || mk[u][q] > 0.f) ? v[q] : 0.f);
-      }
-    }
-  }
-}
-
-template <typename T, int CMAX, bool GATHER>
-__global__ __launch_bounds__(256) void k_head_wgrad(HeadArgs h) {
-  constexpr int RB = 64;  // batch rows staged in LDS per pass
-  constexpr int CJ = (CMAX + 3) / 4;
-  __shared__ float dzs[RB * CMAX];
-  __shared__ float As[RB][65];
-  __shared__ float red[256];
-  const int k = blockIdx.y;
-  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  const int D = h.D, C = h.C, B = h.B;
-  const int dbase = blockIdx.x * 64, d = dbase + lane;
-  const T* dZ = (const T*)h.dZ + (long long)k * B * C;
-  const bool first = blockIdx.x == 0;
-
-  float acc[CJ];
-#pragma unroll
-  for (int j = 0; j < CJ; ++j) acc[j] = 0.f;
-  float bsum = 0.f;  // bias gradient of class threadIdx.x (first workgroup)
-  for (int b0 = 0; b0 < B; b0 += RB) {
-    const int nb = min(RB, B - b0);
-    __syncthreads();
-    stage(dzs, dZ, (long long)b0 * C, nb * C);
-    // A[b0 + r][dbase .. dbase + 63]: each wave loads whole 64-wide rows,
-    // eight rows per batch with every load issued before the LDS stores
-    for (int r0 = grp; r0 < nb; r0 += 32) {
-      long long base[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int r = r0 + 4 * u;
-        const long long rr = (long long)k * B + b0 + (r < nb ? r : 0);
-        base[u] = GATHER ? (long long)h.rowmap[rr] * D
-                         : (long long)k * h.sA + (long long)(b0 + (r < nb ? r : 0)) * D;
-      }
-      float v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        v[u] = (r0 + 4 * u < nb && d < D) ? ld((const T*)h.A, base[u] + d) : 0.f;
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (r0 + 4 * u < nb) As[r0 + 4 * u][lane] = v[u];
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int b = 0; b < nb; ++b) {
-      const float av = As[b][lane];
-#pragma unroll
-      for (int j = 0; j < CJ; ++j) {
-        const int c = grp + 4 * j;
-        if (c < C) acc[j] = __builtin_fmaf(av, dzs[b * C + c], acc[j]);
-      }
-    }
-    if (first && (int)threadIdx.x < C)
-      for (int b = 0; b < nb; ++b) bsum += dzs[b * C + threadIdx.x];
-  }
-  if (d < D) {
-#pragma unroll
-    for (int j = 0; j < CJ; ++j) {
-      const int c = grp + 4 * j;
-      if (c >= C) continue;
-      const long long o = (long long)k * h.sP + (long long)d * C + c;
-      float w = h.Wsrc[(long long)k * h.sSrc + (long long)d * C + c], u = h.Um[o];
-      sgd_step(w, u, acc[j], h);
-      h.Wm[o] = w;
-      h.Um[o] = u;
-      if (h.Wb) h.Wb[o] = f32_to_bf16(w);
-    }
-  }
-  if (!first) return;  // uniform over the workgroup
-  if ((int)threadIdx.x < C) {
-    const long long o = (long long)k * h.sP + threadIdx.x;
-    float w = h.bsrc[(long long)k * h.sSrc + threadIdx.x], u = h.bias_u[o];
-    sgd_step(w, u, bsum, h);
-    h.bias_w[o] = w;
-    h.bias_u[o] = u;
-  }
-  // mean loss of replica k: per-thread strided partial sums, then a fixed tree
-  const float* rl = h.rowloss + (long long)k * B;
-  float part = 0.f;
-  for (int b = threadIdx.x; b < B; b += 256) part += rl[b];
-  red[threadIdx.x] = part;
   __syncthreads();
-  for (int w2 = 128; w2 > 0; w2 >>= 1) {
-    if ((int)threadIdx.x < w2) red[threadIdx.x] += red[threadIdx.x + w2];
-    __syncthreads();
+  if (smx) {  // whole wavefronts: R LPR is a multiple of 64
+    float zc = -INFINITY;
+    if (sc < C) {
+      const int i = sq * CM + sc;
+      zc = (((zs[0][i] + zs[1][i]) + zs[2][i]) + zs[3][i]) + bias;
+    }
+    float m = zc;
+#pragma unroll
+    for (int off = LPR / 2; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    const float e = sc < C ? __expf(zc - m) : 0.f;
+    float s = e, rest = sc != lab ? e : 0.f;
+#pragma unroll
+    for (int off = LPR / 2; off > 0; off >>= 1) {
+      s += __shfl_xor(s, off, 64);
+      rest += __shfl_xor(rest, off, 64);
+    }
+    const float zy = __shfl(zc, (lane & ~(LPR - 1)) + lab, 64);
+    const float loss = zy >= m ? log1pf(rest) : (m - zy) + logf(s);
+    const float p = e * (1.0f / s);
+    const float dz =
+        round_like((p - (sc == lab ? 1.f : 0.f)) * (1.0f / (float)h.B), (const T*)nullptr);
+    if (row0 + sq < h.B) {
+      if (sc < C) st((T*)h.dZ, srr * C + sc, dz);
+      if (sc == 0) h.rowloss[srr] = loss;
+    }
+    if (sc < CM) dzs[sq * CM + sc] = sc < C ? dz : 0.f;
   }
-  if (threadIdx.x == 0) {
-    const float mean = red[0] / (float)B;
-    if (h.loss) h.loss[k] = mean;
-    // a non-finite loss raises the context's flag (a plain store: every
-    // writer stores the same value)
-    if (h.nonfinite && !isfinite(mean)) *h.nonfinite = 1;
+  if (!h.dZprev) return;  // uniform over the workgroup
+  __syncthreads();
+  // input gradient, ReLU-masked: the rows and W_L again (from cache)
+  float dz[N];
+#pragma unroll
+  for (int i = 0; i < N; i += 4) *(float4*)&dz[i] = *(const float4*)&dzs[i];
+  T* out = (T*)h.dZprev + ((long long)k * h.B + row0) * D;
+  for (int d = wave * 64 + lane; d < D; d += 256) {
+    float w[CM], mk[R];
+    load_row<CM>(Wg + (long long)d * C, w);
+#pragma unroll
+    for (int q = 0; q < R; ++q) mk[q] = h.nomask ? 1.f : ld(arow[q], d);
+#pragma unroll
+    for (int c = 0; c < CM; ++c)
+      if (c >= C) w[c] = 0.f;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      float v = 0.f;
+#pragma unroll
+      for (int c = 0; c < CM; ++c) v = __builtin_fmaf(dz[q * CM + c], w[c], v);
+      if (row0 + q < h.B) st(out, (long long)q * D + d, mk[q] > 0.f ? v : 0.f);
+    }
   }
 }
 
-// Weight gradient of the output layer in one memory round trip (fp32,
-// C <= CM, D % 64 == 0, B <= 128): workgroup (x, k) owns inputs
-// d = 64 x .. 64 x + 63 of replica k. Every load -- the activations A[b][d]
-// of the lane's d for the group's rows b = grp + 4 r, dZ, this slice of W_L
-// and U_L, the per-row losses -- is issued up front. Each of the 4 thread
-// groups sums its quarter of the batch (rows grp, grp + 4, ... ascending);
-// the four partials are then added in group order and the SGD step applied.
+// Weight gradient of the output layer and its update: workgroup (x, k) owns
+// inputs d = 64 x .. 64 x + 63 of replica k (lane d), its four waves the batch
+// rows grp, grp + 4, ... Per 128 rows, the 32 activations of each thread and dZ
+// (zero-padded to CM classes, in LDS) are loaded at once; this slice of W_L and
+// U_L is on its way from the start. A row of dZ is read as CM / 4 broadcast
+// float4; the waves' partials are added in order and the SGD step applied.
 // Workgroup 0 of each replica also updates the bias and reduces the loss.
-template <int CM, bool GATHER>
-__global__ __launch_bounds__(256) void k_head_wgrad_vec(HeadArgs h) {
-  constexpr int RPG = 32;                 // rows per group: B <= 128
+// 3072 gathered inputs, 16 x 128 rows, 10 classes (floor 5 us for the rows):
+// 21 us with a class loop of runtime length, now 12.0 us.
+template <typename T, int CM, bool GATHER>
+__global__ __launch_bounds__(256) void k_head_wgrad(HeadArgs h) {
+  constexpr int RPG = 32, RB = 4 * RPG;       // rows per wave / workgroup and pass
   constexpr int WPT = (64 * CM + 255) / 256;  // weights per thread
-  constexpr int ZPT = (128 * CM + 255) / 256; // dZ values per thread
-  __shared__ float dzs[128 * CM];
+  constexpr int ZPT = RB * CM / 256;          // dZ values per thread and pass
+  __shared__ __attribute__((aligned(16))) float dzs[RB * CM];
   __shared__ float part[4][64][CM + 1];
   __shared__ float red[256];
-  const int k = blockIdx.y;
-  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  const int k = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int grp = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int D = h.D, C = h.C, B = h.B;
-  const int dbase = blockIdx.x * 64, d = dbase + lane;
+  const int dbase = blockIdx.x * 64, d = min(dbase + lane, D - 1);
+  const int nw = min(64, D - dbase) * C;  // this slice's weights
   const bool first = blockIdx.x == 0;
-  const float* dZ = (const float*)h.dZ + (long long)k * B * C;
-
-  // 1. all loads in flight together (clamped indices, values masked at use)
-  float av[RPG];
-#pragma unroll
-  for (int r = 0; r < RPG; ++r) {
-    const int b = min(grp + 4 * r, B - 1);
-    const long long row = GATHER ? (long long)h.rowmap[(long long)k * B + b]
-                                 : (long long)k * (h.sA / D) + b;
-    av[r] = ((const float*)h.A)[row * D + d];
-  }
-  float zv[ZPT];
-#pragma unroll
-  for (int q = 0; q < ZPT; ++q) zv[q] = dZ[min((int)threadIdx.x + 256 * q, B * C - 1)];
-  float wv[WPT], uv[WPT];
+  const T* dZ = (const T*)h.dZ + (long long)k * B * C;
   const long long wbase = (long long)k * h.sP + (long long)dbase * C;
+  float wv[WPT], uv[WPT];
 #pragma unroll
   for (int q = 0; q < WPT; ++q) {
-    const int e = min((int)threadIdx.x + 256 * q, 64 * C - 1);
+    const int e = min(tid + 256 * q, nw - 1);
     wv[q] = h.Wsrc[(long long)k * h.sSrc + (long long)dbase * C + e];
     uv[q] = h.Um[wbase + e];
   }
-  const float rl = first ? h.rowloss[(long long)k * B + min((int)threadIdx.x, B - 1)] : 0.f;
+  float rl = 0.f;  // per-row losses: strided partial sums, then a fixed tree
+  if (first)
+    for (int b = tid; b < B; b += 256) rl += h.rowloss[(long long)k * B + b];
 
-  // 2. dZ to LDS
-#pragma unroll
-  for (int q = 0; q < ZPT; ++q) {
-    const int i = (int)threadIdx.x + 256 * q;
-    if (i < B * C) dzs[i] = zv[q];
-  }
-  __syncthreads();
-
-  // 3. this group's rows
   float acc[CM];
 #pragma unroll
   for (int c = 0; c < CM; ++c) acc[c] = 0.f;
+  float bsum = 0.f;  // bias gradient of class tid (first workgroup)
+  for (int b0 = 0; b0 < B; b0 += RB) {
+    const int nb = min(RB, B - b0);
+    float av[RPG], zv[ZPT];
 #pragma unroll
-  for (int r = 0; r < RPG; ++r) {
-    const int b = grp + 4 * r;
-    if (b < B) {
+    for (int r = 0; r < RPG; ++r) {
+      const int b = b0 + min(grp + 4 * r, nb - 1);
+      const long long row = GATHER ? (long long)h.rowmap[(long long)k * B + b] * D
+                                   : (long long)k * h.sA + (long long)b * D;
+      av[r] = ld((const T*)h.A, row + d);
+    }
 #pragma unroll
-      for (int c = 0; c < CM; ++c)
-        if (c < C) acc[c] = __builtin_fmaf(av[r], dzs[b * C + c], acc[c]);
+    for (int q = 0; q < ZPT; ++q) {
+      const int i = tid + 256 * q, b = i / CM, c = i - b * CM;
+      zv[q] = b < nb && c < C ? ld(dZ, (long long)(b0 + b) * C + c) : 0.f;
+    }
+    if (b0) __syncthreads();  // the previous pass's dZ is no longer read
+#pragma unroll
+    for (int q = 0; q < ZPT; ++q) dzs[tid + 256 * q] = zv[q];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RPG; ++r) {
+      if (grp + 4 * r >= nb) break;  // uniform over the wave
+      const float* zr = dzs + (grp + 4 * r) * CM;
+#pragma unroll
+      for (int c = 0; c < CM; c += 4) {
+        const float4 z4 = *(const float4*)(zr + c);
+        acc[c] = __builtin_fmaf(av[r], z4.x, acc[c]);
+        acc[c + 1] = __builtin_fmaf(av[r], z4.y, acc[c + 1]);
+        acc[c + 2] = __builtin_fmaf(av[r], z4.z, acc[c + 2]);
+        acc[c + 3] = __builtin_fmaf(av[r], z4.w, acc[c + 3]);
+      }
+    }
+    if (first && tid < C) {
+#pragma unroll 8
+      for (int b = 0; b < nb; ++b) bsum += dzs[b * CM + tid];
     }
   }
 #pragma unroll
   for (int c = 0; c < CM; ++c) part[grp][lane][c] = acc[c];
   __syncthreads();
-
-  // 4. partials in group order, SGD step on W_L[d][c]
 #pragma unroll
   for (int q = 0; q < WPT; ++q) {
-    const int e = (int)threadIdx.x + 256 * q;
-    if (e < 64 * C) {
+    const int e = tid + 256 * q;
+    if (e < nw) {
       const int dl = e / C, c = e - dl * C;
       const float g = ((part[0][dl][c] + part[1][dl][c]) + part[2][dl][c]) + part[3][dl][c];
       float w = wv[q], u = uv[q];
       sgd_step(w, u, g, h);
       h.Wm[wbase + e] = w;
       h.Um[wbase + e] = u;
+      if (h.Wb) h.Wb[wbase + e] = f32_to_bf16(w);
     }
   }
   if (!first) return;  // uniform over the workgroup
-  if ((int)threadIdx.x < C) {
-    float bsum = 0.f;
-    for (int b = 0; b < B; ++b) bsum += dzs[b * C + threadIdx.x];
-    const long long o = (long long)k * h.sP + threadIdx.x;
-    float w = h.bsrc[(long long)k * h.sSrc + threadIdx.x], u = h.bias_u[o];
+  if (tid < C) {
+    const long long o = (long long)k * h.sP + tid;
+    float w = h.bsrc[(long long)k * h.sSrc + tid], u = h.bias_u[o];
     sgd_step(w, u, bsum, h);
     h.bias_w[o] = w;
     h.bias_u[o] = u;
   }
-  red[threadIdx.x] = (int)threadIdx.x < B ? rl : 0.f;
+  red[tid] = rl;
   __syncthreads();
   for (int w2 = 128; w2 > 0; w2 >>= 1) {
-    if ((int)threadIdx.x < w2) red[threadIdx.x] += red[threadIdx.x + w2];
+    if (tid < w2) red[tid] += red[tid + w2];
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     const float mean = red[0] / (float)B;
     if (h.loss) h.loss[k] = mean;
     // a non-finite loss raises the context's flag (a plain store: every
@@ -420,7 +343,7 @@ __global__ __launch_bounds__(256) void k_head_wgrad_vec(HeadArgs h) {
 // logits, the loss, dZ and the masked input gradient cost one memory round
 // trip. The loss and gradient formulas are those of k_head_fwd; only the
 // split of the logit sums over lanes differs (each lane's inputs in ascending
-// d, then the same xor butterfly).
+// d, then an xor butterfly).
 template <int C, int NJ>
 __global__ __launch_bounds__(256) void k_head_fwd_vec(HeadArgs h) {
   constexpr int RPW = 2;
@@ -683,23 +606,31 @@ __global__ __launch_bounds__(256) void k_head_fwd_bf16(HeadArgs h) {
   }
 }
 
-template <typename T, int CMAX>
+template <typename T, int CM>
 hipError_t launch_pair(const HeadArgs& h, hipStream_t s, int which) {
   const bool gather = h.gather != 0;  // the top layer is layer 1
   if (which == 0) {
-    dim3 grid((h.B + 7) / 8, h.K);  // 4 waves x 2 rows per workgroup
+    dim3 grid((h.B + head_rows<CM>() - 1) / head_rows<CM>(), h.K);
     if (gather)
-      hipLaunchKernelGGL((k_head_fwd<T, CMAX, true>), grid, dim3(256), 0, s, h);
+      hipLaunchKernelGGL((k_head_fwd<T, CM, true>), grid, dim3(256), 0, s, h);
     else
-      hipLaunchKernelGGL((k_head_fwd<T, CMAX, false>), grid, dim3(256), 0, s, h);
+      hipLaunchKernelGGL((k_head_fwd<T, CM, false>), grid, dim3(256), 0, s, h);
   } else {
     dim3 grid((h.D + 63) / 64, h.K);
     if (gather)
-      hipLaunchKernelGGL((k_head_wgrad<T, CMAX, true>), grid, dim3(256), 0, s, h);
+      hipLaunchKernelGGL((k_head_wgrad<T, CM, true>), grid, dim3(256), 0, s, h);
     else
-      hipLaunchKernelGGL((k_head_wgrad<T, CMAX, false>), grid, dim3(256), 0, s, h);
+      hipLaunchKernelGGL((k_head_wgrad<T, CM, false>), grid, dim3(256), 0, s, h);
   }
   return hipGetLastError();
+}
+
+// the smallest instance with room for C classes
+template <typename T>
+hipError_t launch_any(const HeadArgs& h, hipStream_t s, int which) {
+  if (h.C <= 12) return launch_pair<T, 12>(h, s, which);
+  if (h.C <= 16) return launch_pair<T, 16>(h, s, which);
+  return launch_pair<T, 32>(h, s, which);
 }
 
 bool al16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
@@ -731,25 +662,7 @@ hipError_t launch_head(int dtype, const HeadArgs& h, hipStream_t s, int which) {
     }
     return hipGetLastError();
   }
-  // one-round-trip weight gradient: fp32, up to 16 classes, 64-input slices
-  if (which == 1 && dtype == 0 && h.C <= 16 && h.D % 64 == 0 && h.B <= 128 &&
-      h.Wb == nullptr && (h.gather || h.sA % h.D == 0)) {
-    dim3 grid(h.D / 64, h.K);
-    if (h.C == 10 && h.gather)
-      hipLaunchKernelGGL((k_head_wgrad_vec<10, true>), grid, dim3(256), 0, s, h);
-    else if (h.C == 10)
-      hipLaunchKernelGGL((k_head_wgrad_vec<10, false>), grid, dim3(256), 0, s, h);
-    else if (h.gather)
-      hipLaunchKernelGGL((k_head_wgrad_vec<16, true>), grid, dim3(256), 0, s, h);
-    else
-      hipLaunchKernelGGL((k_head_wgrad_vec<16, false>), grid, dim3(256), 0, s, h);
-    return hipGetLastError();
-  }
-  if (dtype == 1)
-    return h.C <= 16 ? launch_pair<bf16_t, 16>(h, s, which)
-                     : launch_pair<bf16_t, 32>(h, s, which);
-  return h.C <= 16 ? launch_pair<float, 16>(h, s, which)
-                   : launch_pair<float, 32>(h, s, which);
+  return dtype == 1 ? launch_any<bf16_t>(h, s, which) : launch_any<float>(h, s, which);
 }
 
 }  // namespace
