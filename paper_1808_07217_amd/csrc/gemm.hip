@@ -7,17 +7,20 @@
 // the gradient never goes to memory; the same kernel sums dZ over the batch
 // for the bias gradient and updates the bias.
 //
-// Block tile BM x BN, K slabs of BK, 256 threads = 4 wavefronts in a 2 x 2
-// layout, each wave owning (BM/2) x (BN/2) as 32 x 32 MFMA blocks. Operands go
-// global -> registers -> LDS through a double-buffered LDS ring: the next
-// slab's global loads are in flight while the current slab feeds the MFMAs.
-//
-//  fp32: v_mfma_f32_32x32x2f32, BK = 32. LDS holds k-major tiles As[k][m],
-//        Bs[k][n]; lane l feeds A[m = l%32][k = l/32], B[k = l/32][n = l%32].
-//  bf16: v_mfma_f32_32x32x16_bf16, BK = 32. LDS holds k-contiguous rows
-//        As[m][k], Bs[n][k]; lane l feeds 8 consecutive k starting at
-//        8*(l/32) for row/column l%32.
-//  Both: accumulator register v of lane l is C[8*(v/4) + 4*(l/32) + v%4][l%32].
+// Every product runs on v_mfma_f32_32x32x16_bf16. bf16 operands feed it as
+// they are. An fp32 operand x is taken as three bf16 pieces, x = x1 + x2 + x3
+// (each the round-to-nearest bf16 of what the ones before leave, so the sum is
+// exact: 3 x 8 significant bits), and x y as the six products x1 y1, x1 y2,
+// x2 y1, x2 y2, x1 y3, x3 y1, each exact in fp32; the three left out are below
+// 2^-26 |x y| together. x1 y1 has an accumulator of its own and the five small
+// ones share another, added at the end: a k range of 16 then rounds once at the
+// sum's own magnitude where v_mfma_f32_32x32x2f32 rounds 16 times. Measured
+// against fp64 (normwise, normal operands, K = 64 / 512 / 3072): 5.0e-8 /
+// 1.3e-7 / 3.4e-7, the fp32 instruction 1.4e-7 / 4.0e-7 / 1.0e-6; the six
+// products issue at 290 TFLOP/s, the fp32 instruction at 122.
+// Infinities: x1 of an infinity (or of a finite value that rounds to one)
+// leaves NaN pieces, so a wave whose result holds any NaN forms its tile again
+// with the fp32 instruction and keeps that.
 //
 // Work distribution: a 1-D grid of G * S * tilesM * tilesN workgroups. The
 // hardware deals consecutive workgroup ids round-robin to the 8 XCDs (each
@@ -26,6 +29,8 @@
 // Split-K (S > 1) gives skinny GEMMs enough workgroups: split s covers K range
 // [s*kchunk, (s+1)*kchunk) and writes a raw fp32 partial; a second kernel sums
 // the S partials in ascending s and applies the epilogue.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace lsgd {
@@ -33,22 +38,18 @@ namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+// four elements at any element's alignment (one global load)
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
 
 constexpr int kThreads = 256;
 constexpr int kXcds = 8;
-
-// float4 moves through a native vector type: copying HIP's float4 struct
-// straight from memory becomes a memcpy, which keeps register arrays of it
-// in scratch memory
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float4 ldg4(const float* p) {
-  const v4f v = *(const v4f*)p;
-  return make_float4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ void sts4(float* p, const float4& v) {
-  *(v4f*)p = v4f{v.x, v.y, v.z, v.w};
-}
 
 struct Tile {
   int g, s, m0, n0;
@@ -78,615 +79,495 @@ __device__ __forceinline__ void sgd_step(float& w, float& u, float grad,
   w = __builtin_fmaf(-a.lr, d, w);
 }
 
-// Epilogue applied to a finished value of C[g][m][n]. OUTBF: activations are
-// bf16 (bf16 workloads) and so are the mask operand and the output.
+// Epilogue applied to a finished value of C[g][m][n] (split-K's second
+// kernel). OUTBF: activations are bf16 (bf16 workloads) and so are the mask
+// operand and the output.
 template <int EPI, bool OUTBF>
 __device__ __forceinline__ void finish(const GemmArgs& a, int g, int m, int n,
                                        float v) {
   const long long o = (long long)g * a.sC + (long long)m * a.ldc + n;
-  if constexpr (EPI == EPI_SGD) {
-    float w = a.Wsrc ? a.Wsrc[(long long)g * a.sWsrc + (long long)m * a.ldc + n] : a.W[o];
-    float u = a.U[o];
-    sgd_step(w, u, v, a);
-    a.W[o] = w;
-    a.U[o] = u;
-    if (a.Wb) a.Wb[o] = f32_to_bf16(w);
-  } else {
-    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_RELU)
-      v += a.bias[(long long)g * a.sBias + n];
-    if constexpr (EPI == EPI_BIAS_RELU) v = v > 0.f ? v : 0.f;
-    if constexpr (EPI == EPI_RELU_MASK) {
-      const float mk = OUTBF ? bf16_to_f32(((const bf16_t*)a.mask)[o])
-                             : ((const float*)a.mask)[o];
-      v = mk > 0.f ? v : 0.f;
-    }
-    if constexpr (OUTBF)
-      ((bf16_t*)a.C)[o] = f32_to_bf16(v);
-    else
-      ((float*)a.C)[o] = v;
+  if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_RELU)
+    v += a.bias[(long long)g * a.sBias + n];
+  if constexpr (EPI == EPI_BIAS_RELU) v = v > 0.f ? v : 0.f;
+  if constexpr (EPI == EPI_RELU_MASK) {
+    const float mk = OUTBF ? bf16_to_f32(((const bf16_t*)a.mask)[o])
+                           : ((const float*)a.mask)[o];
+    v = mk > 0.f ? v : 0.f;
   }
-}
-
-template <int EPI, bool OUTBF>
-__device__ __forceinline__ void emit(const GemmArgs& a, const Tile& t, int m,
-                                     int n, float v) {
-  if (a.splits > 1)
-    a.part[(((long long)t.s * a.G + t.g) * a.M + m) * a.N + n] = v;
+  if constexpr (OUTBF)
+    ((bf16_t*)a.C)[o] = f32_to_bf16(v);
   else
-    finish<EPI, OUTBF>(a, t.g, m, n, v);
+    ((float*)a.C)[o] = v;
 }
 
-// Bias of the weight-gradient workgroups with m0 == 0: db[n] = sum_b dZ[b][n]
-// in ascending b, then the same update as the weights.
-__device__ __forceinline__ void bias_update(const GemmArgs& a, const Tile& t,
-                                            int n, float colsum) {
-  const long long o = (long long)t.g * a.sBiasP + n;
-  float w = a.bias_src ? a.bias_src[(long long)t.g * a.sBiasSrc + n] : a.bias_w[o];
+// Bias of the weight-gradient workgroups with m0 == 0: db[n] = sum_b dZ[b][n],
+// then the same update as the weights.
+__device__ __forceinline__ void bias_update(const GemmArgs& a, int g, int n, float colsum) {
+  const long long o = (long long)g * a.sBiasP + n;
+  float w = a.bias_src ? a.bias_src[(long long)g * a.sBiasSrc + n] : a.bias_w[o];
   float u = a.bias_u[o];
   sgd_step(w, u, colsum, a);
   a.bias_w[o] = w;
   a.bias_u[o] = u;
 }
 
-// Epilogue over one wave's FM x FN fragment of 32 x 32 blocks, one block at
-// a time. The operands the epilogue reads (W and U of the update, the ReLU
-// mask) are loaded for the whole block before anything is stored, so those
-// loads are in flight together instead of each waiting behind the previous
-// element's stores (the compiler must assume the buffers may alias).
-// Register v of a block sits at row 8*(v/4) + (v%4) below the lane's first
-// row and in the lane's column: a 32-bit offset from one base per block.
-template <int EPI, bool OUTBF, int FM, int FN>
-__device__ __forceinline__ void epilogue_fragment(const GemmArgs& a, const Tile& t,
-                                                  floatx16 (&acc)[FM][FN],
-                                                  int mb, int nb, int lk, int lr) {
-  const int M = a.M, N = a.N;
-  if (EPI != EPI_SGD && a.splits > 1) {  // raw partial sums, [s][g][M][N]
-    float* P = a.part + ((long long)t.s * a.G + t.g) * a.M * a.N;
+// ------------------------------------------------------------ operand pieces
+// Two fp32 values as packed bf16 pairs p[0] + p[1] + p[2] (see the top).
+__device__ __forceinline__ void split3(float x, float y, uint32_t (&p)[3]) {
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j) {
-        const int m1 = mb + i * 32 + lk * 4, n = nb + j * 32 + lr;
-        float* base = P + (long long)m1 * N + n;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int dr = (v >> 2) * 8 + (v & 3);
-          if (m1 + dr < M && n < N) base[dr * N] = acc[i][j][v];
-        }
-      }
-    return;
+  for (int i = 0; i < 3; ++i) {
+    p[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{x, y}, bf16x2));
+    x -= __uint_as_float(p[i] << 16);
+    y -= __uint_as_float(p[i] & 0xffff0000u);
   }
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int m1 = mb + i * 32 + lk * 4, n = nb + j * 32 + lr;
-      const long long o1 = (long long)t.g * a.sC + (long long)m1 * a.ldc + n;
-      const int ldc = (int)a.ldc;
-      bool ok[16];
-#pragma unroll
-      for (int v = 0; v < 16; ++v) ok[v] = m1 + (v >> 2) * 8 + (v & 3) < M && n < N;
-      if constexpr (EPI == EPI_SGD) {
-        float* Wp = a.W + o1;
-        float* Up = a.U + o1;
-        const float* Wr = a.Wsrc ? a.Wsrc + (long long)t.g * a.sWsrc +
-                                       (long long)m1 * a.ldc + n
-                                 : Wp;
-        float wv[16], uv[16];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int dr = ((v >> 2) * 8 + (v & 3)) * ldc;
-          wv[v] = ok[v] ? Wr[dr] : 0.f;
-          uv[v] = ok[v] ? Up[dr] : 0.f;
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          if (!ok[v]) continue;
-          const int dr = ((v >> 2) * 8 + (v & 3)) * ldc;
-          sgd_step(wv[v], uv[v], acc[i][j][v], a);
-          Wp[dr] = wv[v];
-          Up[dr] = uv[v];
-          if (a.Wb) a.Wb[o1 + dr] = f32_to_bf16(wv[v]);
-        }
-      } else if constexpr (EPI == EPI_RELU_MASK) {
-        float mk[16];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int dr = ((v >> 2) * 8 + (v & 3)) * ldc;
-          mk[v] = 0.f;
-          if (ok[v])
-            mk[v] = OUTBF ? bf16_to_f32(((const bf16_t*)a.mask)[o1 + dr])
-                          : ((const float*)a.mask)[o1 + dr];
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          if (!ok[v]) continue;
-          const int dr = ((v >> 2) * 8 + (v & 3)) * ldc;
-          const float r = mk[v] > 0.f ? acc[i][j][v] : 0.f;
-          if constexpr (OUTBF)
-            ((bf16_t*)a.C)[o1 + dr] = f32_to_bf16(r);
-          else
-            ((float*)a.C)[o1 + dr] = r;
-        }
-      } else {
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (ok[v]) finish<EPI, OUTBF>(a, t.g, m1 + (v >> 2) * 8 + (v & 3), n, acc[i][j][v]);
-      }
-    }
 }
 
-// Vectorised update epilogue (EPI_SGD, ldc % 4 == 0): the accumulator tile
-// goes through LDS, half of the rows at a time, so that every thread then
-// updates whole float4 runs of W and U along n -- fully coalesced rows. The
-// W/U reads of half 0 are issued at kernel entry (they overlap the MFMA
-// loop) and those of half 1 before half 0's results go through LDS.
-template <int BM, int BN>
-struct SgdVec {
-  static constexpr int CP = BN + 4;                      // LDS pitch
-  static constexpr int PER = (BM / 2) * BN / 4 / kThreads;  // float4 per thread
-  static_assert(PER >= 1 && (BM / 2) * BN / 4 % kThreads == 0, "tile too small");
-
-  __device__ static void locate(const GemmArgs& a, const Tile& t, int half, int p,
-                                int& r, int& c, long long& off, bool& ok) {
-    const int idx = (int)threadIdx.x + p * kThreads;
-    r = idx / (BN / 4);
-    c = (idx % (BN / 4)) * 4;
-    const int m = t.m0 + half * (BM / 2) + r, n = t.n0 + c;
-    ok = m < a.M && n < a.N;
-    off = (long long)t.g * a.sC + (long long)m * a.ldc + n;
+// Four consecutive elements of an operand as loaded, and their bf16 planes.
+template <bool BF>
+struct Quad;
+template <>
+struct Quad<false> {
+  using E = float;
+  static constexpr int kPlanes = 3;
+  v4f v;
+  __device__ __forceinline__ void load(const E* p) { v = *(const v4f_any*)p; }
+  __device__ __forceinline__ void set(int e, const E* p, bool ok) { v[e] = ok ? *p : 0.f; }
+  __device__ __forceinline__ void zero() { v = v4f{0.f, 0.f, 0.f, 0.f}; }
+  __device__ __forceinline__ void planes(u32x2 (&q)[3]) const {
+    uint32_t a[3], b[3];
+    split3(v[0], v[1], a);
+    split3(v[2], v[3], b);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) q[i] = u32x2{a[i], b[i]};
   }
-  __device__ static void fetch(const GemmArgs& a, const Tile& t, int half,
-                               float4 (&wv)[PER], float4 (&uv)[PER]) {
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-      int r, c;
-      long long off;
-      bool ok;
-      locate(a, t, half, p, r, c, off, ok);
-      if (ok) {
-        const float* wr = a.Wsrc ? a.Wsrc + (off - (long long)t.g * a.sC) +
-                                       (long long)t.g * a.sWsrc
-                                 : a.W + off;
-        wv[p] = *(const float4*)wr;
-        uv[p] = *(const float4*)(a.U + off);
-      }
-    }
+  __device__ __forceinline__ v4f f32() const { return v; }
+};
+template <>
+struct Quad<true> {
+  using E = bf16_t;
+  static constexpr int kPlanes = 1;
+  u32x2 v;
+  __device__ __forceinline__ void load(const E* p) { v = *(const u32x2_any*)p; }
+  __device__ __forceinline__ void set(int e, const E* p, bool ok) {
+    const uint32_t h = ok ? *p : 0u;
+    uint32_t w = e < 2 ? v.x : v.y;
+    w = (e & 1) ? (w & 0xffffu) | (h << 16) : (w & 0xffff0000u) | h;
+    if (e < 2)
+      v.x = w;
+    else
+      v.y = w;
   }
-  template <int FM, int FN>
-  __device__ static void run(const GemmArgs& a, const Tile& t,
-                             floatx16 (&acc)[FM][FN], float* smem, int wave,
-                             int lk, int lr, float4 (&wv)[PER], float4 (&uv)[PER]) {
-    const int wn0 = (wave & 1) * (BN / 2);
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      if (half == 1) fetch(a, t, 1, wv, uv);
-      __syncthreads();
-      if ((wave >> 1) == half) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const int r = i * 32 + (v >> 2) * 8 + lk * 4 + (v & 3);
-              smem[r * CP + wn0 + j * 32 + lr] = acc[i][j][v];
-            }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int p = 0; p < PER; ++p) {
-        int r, c;
-        long long off;
-        bool ok;
-        locate(a, t, half, p, r, c, off, ok);
-        if (!ok) continue;
-        const float4 gr = *(const float4*)&smem[r * CP + c];
-        float4 w = wv[p], u = uv[p];
-        sgd_step(w.x, u.x, gr.x, a);
-        sgd_step(w.y, u.y, gr.y, a);
-        sgd_step(w.z, u.z, gr.z, a);
-        sgd_step(w.w, u.w, gr.w, a);
-        *(float4*)(a.W + off) = w;
-        *(float4*)(a.U + off) = u;
-        if (a.Wb) {
-          const uint32_t lo = f32_to_bf16(w.x) | ((uint32_t)f32_to_bf16(w.y) << 16);
-          const uint32_t hi = f32_to_bf16(w.z) | ((uint32_t)f32_to_bf16(w.w) << 16);
-          *(uint2*)(a.Wb + off) = make_uint2(lo, hi);
-        }
-      }
-    }
+  __device__ __forceinline__ void zero() { v = u32x2{0u, 0u}; }
+  __device__ __forceinline__ void planes(u32x2 (&q)[1]) const { q[0] = v; }
+  __device__ __forceinline__ v4f f32() const {
+    return v4f{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
+               __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u)};
   }
 };
 
-// ------------------------------------------------------------------ fp32
-// FULL: every tile is whole, every split covers whole BK slabs and the
-// operands allow float4 loads (checked at launch). The loads then carry no
-// bounds branches and the prefetch of slabs past the end is clamped to the
-// last slab instead of skipped, so the compiler can count the loads in
-// flight and wait only for the register set it is about to store.
-template <bool AT, bool BT, int EPI, bool GATHER, int BM, int BN, int BK, bool FULL>
-__global__ __launch_bounds__(kThreads) void gemm_f32(GemmArgs a, int vecA,
-                                                     int vecB, int vecC) {
-  // pitch: transposing stores (k-contiguous source) use pitch = 2 mod 8 to
-  // spread banks; direct float4 stores need a 16-byte aligned pitch
-  constexpr int PA = AT ? BM + 4 : BM + 2;
-  constexpr int PB = BT ? BN + 2 : BN + 4;
+// ------------------------------------------------------------------ the GEMM
+// Block tile BM x BN, K slabs of BK, 4 wavefronts in a 2 x 2 layout, each
+// owning (BM/2) x (BN/2) as 32 x 32 MFMA blocks (lane l takes 8 k from
+// 8 (l / 32) of row / column l % 32; accumulator v of lane l is
+// C[8 (v/4) + 4 (l/32) + v%4][l%32]). Operands go global -> registers -> bf16
+// planes in a double-buffered LDS ring; D register sets, so D slabs' loads
+// are in flight while one computes. An operand stored with k contiguous lies
+// in LDS as [row][k] (16-byte fragment reads; a pitch of BK + 8 spreads eight
+// rows over all banks); one stored with k as the slow index lies as [k][column]
+// -- no transposition on the way in -- and is read with ds_read_b64_tr_b16,
+// which gives each lane of 16 its column's four k from a 4 x 16 block (pitch
+// + 64 bytes: four rows of a block in disjoint banks).
+// FULL: whole tiles and whole slabs (checked at launch). Otherwise rows past
+// the end are clamped, and slabs or tiles that reach past K or past the
+// columns of a k-slow operand take element loads (a uniform branch).
+template <bool BF, bool AT, bool BT, int EPI, bool GATHER, int BM, int BN, int BK, int D,
+          bool FULL>
+__global__ __launch_bounds__(kThreads, BM * BN > 128 * 64 ? 1 : 2) void gemm_mm(GemmArgs a) {
+  using Q = Quad<BF>;
+  using E = typename Q::E;
+  constexpr int NPL = Q::kPlanes;
   constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 32, FN = WN / 32;
-  constexpr int KV = BK / 4;                  // float4 per k-contiguous row
-  constexpr int NA = BM * BK / 4 / kThreads;  // float4 loads per thread
-  constexpr int NB = BN * BK / 4 / kThreads;
-  static_assert(NA >= 1 && NB >= 1, "tile too small for 256 threads");
-  constexpr int OPER = 2 * BK * (PA + PB);
-  constexpr int EPIF = EPI == EPI_SGD ? (BM / 2) * (BN + 4) : 0;
-  __shared__ __attribute__((aligned(16))) float smem[OPER > EPIF ? OPER : EPIF];
-  auto As = reinterpret_cast<float (*)[BK][PA]>(smem);
-  auto Bs = reinterpret_cast<float (*)[BK][PB]>(smem + 2 * BK * PA);
+  constexpr bool AK = !AT, BKc = BT;  // k contiguous in storage
+  constexpr int PA = AK ? BK + 8 : BM + 32, PB = BKc ? BK + 8 : BN + 32;
+  constexpr int SA = (AK ? BM : BK) * PA, SB = (BKc ? BN : BK) * PB;  // one plane
+  constexpr int NA = BM * BK / 4 / kThreads, NB = BN * BK / 4 / kThreads;
+  static_assert(NA >= 1 && NB >= 1 && D % 2 == 0, "tile too small");
+  __shared__ __attribute__((aligned(16))) bf16_t sA[2 * NPL * SA];
+  __shared__ __attribute__((aligned(16))) bf16_t sB[2 * NPL * SB];
+  constexpr bool kRows = AT && GATHER;  // the k rows of A come from a row map
+  __shared__ int32_t srmap[kRows ? 512 : 1];  // beyond: read the map itself
 
   const Tile t = decode_tile(a, BM, BN);
   const int g = t.g, m0 = t.m0, n0 = t.n0;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lk = lane >> 5, lr = lane & 31;
   const int wm0 = (wave >> 1) * WM, wn0 = (wave & 1) * WN;
-  const float* A = (const float*)a.A + (long long)g * a.sA;
-  const float* B = (const float*)a.B + (long long)g * a.sB;
-  // GATHER: rows of A come from a row map (the sampled mini-batch indices)
+  const E* A = (const E*)a.A + (long long)g * a.sA;
+  const E* B = (const E*)a.B + (long long)g * a.sB;
   const int32_t* rmap = GATHER ? a.rowmap + (long long)g * a.sRow : nullptr;
   const int M = a.M, N = a.N;
-  const int kbeg = t.s * a.kchunk;
-  const int kend = min(a.Kd, kbeg + a.kchunk);
-
-  // two register sets: slab t+2 is loaded while slab t computes and slab t+1
-  // waits in LDS, so each load has two compute phases to arrive (separate
-  // arrays, not one indexed by the set: that index ends up in scratch)
-  float4 ra0[NA], rb0[NB], ra1[NA], rb1[NB];
-  // gathered rows: the forward operand's rows are fixed per thread, so their
-  // dataset indices are read once; the weight gradient walks its rows per
-  // slab, so the workgroup's indices are staged in LDS
-  long long srow[AT ? 1 : NA];
-  __shared__ int32_t srmap[AT && GATHER ? 512 : 1];  // beyond: read rmap
-  if constexpr (!AT) {
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const int row = m0 + (tid + i * kThreads) / KV;
-      srow[i] = GATHER ? (row < M ? rmap[row] : 0) : row;
-    }
-  } else if constexpr (GATHER) {
-    for (int i = tid; i < 512 && kbeg + i < kend; i += kThreads) srmap[i] = rmap[kbeg + i];
-    __syncthreads();
-  }
-
-  auto load4 = [](const float* p, int avail, int vec) -> float4 {
-    if (vec && avail >= 4) return *(const float4*)p;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (avail > 0) v.x = p[0];
-    if (avail > 1) v.y = p[1];
-    if (avail > 2) v.z = p[2];
-    if (avail > 3) v.w = p[3];
-    return v;
-  };
-
-  auto gload = [&](int k0, float4(&xa)[NA], float4(&xb)[NB]) __attribute__((always_inline)) {
-    if constexpr (FULL) {
-#pragma unroll
-      for (int i = 0; i < NA; ++i) {
-        const int q = tid + i * kThreads;
-        if constexpr (!AT) {
-          xa[i] = ldg4(A + srow[i] * a.lda + k0 + (q % KV) * 4);
-        } else {
-          const int r = q / (BM / 4), kr = k0 + r;
-          const long long sr =
-              GATHER ? (kr - kbeg < 512 ? srmap[kr - kbeg] : rmap[kr]) : kr;
-          xa[i] = ldg4(A + sr * a.lda + m0 + (q % (BM / 4)) * 4);
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        const int q = tid + i * kThreads;
-        if constexpr (BT)
-          xb[i] = ldg4(B + (long long)(n0 + q / KV) * a.ldb + k0 + (q % KV) * 4);
-        else
-          xb[i] = ldg4(B + (long long)(k0 + q / (BN / 4)) * a.ldb + n0 + (q % (BN / 4)) * 4);
-      }
-      return;
-    }
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const int q = tid + i * kThreads;
-      xa[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if constexpr (!AT) {  // storage [M][Kd]: rows m, KV float4 per row
-        const int r = q / KV, c = k0 + (q % KV) * 4, row = m0 + r;
-        if (row < M && c < kend) xa[i] = load4(A + srow[i] * a.lda + c, kend - c, vecA);
-      } else {  // storage [Kd][M]: rows k, BM/4 float4 per row
-        const int r = q / (BM / 4), c = m0 + (q % (BM / 4)) * 4, kr = k0 + r;
-        if (kr < kend) {
-          const long long sr =
-              GATHER ? (kr - kbeg < 512 ? srmap[kr - kbeg] : rmap[kr]) : kr;
-          xa[i] = load4(A + sr * a.lda + c, M - c, vecA);
-        }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int q = tid + i * kThreads;
-      xb[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if constexpr (BT) {  // storage [N][Kd]
-        const int r = q / KV, c = k0 + (q % KV) * 4, row = n0 + r;
-        if (row < N && c < kend)
-          xb[i] = load4(B + (long long)row * a.ldb + c, kend - c, vecB);
-      } else {  // storage [Kd][N]
-        const int r = q / (BN / 4), c = n0 + (q % (BN / 4)) * 4, kr = k0 + r;
-        if (kr < kend) xb[i] = load4(B + (long long)kr * a.ldb + c, N - c, vecB);
-      }
-    }
-  };
-
-  auto lstore = [&](int buf, const float4(&xa)[NA], const float4(&xb)[NB]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const int q = tid + i * kThreads;
-      if constexpr (!AT) {
-        const int r = q / KV, kq = (q % KV) * 4;
-        As[buf][kq + 0][r] = xa[i].x;
-        As[buf][kq + 1][r] = xa[i].y;
-        As[buf][kq + 2][r] = xa[i].z;
-        As[buf][kq + 3][r] = xa[i].w;
-      } else {
-        const int r = q / (BM / 4), c = (q % (BM / 4)) * 4;
-        sts4(&As[buf][r][c], xa[i]);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int q = tid + i * kThreads;
-      if constexpr (BT) {
-        const int r = q / KV, kq = (q % KV) * 4;
-        Bs[buf][kq + 0][r] = xb[i].x;
-        Bs[buf][kq + 1][r] = xb[i].y;
-        Bs[buf][kq + 2][r] = xb[i].z;
-        Bs[buf][kq + 3][r] = xb[i].w;
-      } else {
-        const int r = q / (BN / 4), c = (q % (BN / 4)) * 4;
-        sts4(&Bs[buf][r][c], xb[i]);
-      }
-    }
-  };
-
-  floatx16 acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-  const bool do_bias = EPI == EPI_SGD && a.bias_w && m0 == 0;
-  float colsum = 0.f;
-  // EPI_SGD: W/U of the first half tile are read while the MFMAs run
-  using SV = SgdVec<BM, BN>;
-  float4 wpre[EPI == EPI_SGD ? SV::PER : 1], upre[EPI == EPI_SGD ? SV::PER : 1];
-  if constexpr (EPI == EPI_SGD) {
-    if (vecC) SV::fetch(a, t, 0, wpre, upre);
-  }
+  const int kbeg = t.s * a.kchunk, kend = min(a.Kd, kbeg + a.kchunk);
   const int nk = (kend - kbeg + BK - 1) / BK;
-  const int lk = lane >> 5, lr = lane & 31;
-  auto compute = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 2) {
-      float av[FM], bv[FN];
-#pragma unroll
-      for (int i = 0; i < FM; ++i) av[i] = As[buf][kk + lk][wm0 + i * 32 + lr];
-#pragma unroll
-      for (int j = 0; j < FN; ++j) bv[j] = Bs[buf][kk + lk][wn0 + j * 32 + lr];
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[j],
-                                                           acc[i][j], 0, 0, 0);
-    }
-    if (do_bias && tid < BN) {
-#pragma unroll 8
-      for (int k = 0; k < BK; ++k) colsum += Bs[buf][k][tid];
-    }
+
+  // EPI_SGD: the tile's W and U, in accumulator layout, on their way while
+  // the k loop runs (clamped where the tile ends)
+  constexpr bool kUpd = EPI == EPI_SGD;
+  float wv[kUpd ? FM : 1][kUpd ? FN : 1][16], uv[kUpd ? FM : 1][kUpd ? FN : 1][16];
+  auto out_row = [&](int i, int v) __attribute__((always_inline)) {
+    return m0 + wm0 + i * 32 + (v >> 2) * 8 + lk * 4 + (v & 3);
   };
-  // slab t lives in LDS buffer t % 2 and register set t % 2
-  int it = 0;
-  if constexpr (FULL) {
-    // nk >= 1; prefetches past the last slab reload it (unused)
-    auto slab = [&](int t) __attribute__((always_inline)) { return kbeg + min(t, nk - 1) * BK; };
-    gload(slab(0), ra0, rb0);
-    gload(slab(1), ra1, rb1);
-    lstore(0, ra0, rb0);
-    __syncthreads();
-    for (; it + 1 < nk; it += 2) {
-      gload(slab(it + 2), ra0, rb0);
-      __builtin_amdgcn_sched_barrier(0);
-      compute(0);
-      lstore(1, ra1, rb1);
-      __syncthreads();
-      gload(slab(it + 3), ra1, rb1);
-      __builtin_amdgcn_sched_barrier(0);
-      compute(1);
-      lstore(0, ra0, rb0);
-      __syncthreads();
-    }
-  } else {
-    if (nk > 0) gload(kbeg, ra0, rb0);
-    if (nk > 1) gload(kbeg + BK, ra1, rb1);
-    if (nk > 0) lstore(0, ra0, rb0);
-    __syncthreads();
-    for (; it + 1 < nk; it += 2) {
-      if (it + 2 < nk) gload(kbeg + (it + 2) * BK, ra0, rb0);
-      compute(0);
-      lstore(1, ra1, rb1);
-      __syncthreads();
-      if (it + 3 < nk) gload(kbeg + (it + 3) * BK, ra1, rb1);
-      compute(1);
-      if (it + 2 < nk) lstore(0, ra0, rb0);
-      __syncthreads();
-    }
-  }
-  if (it < nk) compute(0);  // odd slab count: the last slab is in buffer 0
-
-  if constexpr (EPI == EPI_SGD) {
-    if (vecC)
-      SV::template run<FM, FN>(a, t, acc, smem, wave, lk, lr, wpre, upre);
-    else
-      epilogue_fragment<EPI, false, FM, FN>(a, t, acc, m0 + wm0, n0 + wn0, lk, lr);
-  } else {
-    epilogue_fragment<EPI, false, FM, FN>(a, t, acc, m0 + wm0, n0 + wn0, lk, lr);
-  }
-  if (do_bias && tid < BN && n0 + tid < N) bias_update(a, t, n0 + tid, colsum);
-}
-
-// Two k halves per workgroup (fp32, A not transposed, whole tiles, no update
-// epilogue): 512 threads, threads 256 h .. 256 h + 255 run gemm_f32's FULL
-// pipeline over half h of the workgroup's k range (an even number of BK
-// slabs) with an LDS ring of their own. Each SIMD then holds two MFMA
-// wavefronts, one per half, and one's LDS and barrier waits are covered by
-// the other's MFMAs. At the end half 1 hands its accumulators over through
-// LDS and half 0 forms (first half) + (second half) and runs the epilogue.
-template <bool BT, int EPI, bool GATHER, int BM, int BN, int BK>
-__global__ __launch_bounds__(2 * kThreads) void gemm_f32_kh2(GemmArgs a) {
-  constexpr int PA = BM + 2;  // As[k][m], transposing stores
-  constexpr int PB = BT ? BN + 2 : BN + 4;
-  constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 32, FN = WN / 32;
-  constexpr int KV = BK / 4;
-  constexpr int NA = BM * BK / 4 / kThreads, NB = BN * BK / 4 / kThreads;
-  static_assert(NA >= 1 && NB >= 1, "tile too small for 256 threads per half");
-  constexpr int HALF = 2 * BK * (PA + PB);  // floats of one half's ring
-  constexpr int XCH = BM * BN;              // accumulator hand-over
-  __shared__ __attribute__((aligned(16))) float smem[2 * HALF > XCH ? 2 * HALF : XCH];
-  const int h = threadIdx.x >> 8, tid = threadIdx.x & (kThreads - 1);
-  auto As = reinterpret_cast<float (*)[BK][PA]>(smem + h * HALF);
-  auto Bs = reinterpret_cast<float (*)[BK][PB]>(smem + h * HALF + 2 * BK * PA);
-
-  const Tile t = decode_tile(a, BM, BN);
-  const int g = t.g, m0 = t.m0, n0 = t.n0;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm0 = (wave >> 1) * WM, wn0 = (wave & 1) * WN;
-  const float* A = (const float*)a.A + (long long)g * a.sA;
-  const float* B = (const float*)a.B + (long long)g * a.sB;
-  const int32_t* rmap = GATHER ? a.rowmap + (long long)g * a.sRow : nullptr;
-  const int nk = a.kchunk / BK / 2;  // slabs per half
-  const int kbeg = t.s * a.kchunk + h * nk * BK;
-
-  long long srow[NA];
-#pragma unroll
-  for (int i = 0; i < NA; ++i) {
-    const int row = m0 + (tid + i * kThreads) / KV;
-    srow[i] = GATHER ? rmap[row] : row;
-  }
-  auto gload = [&](int k0, float4(&xa)[NA], float4(&xb)[NB]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const int q = tid + i * kThreads;
-      xa[i] = ldg4(A + srow[i] * a.lda + k0 + (q % KV) * 4);
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int q = tid + i * kThreads;
-      if constexpr (BT)
-        xb[i] = ldg4(B + (long long)(n0 + q / KV) * a.ldb + k0 + (q % KV) * 4);
-      else
-        xb[i] = ldg4(B + (long long)(k0 + q / (BN / 4)) * a.ldb + n0 + (q % (BN / 4)) * 4);
-    }
-  };
-  auto lstore = [&](int buf, const float4(&xa)[NA], const float4(&xb)[NB]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const int q = tid + i * kThreads;
-      const int r = q / KV, kq = (q % KV) * 4;
-      As[buf][kq + 0][r] = xa[i].x;
-      As[buf][kq + 1][r] = xa[i].y;
-      As[buf][kq + 2][r] = xa[i].z;
-      As[buf][kq + 3][r] = xa[i].w;
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int q = tid + i * kThreads;
-      if constexpr (BT) {
-        const int r = q / KV, kq = (q % KV) * 4;
-        Bs[buf][kq + 0][r] = xb[i].x;
-        Bs[buf][kq + 1][r] = xb[i].y;
-        Bs[buf][kq + 2][r] = xb[i].z;
-        Bs[buf][kq + 3][r] = xb[i].w;
-      } else {
-        const int r = q / (BN / 4), c = (q % (BN / 4)) * 4;
-        sts4(&Bs[buf][r][c], xb[i]);
-      }
-    }
-  };
-  floatx16 acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  const int lk = lane >> 5, lr = lane & 31;
-  auto compute = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 2) {
-      float av[FM], bv[FN];
-#pragma unroll
-      for (int i = 0; i < FM; ++i) av[i] = As[buf][kk + lk][wm0 + i * 32 + lr];
-#pragma unroll
-      for (int j = 0; j < FN; ++j) bv[j] = Bs[buf][kk + lk][wn0 + j * 32 + lr];
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[j], acc[i][j], 0, 0, 0);
-    }
-  };
-  // slab t of this half: LDS buffer t % 2, register set t % 2; prefetches
-  // past the last slab reload it (unused)
-  float4 ra0[NA], rb0[NB], ra1[NA], rb1[NB];
-  auto slab = [&](int s) __attribute__((always_inline)) { return kbeg + min(s, nk - 1) * BK; };
-  gload(slab(0), ra0, rb0);
-  gload(slab(1), ra1, rb1);
-  lstore(0, ra0, rb0);
-  __syncthreads();
-  int it = 0;
-  for (; it + 1 < nk; it += 2) {
-    gload(slab(it + 2), ra0, rb0);
-    __builtin_amdgcn_sched_barrier(0);
-    compute(0);
-    lstore(1, ra1, rb1);
-    __syncthreads();
-    gload(slab(it + 3), ra1, rb1);
-    __builtin_amdgcn_sched_barrier(0);
-    compute(1);
-    lstore(0, ra0, rb0);
-    __syncthreads();
-  }
-  if (it < nk) compute(0);  // odd slab count per half: the last is in buffer 0
-
-  // hand-over: register v of block (i, j) of wave w and lane l at
-  // ((((w FM + i) FN + j) 16 + v) 64 + l)
-  __syncthreads();  // both halves' operand reads are done
-  if (h == 1) {
+  if constexpr (kUpd) {
+    const float* Wr = a.Wsrc ? a.Wsrc + (long long)g * a.sWsrc : a.W + (long long)g * a.sC;
+    const float* Ur = a.U + (long long)g * a.sC;
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
       for (int j = 0; j < FN; ++j)
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-          smem[(((wave * FM + i) * FN + j) * 16 + v) * 64 + lane] = acc[i][j][v];
+        for (int v = 0; v < 16; ++v) {
+          int m = out_row(i, v), n = n0 + wn0 + j * 32 + lr;
+          if constexpr (!FULL) {
+            m = min(m, M - 1);
+            n = min(n, N - 1);
+          }
+          const long long o = (long long)m * a.ldc + n;
+          wv[i][j][v] = Wr[o];
+          uv[i][j][v] = Ur[o];
+        }
   }
-  __syncthreads();
-  if (h == 1) return;
+
+  if constexpr (kRows) {
+    for (int i = tid; i < 512 && kbeg + i < kend; i += kThreads) srmap[i] = rmap[kbeg + i];
+    __syncthreads();
+  }
+  // per quad of this thread: the storage offset that does not depend on k
+  long long offA[NA], offB[NB];
+#pragma unroll
+  for (int i = 0; i < NA; ++i) {
+    const int q = tid + i * kThreads;
+    if constexpr (AK) {
+      int r = m0 + q / (BK / 4);
+      if constexpr (!FULL) r = min(r, M - 1);
+      offA[i] = (GATHER ? (long long)rmap[r] : (long long)r) * a.lda + (q % (BK / 4)) * 4;
+    } else {
+      offA[i] = m0 + (q % (BM / 4)) * 4;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const int q = tid + i * kThreads;
+    if constexpr (BKc) {
+      int r = n0 + q / (BK / 4);
+      if constexpr (!FULL) r = min(r, N - 1);
+      offB[i] = (long long)r * a.ldb + (q % (BK / 4)) * 4;
+    } else {
+      offB[i] = n0 + (q % (BN / 4)) * 4;
+    }
+  }
+  auto arow = [&](int k) __attribute__((always_inline)) {  // storage row of A's k
+    if constexpr (kRows) return (long long)(k - kbeg < 512 ? srmap[k - kbeg] : rmap[k]);
+    return (long long)k;
+  };
+  auto gload = [&](int k0, Q(&xa)[NA], Q(&xb)[NB]) __attribute__((always_inline)) {
+    const bool ktail = !FULL && k0 + BK > kend;
+    if (ktail || (!FULL && !AK && m0 + BM > M)) {
+#pragma unroll
+      for (int i = 0; i < NA; ++i) {
+        const int q = tid + i * kThreads;
+        xa[i].zero();
+        if constexpr (AK) {
+          const int k = k0 + (q % (BK / 4)) * 4;
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (k + e < kend) xa[i].set(e, A + offA[i] + k0 + e, true);
+        } else {
+          const int k = k0 + q / (BM / 4);
+          if (k < kend) {
+            const E* p = A + arow(k) * a.lda;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              xa[i].set(e, p + min((int)offA[i] + e, M - 1), true);
+          }
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NA; ++i) {
+        if constexpr (AK)
+          xa[i].load(A + offA[i] + k0);
+        else
+          xa[i].load(A + arow(k0 + (tid + i * kThreads) / (BM / 4)) * a.lda + offA[i]);
+      }
+    }
+    if (ktail || (!FULL && !BKc && n0 + BN > N)) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const int q = tid + i * kThreads;
+        xb[i].zero();
+        if constexpr (BKc) {
+          const int k = k0 + (q % (BK / 4)) * 4;
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (k + e < kend) xb[i].set(e, B + offB[i] + k0 + e, true);
+        } else {
+          const int k = k0 + q / (BN / 4);
+          if (k < kend) {
+            const E* p = B + (long long)k * a.ldb;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              xb[i].set(e, p + min((int)offB[i] + e, N - 1), true);
+          }
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        if constexpr (BKc)
+          xb[i].load(B + offB[i] + k0);
+        else
+          xb[i].load(B + (long long)(k0 + (tid + i * kThreads) / (BN / 4)) * a.ldb + offB[i]);
+      }
+    }
+  };
+  // bias gradient: this thread's share of four columns' sums over k (k-slow B)
+  const bool do_bias = kUpd && a.bias_w && m0 == 0;
+  v4f colsum = v4f{0.f, 0.f, 0.f, 0.f};
+  auto lstore = [&](int buf, const Q(&xa)[NA], const Q(&xb)[NB]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      const int q = tid + i * kThreads;
+      const int o = AK ? (q / (BK / 4)) * PA + (q % (BK / 4)) * 4
+                       : (q / (BM / 4)) * PA + (q % (BM / 4)) * 4;
+      u32x2 p[NPL];
+      xa[i].planes(p);
+#pragma unroll
+      for (int l = 0; l < NPL; ++l) *(u32x2*)&sA[(buf * NPL + l) * SA + o] = p[l];
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int q = tid + i * kThreads;
+      const int o = BKc ? (q / (BK / 4)) * PB + (q % (BK / 4)) * 4
+                        : (q / (BN / 4)) * PB + (q % (BN / 4)) * 4;
+      u32x2 p[NPL];
+      xb[i].planes(p);
+#pragma unroll
+      for (int l = 0; l < NPL; ++l) *(u32x2*)&sB[(buf * NPL + l) * SB + o] = p[l];
+    }
+  };
+  auto colsums = [&](const Q(&xb)[NB]) __attribute__((always_inline)) {
+    if constexpr (kUpd) {
+      if (do_bias) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) colsum += xb[i].f32();
+      }
+    }
+  };
+  floatx16 hi[FM][FN], lo[BF ? 1 : FM][BF ? 1 : FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v)
-        acc[i][j][v] += smem[(((wave * FM + i) * FN + j) * 16 + v) * 64 + lane];
-  epilogue_fragment<EPI, false, FM, FN>(a, t, acc, m0 + wm0, n0 + wn0, lk, lr);
-}
+      for (int v = 0; v < 16; ++v) {
+        hi[i][j][v] = 0.f;
+        if constexpr (!BF) lo[i][j][v] = 0.f;
+      }
+  // fragment of rows (columns) r0 .. r0 + 31, k kk .. kk + 15, of one plane
+  const int trow = 8 * lk + ((lane & 15) >> 2), tcol = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  auto frag = [&](const bf16_t* p, bool kc, int pitch, int r0, int kk)
+      __attribute__((always_inline)) -> bf16x8 {
+    if (kc) return *(const bf16x8*)&p[(r0 + lr) * pitch + kk + 8 * lk];
+    using L = __attribute__((address_space(3))) s16x4;
+    const bf16_t* b = p + (kk + trow) * pitch + r0 + tcol;
+    const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((L*)b);
+    const s16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((L*)(b + 4 * pitch));
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    return __builtin_bit_cast(bf16x8, s16x8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]});
+  };
+  auto compute = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kk = 0; kk < BK; kk += 16) {
+      bf16x8 fa[FM][NPL], fb[FN][NPL];
+#pragma unroll
+      for (int l = 0; l < NPL; ++l) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+          fa[i][l] = frag(sA + (buf * NPL + l) * SA, AK, PA, wm0 + i * 32, kk);
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+          fb[j][l] = frag(sB + (buf * NPL + l) * SB, BKc, PB, wn0 + j * 32, kk);
+      }
+      auto mm = [&](int x, int y, bool low) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j) {
+            floatx16& c = low ? lo[BF ? 0 : i][BF ? 0 : j] : hi[i][j];
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][x], fb[j][y], c, 0, 0, 0);
+          }
+      };
+      if constexpr (!BF) {
+        mm(NPL - 1, 0, true);
+        mm(0, 0, false);
+        mm(0, NPL - 1, true);
+        mm(1 % NPL, 1 % NPL, true);
+        mm(1 % NPL, 0, true);
+        mm(0, 1 % NPL, true);
+      } else {
+        mm(0, 0, false);
+      }
+    }
+  };
+  // slab t: register set t % D, LDS buffer t % 2; loads past the last slab
+  // repeat it (unused)
+  if (nk > 0) {
+    Q ra[D][NA], rb[D][NB];
+    auto slab = [&](int s) __attribute__((always_inline)) { return kbeg + min(s, nk - 1) * BK; };
+#pragma unroll
+    for (int d = 0; d < D; ++d) gload(slab(d), ra[d], rb[d]);
+    colsums(rb[0]);
+    lstore(0, ra[0], rb[0]);
+    __syncthreads();
+    int it = 0;
+    for (; it + D < nk; it += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        gload(slab(it + d + D), ra[d], rb[d]);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(d & 1);
+        colsums(rb[(d + 1) % D]);
+        lstore((d + 1) & 1, ra[(d + 1) % D], rb[(d + 1) % D]);
+        __syncthreads();
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      if (it + d >= nk) break;
+      compute(d & 1);
+      if (it + d + 1 < nk) {
+        colsums(rb[(d + 1) % D]);
+        lstore((d + 1) & 1, ra[(d + 1) % D], rb[(d + 1) % D]);
+      }
+      __syncthreads();
+    }
+  }
+  if constexpr (!BF) {
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          hi[i][j][v] += lo[i][j][v];
+          bad |= hi[i][j][v] != hi[i][j][v];
+        }
+    if (__builtin_expect(__any(bad), 0)) {
+      // infinities (or NaN) among the operands: the fp32 instruction, from
+      // memory
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          floatx16 acc;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+          const int m = min(m0 + wm0 + i * 32 + lr, M - 1), n = min(n0 + wn0 + j * 32 + lr, N - 1);
+          for (int k = kbeg; k < kend; k += 2) {
+            const int kx = k + lk, kc = min(kx, kend - 1);
+            const long long oa = AT ? (GATHER ? (long long)rmap[kc] : (long long)kc) * a.lda + m
+                                    : (GATHER ? (long long)rmap[m] : (long long)m) * a.lda + kc;
+            const long long ob = BT ? (long long)n * a.ldb + kc : (long long)kc * a.ldb + n;
+            const float x = kx < kend ? ((const float*)A)[oa] : 0.f;
+            const float y = kx < kend ? ((const float*)B)[ob] : 0.f;
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, acc, 0, 0, 0);
+          }
+          hi[i][j] = acc;
+        }
+    }
+  }
 
+  // epilogue
+  constexpr bool OUTBF = BF && (EPI == EPI_BIAS_RELU || EPI == EPI_RELU_MASK);
+  if constexpr (kUpd) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int m = out_row(i, v), n = n0 + wn0 + j * 32 + lr;
+          if (!FULL && (m >= M || n >= N)) continue;
+          const long long o = (long long)g * a.sC + (long long)m * a.ldc + n;
+          sgd_step(wv[i][j][v], uv[i][j][v], hi[i][j][v], a);
+          a.W[o] = wv[i][j][v];
+          a.U[o] = uv[i][j][v];
+          if (a.Wb) a.Wb[o] = f32_to_bf16(wv[i][j][v]);
+        }
+    if (do_bias) {
+      // the threads that share a column's quad, in ascending thread order
+      constexpr int RQ = BN / 4, TPC = kThreads / RQ;
+      float* red = (float*)sA;  // [TPC][BN] floats (the k loop is done with it)
+      static_assert(TPC * BN * 4 <= 2 * NPL * SA * 2, "column sums fit");
+      __syncthreads();
+      *(v4f*)&red[(tid / RQ) * BN + (tid % RQ) * 4] = colsum;
+      __syncthreads();
+      if (tid < BN && n0 + tid < N) {
+        float s = red[tid];
+#pragma unroll
+        for (int q = 1; q < TPC; ++q) s += red[q * BN + tid];
+        bias_update(a, g, n0 + tid, s);
+      }
+    }
+  } else if (a.splits > 1) {  // raw partial sums, [s][g][M][N]
+    float* P = a.part + ((long long)t.s * a.G + g) * M * N;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int m = out_row(i, v), n = n0 + wn0 + j * 32 + lr;
+          if (FULL || (m < M && n < N)) P[(long long)m * N + n] = hi[i][j][v];
+        }
+  } else {
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      const int n = n0 + wn0 + j * 32 + lr;
+      float bias = 0.f;
+      if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_RELU)
+        bias = a.bias[(long long)g * a.sBias + (FULL ? n : min(n, N - 1))];
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        float mk[16];
+        if constexpr (EPI == EPI_RELU_MASK) {  // the mask first: 16 loads in flight
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            int m = out_row(i, v);
+            if constexpr (!FULL) m = min(m, M - 1);
+            const long long o = (long long)g * a.sC + (long long)m * a.ldc + (FULL ? n : min(n, N - 1));
+            mk[v] = OUTBF ? bf16_to_f32(((const bf16_t*)a.mask)[o]) : ((const float*)a.mask)[o];
+          }
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int m = out_row(i, v);
+          if (!FULL && (m >= M || n >= N)) continue;
+          const long long o = (long long)g * a.sC + (long long)m * a.ldc + n;
+          float r = hi[i][j][v] + bias;
+          if constexpr (EPI == EPI_STORE) r = hi[i][j][v];
+          if constexpr (EPI == EPI_BIAS_RELU) r = r > 0.f ? r : 0.f;
+          if constexpr (EPI == EPI_RELU_MASK) r = mk[v] > 0.f ? hi[i][j][v] : 0.f;
+          if constexpr (OUTBF)
+            ((bf16_t*)a.C)[o] = f32_to_bf16(r);
+          else
+            ((float*)a.C)[o] = r;
+        }
+      }
+    }
+  }
+}
 
 // ------------------------------------------------- fp32 update, specialised
 // Fused weight gradient + momentum-SGD update over the 128 x 128 tiles of one
@@ -957,11 +838,9 @@ __global__ __launch_bounds__(kWsThreads) void gemm_f32_sgd_ws(WsArgs w) {
           cs0 += __shfl_xor(cs0, 32, 64);
           cs1 += __shfl_xor(cs1, 32, 64);
           if (lk == 0) {
-            Tile bt;
-            bt.g = cur.g;
             const int n = cur.n0 + wn0 + 2 * lr;
-            bias_update(a, bt, n, cs0);
-            bias_update(a, bt, n + 1, cs1);
+            bias_update(a, cur.g, n, cs0);
+            bias_update(a, cur.g, n + 1, cs1);
           }
         }
       }
@@ -1046,257 +925,6 @@ bool ws_eligible(int dtype, const GemmArgs& a) {
          (a.Wsrc == nullptr || (al(a.Wsrc, 15) && a.sWsrc % 4 == 0));
 }
 
-// ------------------------------------------------------------------ bf16
-template <bool AT, bool BT, int EPI, bool GATHER, int BM, int BN>
-__global__ __launch_bounds__(kThreads) void gemm_bf16(GemmArgs a, int vecA,
-                                                      int vecB, int vecC) {
-  constexpr int BK = 32, KP = BK + 8;  // row pitch 80 B keeps 16-B alignment
-  constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 32, FN = WN / 32;
-  constexpr int NA = BM * BK / 8 / kThreads;  // 8-element vectors per thread
-  constexpr int NB = BN * BK / 8 / kThreads;
-  static_assert(NA >= 1 && NB >= 1, "tile too small for 256 threads");
-  __shared__ __attribute__((aligned(16))) bf16_t As[2][BM][KP];
-  __shared__ __attribute__((aligned(16))) bf16_t Bs[2][BN][KP];
-
-  const Tile t = decode_tile(a, BM, BN);
-  const int g = t.g, m0 = t.m0, n0 = t.n0;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm0 = (wave >> 1) * WM, wn0 = (wave & 1) * WN;
-  const bf16_t* A = (const bf16_t*)a.A + (long long)g * a.sA;
-  const bf16_t* B = (const bf16_t*)a.B + (long long)g * a.sB;
-  const int32_t* rmap = GATHER ? a.rowmap + (long long)g * a.sRow : nullptr;
-  const int M = a.M, N = a.N;
-  const int kbeg = t.s * a.kchunk;
-  const int kend = min(a.Kd, kbeg + a.kchunk);
-
-  uint4 ra[NA], rb[NB];
-
-  auto load8 = [](const bf16_t* p, int avail, int vec) -> uint4 {
-    if (vec && avail >= 8) return *(const uint4*)p;
-    uint16_t h[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) h[e] = e < avail ? p[e] : (uint16_t)0;
-    return make_uint4(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16),
-                      h[4] | ((uint32_t)h[5] << 16), h[6] | ((uint32_t)h[7] << 16));
-  };
-
-  auto gload = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const int q = tid + i * kThreads;
-      ra[i] = make_uint4(0, 0, 0, 0);
-      if constexpr (!AT) {  // [M][Kd]: 4 vectors per row
-        const int r = q >> 2, c = k0 + (q & 3) * 8, row = m0 + r;
-        if (row < M) {
-          const long long sr = GATHER ? rmap[row] : row;
-          ra[i] = load8(A + sr * a.lda + c, kend - c, vecA);
-        }
-      } else {  // [Kd][M]: BM/8 vectors per row
-        const int r = q / (BM / 8), c = m0 + (q % (BM / 8)) * 8, kr = k0 + r;
-        if (kr < kend) {
-          const long long sr = GATHER ? rmap[kr] : kr;
-          ra[i] = load8(A + sr * a.lda + c, M - c, vecA);
-        }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int q = tid + i * kThreads;
-      rb[i] = make_uint4(0, 0, 0, 0);
-      if constexpr (BT) {  // [N][Kd]
-        const int r = q >> 2, c = k0 + (q & 3) * 8, row = n0 + r;
-        if (row < N) rb[i] = load8(B + (long long)row * a.ldb + c, kend - c, vecB);
-      } else {  // [Kd][N]
-        const int r = q / (BN / 8), c = n0 + (q % (BN / 8)) * 8, kr = k0 + r;
-        if (kr < kend) rb[i] = load8(B + (long long)kr * a.ldb + c, N - c, vecB);
-      }
-    }
-  };
-
-  auto scatter = [](bf16_t (*T)[KP], int r0, int k, uint4 v) {
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      T[r0 + 2 * e][k] = (bf16_t)(w[e] & 0xFFFFu);
-      T[r0 + 2 * e + 1][k] = (bf16_t)(w[e] >> 16);
-    }
-  };
-
-  auto lstore = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const int q = tid + i * kThreads;
-      if constexpr (!AT) {
-        const int r = q >> 2, c = (q & 3) * 8;
-        *(uint4*)&As[buf][r][c] = ra[i];
-      } else {
-        const int r = q / (BM / 8), c = (q % (BM / 8)) * 8;
-        scatter(As[buf], c, r, ra[i]);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int q = tid + i * kThreads;
-      if constexpr (BT) {
-        const int r = q >> 2, c = (q & 3) * 8;
-        *(uint4*)&Bs[buf][r][c] = rb[i];
-      } else {
-        const int r = q / (BN / 8), c = (q % (BN / 8)) * 8;
-        scatter(Bs[buf], c, r, rb[i]);
-      }
-    }
-  };
-
-  floatx16 acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-  const bool do_bias = EPI == EPI_SGD && a.bias_w && m0 == 0;
-  float colsum = 0.f;
-  const int nk = (kend - kbeg + BK - 1) / BK;
-  if (nk > 0) {
-    gload(kbeg);
-    lstore(0);
-  }
-  __syncthreads();
-  const int lk = lane >> 5, lr = lane & 31;
-  for (int it = 0; it < nk; ++it) {
-    const int buf = it & 1;
-    if (it + 1 < nk) gload(kbeg + (it + 1) * BK);
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 16) {
-      bf16x8 av[FM], bv[FN];
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-        av[i] = *(const bf16x8*)&As[buf][wm0 + i * 32 + lr][kk + lk * 8];
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-        bv[j] = *(const bf16x8*)&Bs[buf][wn0 + j * 32 + lr][kk + lk * 8];
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bv[j],
-                                                              acc[i][j], 0, 0, 0);
-    }
-    if (do_bias && tid < BN) {
-#pragma unroll 8
-      for (int k = 0; k < BK; ++k) colsum += bf16_to_f32(Bs[buf][tid][k]);
-    }
-    if (it + 1 < nk) lstore(buf ^ 1);
-    __syncthreads();
-  }
-
-  constexpr bool OUTBF = EPI == EPI_BIAS_RELU || EPI == EPI_RELU_MASK;
-  epilogue_fragment<EPI, OUTBF, FM, FN>(a, t, acc, m0 + wm0, n0 + wn0, lk, lr);
-  if (do_bias && tid < BN && n0 + tid < N) bias_update(a, t, n0 + tid, colsum);
-}
-
-// bf16 operands, whole 64 x 64 tiles, A stored [M][Kd] (forward and input
-// gradient): a HBM-bound contraction at small M, so the point is to keep
-// many weight bytes in flight. Two register sets of branch-free 16-byte
-// loads (slab t+2 is loaded while slab t computes and slab t+1 waits in
-// LDS), BK = 64, prefetches past the end clamped to the last slab.
-template <bool BT, int EPI, bool GATHER>
-__global__ __launch_bounds__(kThreads) void gemm_bf16_full(GemmArgs a) {
-  constexpr int BM = 64, BN = 64, BK = 64, KP = BK + 8;  // 144-B rows
-  constexpr int FM = 1, FN = 1;
-  constexpr int NA = BM * BK / 8 / kThreads, NB = BN * BK / 8 / kThreads;
-  static_assert(NA == 2 && NB == 2, "tile shape");
-  __shared__ __attribute__((aligned(16))) bf16_t As[2][BM][KP];
-  __shared__ __attribute__((aligned(16))) bf16_t Bs[2][BN][KP];
-
-  const Tile t = decode_tile(a, BM, BN);
-  const int g = t.g, m0 = t.m0, n0 = t.n0;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm0 = (wave >> 1) * 32, wn0 = (wave & 1) * 32;
-  const bf16_t* A = (const bf16_t*)a.A + (long long)g * a.sA;
-  const bf16_t* B = (const bf16_t*)a.B + (long long)g * a.sB;
-  const int kbeg = t.s * a.kchunk;
-  const int nk = a.kchunk / BK;
-  // rows of A are fixed per thread: resolve the gathered indices once
-  long long arow[NA];
-#pragma unroll
-  for (int i = 0; i < NA; ++i) {
-    const int row = m0 + (tid + i * kThreads) / (BK / 8);
-    arow[i] = (GATHER ? (long long)a.rowmap[(long long)g * a.sRow + row] : (long long)row) * a.lda;
-  }
-  auto gload = [&](int k0, u32x4(&xa)[NA], u32x4(&xb)[NB]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const int q = tid + i * kThreads;
-      xa[i] = *(const u32x4*)(A + arow[i] + k0 + (q % (BK / 8)) * 8);
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int q = tid + i * kThreads;
-      if constexpr (BT)  // [N][Kd]
-        xb[i] = *(const u32x4*)(B + (long long)(n0 + q / (BK / 8)) * a.ldb + k0 + (q % (BK / 8)) * 8);
-      else  // [Kd][N]
-        xb[i] = *(const u32x4*)(B + (long long)(k0 + q / (BN / 8)) * a.ldb + n0 + (q % (BN / 8)) * 8);
-    }
-  };
-  auto lstore = [&](int buf, const u32x4(&xa)[NA], const u32x4(&xb)[NB]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const int q = tid + i * kThreads;
-      *(u32x4*)&As[buf][q / (BK / 8)][(q % (BK / 8)) * 8] = xa[i];
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int q = tid + i * kThreads;
-      if constexpr (BT) {
-        *(u32x4*)&Bs[buf][q / (BK / 8)][(q % (BK / 8)) * 8] = xb[i];
-      } else {  // k row r, 8 consecutive n: transpose into Bs[n][k]
-        const int r = q / (BN / 8), c = (q % (BN / 8)) * 8;
-        const uint32_t wds[4] = {xb[i].x, xb[i].y, xb[i].z, xb[i].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          Bs[buf][c + 2 * e][r] = (bf16_t)(wds[e] & 0xFFFFu);
-          Bs[buf][c + 2 * e + 1][r] = (bf16_t)(wds[e] >> 16);
-        }
-      }
-    }
-  };
-  floatx16 acc[FM][FN];
-#pragma unroll
-  for (int v = 0; v < 16; ++v) acc[0][0][v] = 0.f;
-  const int lk = lane >> 5, lr = lane & 31;
-  auto compute = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 16) {
-      const bf16x8 av = *(const bf16x8*)&As[buf][wm0 + lr][kk + lk * 8];
-      const bf16x8 bv = *(const bf16x8*)&Bs[buf][wn0 + lr][kk + lk * 8];
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[0][0], 0, 0, 0);
-    }
-  };
-  u32x4 ra0[NA], rb0[NB], ra1[NA], rb1[NB];
-  auto slab = [&](int s) __attribute__((always_inline)) { return kbeg + min(s, nk - 1) * BK; };
-  gload(slab(0), ra0, rb0);
-  gload(slab(1), ra1, rb1);
-  lstore(0, ra0, rb0);
-  __syncthreads();
-  int it = 0;
-  for (; it + 1 < nk; it += 2) {
-    gload(slab(it + 2), ra0, rb0);
-    __builtin_amdgcn_sched_barrier(0);
-    compute(0);
-    lstore(1, ra1, rb1);
-    __syncthreads();
-    gload(slab(it + 3), ra1, rb1);
-    __builtin_amdgcn_sched_barrier(0);
-    compute(1);
-    lstore(0, ra0, rb0);
-    __syncthreads();
-  }
-  if (it < nk) compute(0);  // odd slab count: the last slab is in buffer 0
-  constexpr bool OUTBF = EPI == EPI_BIAS_RELU || EPI == EPI_RELU_MASK;
-  epilogue_fragment<EPI, OUTBF, FM, FN>(a, t, acc, m0 + wm0, n0 + wn0, lk, lr);
-}
 
 // ------------------------------------------------------------------ split-K
 // C[g][m][n] = epilogue(sum_{s=0}^{S-1} part[s][g][m][n]), s ascending. S is
@@ -1330,21 +958,6 @@ hipError_t launch_reduce(const GemmArgs& a, hipStream_t s) {
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
-}
-
-bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
-
-// Tile shape for a problem: 128 x 128 (four MFMA chains per wave) when both
-// output dimensions allow it on the fp32 path, else 64 x 64.
-// 128 x 128 fp32 tiles when they fill the chip (256 or more) or the inner
-// dimension is long enough for split-K to amortise them; otherwise 64 x 64
-// tiles without split-K. Measured on the 512-wide MLP: its 512-deep layer
-// GEMMs (64 big tiles) take 18 us as 64 x 64 tiles against 25 us as split-K
-// 128 x 128 tiles plus the reduction; the 3072-deep first layer is fastest
-// as 128 x 128 tiles split four ways.
-bool big_tile(int dtype, int M, int N, int G, int Kd) {
-  if (dtype != 0 || M < 128 || N < 128) return false;
-  return (long long)(M / 128) * (N / 128) * G >= 256 || Kd >= 2048;
 }
 
 // Compute units and resident specialised-update workgroups per CU on the
@@ -1419,89 +1032,85 @@ hipError_t launch_gemm_sgd_multi(int dtype, const GemmArgs* list, int n,
 
 namespace {
 
-// k slab of the whole-tile 128 x 128 variant. 32 would halve the barriers
-// per k but doubles the prefetch registers and LDS; measured on the 512-wide
-// MLP it is slower, and costs the update epilogue an occupancy step.
-template <int EPI>
-constexpr int kBigFullBK = 16;
+// Tile of a forward, input-gradient or plain product. Larger tiles read less
+// from LDS per MFMA, but a launch should have a workgroup for each of the 256
+// CUs (two of the 128 x 64 ones): 128 x 128 (fp32) or 128 x 64 tiles where the
+// output has that many, or where the inner dimension is long enough for
+// split-K to get there; else 64 x 64. Measured, 16 replicas of 128 x 512 x
+// 3072, fp32 with the partials' sum: 128 x 128 split 4 46 us, 128 x 64 split 4
+// 51-58, 64 x 64 split 2 53; 128 x 512 x 512: 64 x 64 12 us, 128 x 64 18.
+struct Shape {
+  int BM, BN;
+};
+Shape tile_shape(bool bf, int M, int N, int G, int Kd) {
+  if (M <= 64 || N <= 64) return {64, 64};
+  const bool deep = Kd >= 2048;
+  const long long t128 = (long long)((M + 127) / 128) * ((N + 127) / 128) * G;
+  if (!bf && (t128 >= 256 || (deep && t128 >= 32))) return {128, 128};
+  const long long t64 = (long long)((M + 127) / 128) * ((N + 63) / 64) * G;
+  if (t64 >= 512 || deep) return {128, 64};
+  return {64, 64};
+}
 
-// Whole tiles, whole slabs per split, vector loads: the FULL kernel variant.
-bool full(const GemmArgs& a, int T, int BK, int vecA, int vecB, int vecC) {
-  return vecA && vecB && a.M % T == 0 && a.N % T == 0 && a.kchunk % BK == 0 &&
-         (long long)a.kchunk * a.splits == a.Kd && (vecC || a.W == nullptr);
+// Whole tiles, whole slabs per split: the FULL kernel variant.
+bool full(const GemmArgs& a, int BM, int BN, int BK) {
+  return a.M % BM == 0 && a.N % BN == 0 && a.kchunk % BK == 0 &&
+         (long long)a.kchunk * a.splits == a.Kd;
+}
+
+template <bool BF, bool AT, bool BT, int EPI, bool GATHER, int BM, int BN, int BK, int D>
+hipError_t run_tile(const GemmArgs& a, hipStream_t s) {
+  const long long total =
+      (long long)((a.N + BN - 1) / BN) * ((a.M + BM - 1) / BM) * a.G * a.splits;
+  if (total > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (full(a, BM, BN, BK))
+    hipLaunchKernelGGL((gemm_mm<BF, AT, BT, EPI, GATHER, BM, BN, BK, D, true>), dim3(total),
+                       dim3(kThreads), 0, s, a);
+  else
+    hipLaunchKernelGGL((gemm_mm<BF, AT, BT, EPI, GATHER, BM, BN, BK, D, false>), dim3(total),
+                       dim3(kThreads), 0, s, a);
+  return hipGetLastError();
+}
+
+template <bool BF, bool AT, bool BT, int EPI, bool GATHER>
+hipError_t run_type(const GemmArgs& a, hipStream_t s) {
+  if constexpr (EPI == EPI_SGD) {
+    return run_tile<BF, AT, BT, EPI, GATHER, 64, 64, 32, 2>(a, s);
+  } else {
+    const Shape sh = tile_shape(BF, a.M, a.N, a.G, a.Kd);
+    hipError_t e;
+    if (sh.BM == 64)
+      e = run_tile<BF, AT, BT, EPI, GATHER, 64, 64, BF ? 64 : 32, 2>(a, s);
+    else if (BF || sh.BN == 64)
+      e = run_tile<BF, AT, BT, EPI, GATHER, 128, 64, BF ? 32 : 16, 2>(a, s);
+    else
+      e = run_tile<BF, AT, BT, EPI, GATHER, 128, BF ? 64 : 128, BF ? 32 : 16, 2>(a, s);
+    if (e != hipSuccess || a.splits == 1) return e;
+    constexpr bool OUTBF = BF && (EPI == EPI_BIAS_RELU || EPI == EPI_RELU_MASK);
+    return launch_reduce<EPI, OUTBF>(a, s);
+  }
 }
 
 template <bool AT, bool BT, int EPI, bool GATHER>
-hipError_t run(int dtype, GemmArgs a, hipStream_t s) {
+hipError_t run(int dtype, const GemmArgs& a, hipStream_t s) {
   if constexpr (AT && !BT && EPI == EPI_SGD) {
     // one large layer: the specialised update kernel with a one-item list
     if (ws_eligible(dtype, a) &&
         (long long)(a.M / 128) * (a.N / 128) * a.G >= kWsMinTiles)
       return launch_gemm_sgd_multi(dtype, &a, 1, s);
   }
-  const bool big = big_tile(dtype, a.M, a.N, a.G, a.Kd);
-  const int BM = big ? 128 : 64, BN = BM;
-  const long long tiles = (long long)((a.N + BN - 1) / BN) * ((a.M + BM - 1) / BM) * a.G;
-  const long long total = tiles * a.splits;
-  if (total > 0x7fffffffLL) return hipErrorInvalidValue;
-  const int esz = dtype == 1 ? 8 : 4;  // elements per vector load
-  const int vecA = a.lda % esz == 0 && a.sA % esz == 0 && aligned16(a.A);
-  const int vecB = a.ldb % esz == 0 && a.sB % esz == 0 && aligned16(a.B);
-  const int vecC = EPI == EPI_SGD && a.ldc % 4 == 0 && a.sC % 4 == 0 &&
-                   aligned16(a.W) && aligned16(a.U) &&
-                   (a.Wb == nullptr || ((uintptr_t)a.Wb & 7u) == 0) &&
-                   (a.Wsrc == nullptr || (aligned16(a.Wsrc) && a.sWsrc % 4 == 0));
-  if constexpr (!AT && EPI != EPI_SGD) {
-    if (dtype == 1 && vecA && vecB && a.M % 64 == 0 && a.N % 64 == 0 &&
-        a.kchunk % 64 == 0 && (long long)a.kchunk * a.splits == a.Kd) {
-      hipLaunchKernelGGL((gemm_bf16_full<BT, EPI, GATHER>), dim3(total), dim3(kThreads),
-                         0, s, a);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess || a.splits == 1) return e;
-      constexpr bool OUTBF_ACT = EPI == EPI_BIAS_RELU || EPI == EPI_RELU_MASK;
-      return launch_reduce<EPI, OUTBF_ACT>(a, s);
-    }
-  }
-  // two k halves per workgroup (an even number of slabs per split)
-  bool kh2 = false;
-  if constexpr (!AT && EPI != EPI_SGD) {
-    const int bk = big ? kBigFullBK<EPI> : 32;
-    kh2 = dtype == 0 && full(a, BM, bk, vecA, vecB, vecC) && a.kchunk >= 2 * bk &&
-          a.kchunk % (2 * bk) == 0;
-    if (kh2 && big)
-      hipLaunchKernelGGL((gemm_f32_kh2<BT, EPI, GATHER, 128, 128, kBigFullBK<EPI>>),
-                         dim3(total), dim3(2 * kThreads), 0, s, a);
-    else if (kh2)
-      hipLaunchKernelGGL((gemm_f32_kh2<BT, EPI, GATHER, 64, 64, 32>), dim3(total),
-                         dim3(2 * kThreads), 0, s, a);
-  }
-  if (kh2)
-    ;
-  else if (dtype == 1)
-    hipLaunchKernelGGL((gemm_bf16<AT, BT, EPI, GATHER, 64, 64>), dim3(total),
-                       dim3(kThreads), 0, s, a, vecA, vecB, vecC);
-  else if (big && full(a, 128, kBigFullBK<EPI>, vecA, vecB, vecC))
-    hipLaunchKernelGGL((gemm_f32<AT, BT, EPI, GATHER, 128, 128, kBigFullBK<EPI>, true>), dim3(total),
-                       dim3(kThreads), 0, s, a, vecA, vecB, vecC);
-  else if (big)
-    hipLaunchKernelGGL((gemm_f32<AT, BT, EPI, GATHER, 128, 128, 16, false>), dim3(total),
-                       dim3(kThreads), 0, s, a, vecA, vecB, vecC);
-  else if (full(a, 64, 32, vecA, vecB, vecC))
-    hipLaunchKernelGGL((gemm_f32<AT, BT, EPI, GATHER, 64, 64, 32, true>), dim3(total),
-                       dim3(kThreads), 0, s, a, vecA, vecB, vecC);
-  else
-    hipLaunchKernelGGL((gemm_f32<AT, BT, EPI, GATHER, 64, 64, 32, false>), dim3(total),
-                       dim3(kThreads), 0, s, a, vecA, vecB, vecC);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.splits == 1) return e;
-  constexpr bool OUTBF_ACT = EPI == EPI_BIAS_RELU || EPI == EPI_RELU_MASK;
-  if (dtype == 1 && OUTBF_ACT) return launch_reduce<EPI, true>(a, s);
-  return launch_reduce<EPI, false>(a, s);
+  return dtype == 1 ? run_type<true, AT, BT, EPI, GATHER>(a, s)
+                    : run_type<false, AT, BT, EPI, GATHER>(a, s);
 }
 
 template <bool AT, bool BT, int EPI>
 hipError_t dispatch(int dtype, const GemmArgs& a, hipStream_t s) {
-  if (a.rowmap) return run<AT, BT, EPI, true>(dtype, a, s);
+  if (a.rowmap) {  // gathered rows: the first layer's forward and update
+    if constexpr (EPI == EPI_STORE || EPI == EPI_RELU_MASK)
+      return hipErrorInvalidValue;
+    else
+      return run<AT, BT, EPI, true>(dtype, a, s);
+  }
   return run<AT, BT, EPI, false>(dtype, a, s);
 }
 
@@ -1509,12 +1118,13 @@ hipError_t dispatch(int dtype, const GemmArgs& a, hipStream_t s) {
 
 int gemm_splits(int dtype, int M, int N, int Kd, int G, int epi) {
   if (epi == EPI_SGD) return 1;
-  const int T = big_tile(dtype, M, N, G, Kd) ? 128 : 64;
-  const long long tiles = (long long)((N + T - 1) / T) * ((M + T - 1) / T) * G;
+  const Shape sh = tile_shape(dtype == 1, M, N, G, Kd);
+  const long long tiles = (long long)((N + sh.BN - 1) / sh.BN) * ((M + sh.BM - 1) / sh.BM) * G;
+  const int want = sh.BM * sh.BN == 128 * 64 ? 512 : 256;
   int s = 1;
-  // up to 8 splits while the grid has fewer workgroups than compute units
-  // and every split keeps at least 128 of K
-  while (s < 8 && tiles * s < 256 && Kd / (s * 2) >= 128) s *= 2;
+  // up to 8 splits while the grid has fewer workgroups than that and every
+  // split keeps at least 128 of K
+  while (s < 8 && tiles * s < want && Kd / (s * 2) >= 128) s *= 2;
   return s;
 }
 
