@@ -249,7 +249,7 @@ def traffic_for(tag: str, w):
 # convolution families, and the K-way average, the copy-like kernel used to
 # scale the counters.
 TAG_KERNELS = {
-    "wgrad_update": ("gemm_f32_sgd_ws<",),
+    "wgrad_update": ("gemm_update<",),
     "average": ("k_average4<",),
     "conv_fwd": ("k_conv_stem_fwd", "k_conv_halo16<0>", "k_conv_rows<0,"),
     "conv_dgrad": ("k_conv_halo16<1>", "k_conv_rows<1,", "k_conv_dgrad_s2<"),

@@ -427,10 +427,6 @@ hipError_t sample(const lsgd_ctx* c, int64_t step, int32_t* idx, hipStream_t s) 
   return lsgd::launch_sample(cf.seed, step, cf.K, cf.N, cf.B_loc, idx, s);
 }
 
-// Tiles (128 x 128) from which one persistent launch over all hidden layers
-// updates beats per-layer launches (about four per compute unit).
-constexpr int kMergedMinTiles = 1024;
-
 // Weight gradient of layer l fused with its momentum-SGD step and the bias
 // step: G_l = A_{l-1}^T dZ_l over the batch, per replica.
 GemmArgs wgrad_args(const lsgd_ctx* c, int l, float lr) {
@@ -504,7 +500,7 @@ lsgd_status do_local_step(lsgd_ctx* c, float lr, float* d_loss) {
     LSGD_LAUNCH(c, "sample", sample(c, c->step, c->idx(), s));
   c->presampled = -1;
   bool presample = false;
-  bool side0 = false, side1 = false;  // work forked onto the side streams
+  bool side0 = false;  // work forked onto side stream 0
 
   // forward: Z_l = A_{l-1} W_l + b_l, A_l = relu(Z_l) below the top layer
   const int Lg = ly.head ? L - 1 : L;  // layers through the generic GEMMs
@@ -605,67 +601,39 @@ lsgd_status do_local_step(lsgd_ctx* c, float lr, float* d_loss) {
                                                c->dZ(L), dt, d_loss, c->flag(), s));
   }
 
-  // backward, top layer first. The input gradient of layer l reads the
-  // pre-update W_l, so it is enqueued before W_l's fused update. When every
-  // hidden layer's update fits the persistent update kernel and together
-  // they fill the chip, the input gradients go first and one launch then
-  // updates all of those layers (their tiles in one list).
-  GemmArgs upd[lsgd::kWsMaxProblems];
-  int nupd = 0;
-  bool merged = false;
-  if (Lg >= 1 && Lg <= lsgd::kWsMaxProblems) {
-    for (int l = 1; l <= Lg; ++l) upd[l - 1] = wgrad_args(c, l, lr);
-    const int tiles = lsgd::gemm_sgd_multi_tiles(dt, upd, Lg);
-    merged = tiles >= kMergedMinTiles;
-    nupd = Lg;
-  }
-  for (int l = Lg; l >= 1; --l) {
+  // backward, top layer first: the input gradients (they read the pre-update
+  // weights), then one launch that updates every layer below the head
+  for (int l = Lg; l >= 2; --l) {
     const int din = w[l - 1], dout = w[l];
-    if (l > 1 && !(ly.head && l == L)) {
-      GemmArgs a{};
-      a.G = K;
-      a.M = B;
-      a.N = din;
-      a.Kd = dout;
-      a.A = c->dZ(l);
-      a.lda = dout;
-      a.sA = (long long)B * dout;
-      a.B = dt ? (const void*)(Wbr + ly.offW[l - 1]) : (const void*)(Wr + ly.offW[l - 1]);
-      a.ldb = dout;
-      a.sB = sWr;
-      a.C = c->dZ(l - 1);
-      a.ldc = din;
-      a.sC = (long long)B * din;
-      a.mask = c->act(l - 1);
-      a.splits = lsgd::gemm_splits(dt, B, din, dout, K, lsgd::EPI_RELU_MASK);
-      a.part = c->part();
-      LSGD_LAUNCH(c, "dgrad" + std::to_string(l),
-                  lsgd::launch_gemm(dt, 0, 1, lsgd::EPI_RELU_MASK, dt, a, s));
-    }
-    if (merged) continue;
-    const GemmArgs a = wgrad_args(c, l, lr);
-    if (c->use_side && l > 1) {
-      // after its input gradient, layer l's update only has to finish by the
-      // end of the step: side stream 1, overlapping the layers below
-      LSGD_CK(c, hipEventRecord(c->fork[1], s));
-      LSGD_CK(c, hipStreamWaitEvent(c->side[1], c->fork[1], 0));
-      LSGD_LAUNCH_ON(c, c->side[1], "wgrad_update" + std::to_string(l),
-                     lsgd::launch_gemm(dt, 1, 0, lsgd::EPI_SGD, 0, a, c->side[1]));
-      side1 = true;
-    } else {
-      LSGD_LAUNCH(c, "wgrad_update" + std::to_string(l),
-                  lsgd::launch_gemm(dt, 1, 0, lsgd::EPI_SGD, 0, a, s));
-    }
+    GemmArgs a{};
+    a.G = K;
+    a.M = B;
+    a.N = din;
+    a.Kd = dout;
+    a.A = c->dZ(l);
+    a.lda = dout;
+    a.sA = (long long)B * dout;
+    a.B = dt ? (const void*)(Wbr + ly.offW[l - 1]) : (const void*)(Wr + ly.offW[l - 1]);
+    a.ldb = dout;
+    a.sB = sWr;
+    a.C = c->dZ(l - 1);
+    a.ldc = din;
+    a.sC = (long long)B * din;
+    a.mask = c->act(l - 1);
+    a.splits = lsgd::gemm_splits(dt, B, din, dout, K, lsgd::EPI_RELU_MASK);
+    a.part = c->part();
+    LSGD_LAUNCH(c, "dgrad" + std::to_string(l),
+                lsgd::launch_gemm(dt, 0, 1, lsgd::EPI_RELU_MASK, dt, a, s));
   }
-  if (merged)
-    LSGD_LAUNCH(c, "wgrad_update", lsgd::launch_gemm_sgd_multi(dt, upd, nupd, s));
-  // join: the step ends when all of its updates have; a side stream with no
-  // work this step is not waited for (each wait costs the stream some µs)
+  if (Lg >= 1) {
+    GemmArgs upd[lsgd::kUpdMaxProblems];
+    static_assert(LSGD_MAX_LAYERS <= lsgd::kUpdMaxProblems, "every layer in one launch");
+    for (int l = 1; l <= Lg; ++l) upd[l - 1] = wgrad_args(c, l, lr);
+    LSGD_LAUNCH(c, "wgrad_update", lsgd::launch_gemm_update(dt, upd, Lg, s));
+  }
+  // join: the step ends when all of its updates have; without side-stream
+  // work there is nothing to wait for (a wait costs the stream some µs)
   if (side0) LSGD_CK(c, hipStreamWaitEvent(s, c->join[0], 0));
-  if (side1) {
-    LSGD_CK(c, hipEventRecord(c->join[1], c->side[1]));
-    LSGD_CK(c, hipStreamWaitEvent(s, c->join[1], 0));
-  }
   c->step += 1;
   c->pending = false;  // every replica now holds its own stepped model
   if (presample) c->presampled = c->step;

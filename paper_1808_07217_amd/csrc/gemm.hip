@@ -182,7 +182,7 @@ struct Quad<true> {
 // columns of a k-slow operand take element loads (a uniform branch).
 template <bool BF, bool AT, bool BT, int EPI, bool GATHER, int BM, int BN, int BK, int D,
           bool FULL>
-__global__ __launch_bounds__(kThreads, BM * BN > 128 * 64 ? 1 : 2) void gemm_mm(GemmArgs a) {
+__device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t) {
   using Q = Quad<BF>;
   using E = typename Q::E;
   constexpr int NPL = Q::kPlanes;
@@ -194,10 +194,11 @@ __global__ __launch_bounds__(kThreads, BM * BN > 128 * 64 ? 1 : 2) void gemm_mm(
   static_assert(NA >= 1 && NB >= 1 && D % 2 == 0, "tile too small");
   __shared__ __attribute__((aligned(16))) bf16_t sA[2 * NPL * SA];
   __shared__ __attribute__((aligned(16))) bf16_t sB[2 * NPL * SB];
-  constexpr bool kRows = AT && GATHER;  // the k rows of A come from a row map
+  // the k rows of A come from a row map (an update's may have none: its rows
+  // in order)
+  constexpr bool kRows = AT && GATHER;
   __shared__ int32_t srmap[kRows ? 512 : 1];  // beyond: read the map itself
 
-  const Tile t = decode_tile(a, BM, BN);
   const int g = t.g, m0 = t.m0, n0 = t.n0;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -205,40 +206,49 @@ __global__ __launch_bounds__(kThreads, BM * BN > 128 * 64 ? 1 : 2) void gemm_mm(
   const int wm0 = (wave >> 1) * WM, wn0 = (wave & 1) * WN;
   const E* A = (const E*)a.A + (long long)g * a.sA;
   const E* B = (const E*)a.B + (long long)g * a.sB;
-  const int32_t* rmap = GATHER ? a.rowmap + (long long)g * a.sRow : nullptr;
+  const int32_t* rmap = GATHER && a.rowmap ? a.rowmap + (long long)g * a.sRow : nullptr;
   const int M = a.M, N = a.N;
   const int kbeg = t.s * a.kchunk, kend = min(a.Kd, kbeg + a.kchunk);
   const int nk = (kend - kbeg + BK - 1) / BK;
 
-  // EPI_SGD: the tile's W and U, in accumulator layout, on their way while
-  // the k loop runs (clamped where the tile ends)
+  // EPI_SGD: the tile's W and U, in accumulator layout, at 32-bit offsets from
+  // the tile's corner (clamped where the tile ends); loaded before the last D
+  // slabs, when the operand registers fall free (from the start on they cost a
+  // fourth workgroup per CU: 107 against 90 us, see gemm_update)
   constexpr bool kUpd = EPI == EPI_SGD;
   float wv[kUpd ? FM : 1][kUpd ? FN : 1][16], uv[kUpd ? FM : 1][kUpd ? FN : 1][16];
   auto out_row = [&](int i, int v) __attribute__((always_inline)) {
     return m0 + wm0 + i * 32 + (v >> 2) * 8 + lk * 4 + (v & 3);
   };
-  if constexpr (kUpd) {
-    const float* Wr = a.Wsrc ? a.Wsrc + (long long)g * a.sWsrc : a.W + (long long)g * a.sC;
-    const float* Ur = a.U + (long long)g * a.sC;
+  const long long tile0 = (long long)m0 * a.ldc + n0;
+  auto tile_off = [&](int i, int j, int v) __attribute__((always_inline)) {
+    int m = out_row(i, v), n = n0 + wn0 + j * 32 + lr;
+    if constexpr (!FULL) {
+      m = min(m, M - 1);
+      n = min(n, N - 1);
+    }
+    return (unsigned)((m - m0) * (int)a.ldc + (n - n0));
+  };
+  auto wu_load = [&]() __attribute__((always_inline)) {
+    if constexpr (kUpd) {
+      const float* Wr =
+          (a.Wsrc ? a.Wsrc + (long long)g * a.sWsrc : a.W + (long long)g * a.sC) + tile0;
+      const float* Ur = a.U + (long long)g * a.sC + tile0;
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
+      for (int i = 0; i < FM; ++i)
 #pragma unroll
-      for (int j = 0; j < FN; ++j)
+        for (int j = 0; j < FN; ++j)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          int m = out_row(i, v), n = n0 + wn0 + j * 32 + lr;
-          if constexpr (!FULL) {
-            m = min(m, M - 1);
-            n = min(n, N - 1);
+          for (int v = 0; v < 16; ++v) {
+            wv[i][j][v] = Wr[tile_off(i, j, v)];
+            uv[i][j][v] = Ur[tile_off(i, j, v)];
           }
-          const long long o = (long long)m * a.ldc + n;
-          wv[i][j][v] = Wr[o];
-          uv[i][j][v] = Ur[o];
-        }
-  }
+    }
+  };
 
   if constexpr (kRows) {
-    for (int i = tid; i < 512 && kbeg + i < kend; i += kThreads) srmap[i] = rmap[kbeg + i];
+    for (int i = tid; i < 512 && kbeg + i < kend; i += kThreads)
+      srmap[i] = rmap ? rmap[kbeg + i] : kbeg + i;
     __syncthreads();
   }
   // per quad of this thread: the storage offset that does not depend on k
@@ -266,7 +276,8 @@ __global__ __launch_bounds__(kThreads, BM * BN > 128 * 64 ? 1 : 2) void gemm_mm(
     }
   }
   auto arow = [&](int k) __attribute__((always_inline)) {  // storage row of A's k
-    if constexpr (kRows) return (long long)(k - kbeg < 512 ? srmap[k - kbeg] : rmap[k]);
+    if constexpr (kRows)
+      return (long long)(k - kbeg < 512 ? srmap[k - kbeg] : rmap ? rmap[k] : k);
     return (long long)k;
   };
   auto gload = [&](int k0, Q(&xa)[NA], Q(&xb)[NB]) __attribute__((always_inline)) {
@@ -441,6 +452,7 @@ __global__ __launch_bounds__(kThreads, BM * BN > 128 * 64 ? 1 : 2) void gemm_mm(
         __syncthreads();
       }
     }
+    wu_load();  // on their way while the last slabs compute
 #pragma unroll
     for (int d = 0; d < D; ++d) {
       if (it + d >= nk) break;
@@ -476,7 +488,7 @@ __global__ __launch_bounds__(kThreads, BM * BN > 128 * 64 ? 1 : 2) void gemm_mm(
           const int m = min(m0 + wm0 + i * 32 + lr, M - 1), n = min(n0 + wn0 + j * 32 + lr, N - 1);
           for (int k = kbeg; k < kend; k += 2) {
             const int kx = k + lk, kc = min(kx, kend - 1);
-            const long long oa = AT ? (GATHER ? (long long)rmap[kc] : (long long)kc) * a.lda + m
+            const long long oa = AT ? arow(kc) * a.lda + m
                                     : (GATHER ? (long long)rmap[m] : (long long)m) * a.lda + kc;
             const long long ob = BT ? (long long)n * a.ldb + kc : (long long)kc * a.ldb + n;
             const float x = kx < kend ? ((const float*)A)[oa] : 0.f;
@@ -491,6 +503,10 @@ __global__ __launch_bounds__(kThreads, BM * BN > 128 * 64 ? 1 : 2) void gemm_mm(
   // epilogue
   constexpr bool OUTBF = BF && (EPI == EPI_BIAS_RELU || EPI == EPI_RELU_MASK);
   if constexpr (kUpd) {
+    const long long t0 = (long long)g * a.sC + tile0;
+    float* Wt = a.W + t0;
+    float* Ut = a.U + t0;
+    bf16_t* Wbt = a.Wb + t0;
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -499,11 +515,11 @@ __global__ __launch_bounds__(kThreads, BM * BN > 128 * 64 ? 1 : 2) void gemm_mm(
         for (int v = 0; v < 16; ++v) {
           const int m = out_row(i, v), n = n0 + wn0 + j * 32 + lr;
           if (!FULL && (m >= M || n >= N)) continue;
-          const long long o = (long long)g * a.sC + (long long)m * a.ldc + n;
+          const unsigned o = tile_off(i, j, v);
           sgd_step(wv[i][j][v], uv[i][j][v], hi[i][j][v], a);
-          a.W[o] = wv[i][j][v];
-          a.U[o] = uv[i][j][v];
-          if (a.Wb) a.Wb[o] = f32_to_bf16(wv[i][j][v]);
+          Wt[o] = wv[i][j][v];
+          Ut[o] = uv[i][j][v];
+          if (a.Wb) Wbt[o] = f32_to_bf16(wv[i][j][v]);
         }
     if (do_bias) {
       // the threads that share a column's quad, in ascending thread order
@@ -569,362 +585,46 @@ __global__ __launch_bounds__(kThreads, BM * BN > 128 * 64 ? 1 : 2) void gemm_mm(
   }
 }
 
-// ------------------------------------------------- fp32 update, specialised
-// Fused weight gradient + momentum-SGD update over the 128 x 128 tiles of one
-// or several layers (a list of problems whose tiles are concatenated). A
-// workgroup of 8 wavefronts stays resident and walks its share of the tile
-// list; its waves have two roles that run concurrently:
-//   MFMA waves 0-3 each compute a 64 x 64 quarter of tile j. A lane loads its
-//     operands straight from global memory as float2 pairs along m (resp. n);
-//     the two halves of a pair feed two different 32 x 32 MFMA blocks, so
-//     block i's MFMA row r is m = 2 r + i (columns likewise) and no LDS
-//     staging (and so no barrier among the MFMA waves) is needed. A ring of
-//     D k-pairs of registers keeps D loads in flight.
-//   Update waves 4-7 apply the SGD step to tile j-1 from the gradient tile
-//     in LDS (float4 runs along n: coalesced W/U rows), then issue the W/U
-//     reads of tile j, which arrive while tile j's MFMAs run.
-// Two workgroup barriers per tile hand the LDS gradient buffer over. The
-// HBM-bound update of one tile thus overlaps the MFMA phase of the next,
-// where separate workgroups doing both phases in turn fall into step and
-// alternate between compute-only and memory-only periods across the chip.
-// Every problem needs M % 128 == 0, N % 128 == 0, 8-byte aligned operand
-// rows, 16-byte aligned W/U rows and (gathered rows) Kd <= 512; all share
-// lr, momentum, weight decay and Nesterov.
-constexpr int kWsThreads = 512;
-constexpr int kWsMaxRows = 512;
-constexpr int kWsDepth = 8;        // k-pairs of operands in flight per lane
-constexpr int kWsMinTiles = 1024;  // below: one tile per workgroup is as good
+template <bool BF, bool AT, bool BT, int EPI, bool GATHER, int BM, int BN, int BK, int D,
+          bool FULL>
+__global__ __launch_bounds__(kThreads, BM * BN > 128 * 64 ? 1 : 2) void gemm_mm(GemmArgs a) {
+  gemm_tile<BF, AT, BT, EPI, GATHER, BM, BN, BK, D, FULL>(a, decode_tile(a, BM, BN));
+}
 
-struct WsArgs {
-  GemmArgs p[kWsMaxProblems];
-  int start[kWsMaxProblems + 1];  // first tile of each problem; [np] = total
+// Weight gradients fused with their momentum-SGD step, of one or several
+// layers: their 64 x 64 tiles concatenated in one launch. HBM-bound (W and U
+// read and written, 16 B per weight): a workgroup's k loop and its update
+// stream are short, so what counts is how many are in flight -- four per CU
+// (37 KB of LDS at BK = 16, 128 registers) drift apart and keep both busy.
+// 16 x 3072 x 512 from 128 gathered rows: 90 us, 4.7 TB/s with the operands;
+// at three workgroups per CU 101-107, BK = 32 and two 116, and a persistent
+// form of eight waves (four computing 128 x 128 tiles, four updating the tile
+// before) 105 on the fp32 instruction. Ragged tiles (FULL false) need the
+// registers of two slabs for their addresses: D = 2 (12 x 1537 x 771 from 90
+// rows: 69 us, D = 4 77, spilling).
+struct UpdArgs {
+  GemmArgs p[kUpdMaxProblems];
+  int start[kUpdMaxProblems + 1];  // first tile of each problem; [np] = total
   int np;
 };
 
-struct WsTile {
-  int pi, g, m0, n0;
-};
-
-__device__ __forceinline__ bool ws_tile(const WsArgs& w, int j, WsTile& t) {
-  const int total = w.start[w.np];
-  const int p = blockIdx.x, nwg = gridDim.x;
-  int l;
-  if (total % kXcds == 0 && nwg % kXcds == 0) {
-    // XCD x = p % 8 owns tiles [x * total/8, (x+1) * total/8)
-    const int chunk = total / kXcds, q = p / kXcds + j * (nwg / kXcds);
-    if (q >= chunk) return false;
-    l = (p % kXcds) * chunk + q;
-  } else {
-    const long long ll = p + (long long)j * nwg;
-    if (ll >= total) return false;
-    l = (int)ll;
-  }
+template <bool BF, int BK, int D, bool FULL>
+__global__ __launch_bounds__(kThreads, 4) void gemm_update(UpdArgs w) {
+  const int total = w.start[w.np], p = blockIdx.x;
+  int l = (total % kXcds == 0) ? (p % kXcds) * (total / kXcds) + p / kXcds : p;
   int pi = 0;
   while (pi + 1 < w.np && l >= w.start[pi + 1]) ++pi;
   l -= w.start[pi];
-  const int tn = w.p[pi].N / 128, per_g = tn * (w.p[pi].M / 128);
-  t.pi = pi;
+  const GemmArgs& a = w.p[pi];
+  const int tn = (a.N + 63) / 64, per_g = tn * ((a.M + 63) / 64);
+  Tile t;
+  t.s = 0;
   t.g = l / per_g;
   l -= t.g * per_g;
-  t.m0 = (l / tn) * 128;
-  t.n0 = (l % tn) * 128;
-  return true;
+  t.m0 = (l / tn) * 64;
+  t.n0 = (l % tn) * 64;
+  gemm_tile<BF, true, false, EPI_SGD, true, 64, 64, BK, D, FULL>(a, t);
 }
-
-// Row list (sampled dataset indices) of a gathered tile: thread t < 256 of
-// the MFMA role holds entries t and t + 256 (clamped to the last row).
-struct WsRows {
-  int32_t r0, r1;
-};
-__device__ __forceinline__ WsRows ws_rows_load(const WsArgs& w, const WsTile& t) {
-  const GemmArgs& a = w.p[t.pi];
-  const int32_t* rm = a.rowmap + (long long)t.g * a.sRow;
-  const int last = a.Kd - 1, i = threadIdx.x;
-  return WsRows{rm[min(i, last)], rm[min(i + 256, last)]};
-}
-__device__ __forceinline__ void ws_rows_store(int32_t* buf, const WsRows& r) {
-  buf[threadIdx.x] = r.r0;
-  buf[threadIdx.x + 256] = r.r1;
-}
-
-// Operand pairs of the MFMA role: two consecutive fp32 values (float2), or
-// two consecutive bf16 values in one 32-bit word, widened to fp32 at use
-// (bf16 x bf16 products are exact in fp32, so the fp32 MFMA computes what a
-// bf16 MFMA with fp32 accumulation does, up to the order of the sums).
-template <bool BF>
-struct WsOp;
-template <>
-struct WsOp<false> {
-  using E = float;
-  using P = float2;
-  __device__ static P ld(const E* p) { return *(const float2*)p; }
-  __device__ static float lo(P v) { return v.x; }
-  __device__ static float hi(P v) { return v.y; }
-};
-template <>
-struct WsOp<true> {
-  using E = bf16_t;
-  using P = uint32_t;
-  __device__ static P ld(const E* p) { return *(const uint32_t*)p; }
-  __device__ static float lo(P v) { return __uint_as_float(v << 16); }
-  __device__ static float hi(P v) { return __uint_as_float(v & 0xffff0000u); }
-};
-
-// k loop of one MFMA wave over a tile (its 64 x 64 quarter): rows
-// k = 2 kp + lk, kp < nkp. A points at column m0 + wm0 + 2 lr of row 0
-// (gathered: row srm[k]), B at column n0 + wn0 + 2 lr of row 0.
-template <bool BF, int D>
-struct WsK {
-  using Op = WsOp<BF>;
-  using E = typename Op::E;
-  using P = typename Op::P;
-
-  __device__ static void mfma(floatx16 (&acc)[2][2], P ra, P rb, float& cs0, float& cs1) {
-    const float a0 = Op::lo(ra), a1 = Op::hi(ra), b0 = Op::lo(rb), b1 = Op::hi(rb);
-    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-    acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-    acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-    cs0 += b0;
-    cs1 += b1;
-  }
-
-  // Any batch size. Rows past the end are clamped to the last one and their
-  // values replaced by zero at use, so the loads carry no branches and stay
-  // countable in flight; a runtime loop's back edge still makes the compiler
-  // wait for all of them at the top of each block.
-  __device__ static void generic(floatx16 (&acc)[2][2], const E* A, const E* B,
-                                 long long lda, long long ldb, int Kd, bool gather,
-                                 const int32_t* srm, int lk, float& cs0, float& cs1) {
-    P ra[D], rb[D];
-    auto load = [&](int kp, P& x, P& y) __attribute__((always_inline)) {
-      const int k = min(2 * kp + lk, Kd - 1);
-      const int sr = srm[min(k, kWsMaxRows - 1)];
-      const long long row = gather ? (long long)sr : (long long)k;
-      x = Op::ld(A + row * lda);
-      y = Op::ld(B + (long long)k * ldb);
-    };
-#pragma unroll
-    for (int d = 0; d < D; ++d) load(d, ra[d], rb[d]);
-    const int nblk = ((Kd + 1) / 2 + D - 1) / D;
-    for (int blk = 0; blk < nblk; ++blk) {
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        const int kp = blk * D + d;
-        const bool live = 2 * kp + lk < Kd;
-        const P za = live ? ra[d] : P{}, zb = live ? rb[d] : P{};
-        mfma(acc, za, zb, cs0, cs1);
-        load(kp + D, ra[d], rb[d]);
-        // keep each refill right behind its slot's MFMAs: left alone, the
-        // scheduler sinks the refills to the end of the block, where they
-        // have no time left to arrive
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  }
-
-  // ROWS (64 or 128) rows in straight-line code: the wait before each slot's
-  // MFMAs counts exactly the D - 1 younger refills. The row indices sit in
-  // ROWS / 64 registers per lane (rows lane, lane + 64) and a refill takes
-  // its row by readlane at a compile-time lane instead of waiting on an LDS
-  // read between MFMAs; B rows walk with one running pointer.
-  template <int ROWS>
-  __device__ static void unrolled(floatx16 (&acc)[2][2], const E* A, const E* B,
-                                  long long lda, long long ldb, bool gather,
-                                  const int32_t* srm, int lane, int lk, float& cs0,
-                                  float& cs1) {
-    static_assert(ROWS == 64 || ROWS == 128, "one or two index registers per lane");
-    constexpr int NKP = ROWS / 2;
-    P ra[D], rb[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      const int k = 2 * d + lk;
-      const long long row = gather ? (long long)srm[k] : (long long)k;
-      ra[d] = Op::ld(A + row * lda);
-      rb[d] = Op::ld(B + (long long)k * ldb);
-    }
-    const int r_lo = srm[lane], r_hi = ROWS > 64 ? srm[lane + 64] : 0;
-    const E* bq = B + (long long)(2 * D + lk) * ldb;
-    const long long bstep = 2 * ldb;
-#pragma unroll
-    for (int kp = 0; kp < NKP; ++kp) {
-      const int d = kp % D;
-      const P ca = ra[d], cb = rb[d];
-      const float a0 = Op::lo(ca), a1 = Op::hi(ca), b0 = Op::lo(cb), b1 = Op::hi(cb);
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-      if (kp + D < NKP) {
-        // refill of this slot with k-pair kp + D, between the MFMAs
-        const int ke = 2 * (kp + D);
-        const int src = ke < 64 ? r_lo : r_hi;
-        const int se = __builtin_amdgcn_readlane(src, ke & 63);
-        const int so = __builtin_amdgcn_readlane(src, (ke + 1) & 63);
-        const long long row = gather ? (long long)(lk ? so : se) : (long long)(ke + lk);
-        ra[d] = Op::ld(A + row * lda);
-      }
-      acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-      if (kp + D < NKP) {
-        rb[d] = Op::ld(bq);
-        bq += bstep;
-      }
-      acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-      cs0 += b0;
-      cs1 += b1;
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-};
-
-// Both roles walk the same tile list and execute the same barriers: one
-// before the first tile, then two per tile.
-template <bool BF, int D>
-__global__ __launch_bounds__(kWsThreads) void gemm_f32_sgd_ws(WsArgs w) {
-  using K = WsK<BF, D>;
-  using E = typename K::E;
-  constexpr int T = 128, CP = T + 4;  // gradient tile pitch (16-byte rows)
-  constexpr int PER = T * T / 4 / 256;  // float4 per update thread
-  __shared__ __attribute__((aligned(16))) float Gs[T * CP];
-  // row lists, double-buffered: tile j reads buffer j % 2 while the MFMA
-  // role writes tile j+1's list into the other one after its k loop
-  __shared__ int32_t srmap[2][kWsMaxRows];
-  // wave index as a scalar: the role branch below is uniform per wave
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  WsTile cur, prev;
-  bool prev_ok = false;
-
-  if (wave < 4) {
-    // ---- MFMA role: gradient tile j into LDS
-    const int lk = lane >> 5, lr = lane & 31;
-    const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * 64;
-    {
-      WsTile t0;
-      if (ws_tile(w, 0, t0) && w.p[t0.pi].rowmap) ws_rows_store(srmap[0], ws_rows_load(w, t0));
-    }
-    __syncthreads();  // row list of the first tile
-    for (int j = 0;; ++j) {
-      const bool ok = ws_tile(w, j, cur);  // uniform over the workgroup
-      if (!ok && !prev_ok) break;
-      floatx16 acc[2][2];
-      if (ok) {
-        // next tile's row list: issued now, stored after the k loop
-        WsTile nxt;
-        const bool nxt_rows = ws_tile(w, j + 1, nxt) && w.p[nxt.pi].rowmap;
-        WsRows nr{0, 0};
-        if (nxt_rows) nr = ws_rows_load(w, nxt);
-
-        const GemmArgs& a = w.p[cur.pi];
-        const int Kd = a.Kd;
-        const bool gather = a.rowmap != nullptr;
-        const int32_t* srm = srmap[j & 1];
-        const E* A = (const E*)a.A + (long long)cur.g * a.sA + cur.m0 + wm0 + 2 * lr;
-        const E* B = (const E*)a.B + (long long)cur.g * a.sB + cur.n0 + wn0 + 2 * lr;
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][jj][v] = 0.f;
-        float cs0 = 0.f, cs1 = 0.f;
-        if (Kd == 128)
-          K::template unrolled<128>(acc, A, B, a.lda, a.ldb, gather, srm, lane, lk, cs0, cs1);
-        else if (Kd == 64)
-          K::template unrolled<64>(acc, A, B, a.lda, a.ldb, gather, srm, lane, lk, cs0, cs1);
-        else
-          K::generic(acc, A, B, a.lda, a.ldb, Kd, gather, srm, lk, cs0, cs1);
-        if (nxt_rows) ws_rows_store(srmap[(j + 1) & 1], nr);
-        if (a.bias_w && cur.m0 == 0 && wm0 == 0) {
-          // lanes < 32 summed the even batch rows, lanes >= 32 the odd ones
-          cs0 += __shfl_xor(cs0, 32, 64);
-          cs1 += __shfl_xor(cs1, 32, 64);
-          if (lk == 0) {
-            const int n = cur.n0 + wn0 + 2 * lr;
-            bias_update(a, cur.g, n, cs0);
-            bias_update(a, cur.g, n + 1, cs1);
-          }
-        }
-      }
-      __syncthreads();  // the update role has consumed gradient tile j-1
-      if (ok) {
-        // accumulator v of block (i, jj): row 8(v/4) + 4 lk + v%4, column lr
-        // of the block, i.e. tile row wm0 + 2 R + i, column wn0 + 2 lr + jj
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int R = (v >> 2) * 8 + lk * 4 + (v & 3);
-            *(float2*)&Gs[(wm0 + 2 * R + i) * CP + wn0 + 2 * lr] =
-                make_float2(acc[i][0][v], acc[i][1][v]);
-          }
-      }
-      __syncthreads();  // gradient tile j (and tile j+1's row list) in LDS
-      prev_ok = ok;
-    }
-  } else {
-    // ---- update role: SGD step of tile j-1, then tile j's W/U reads
-    const int u = (int)threadIdx.x - 256;
-    float4 wv[PER], uv[PER];
-    __syncthreads();  // row list of the first tile
-    for (int j = 0;; ++j) {
-      const bool ok = ws_tile(w, j, cur);
-      if (!ok && !prev_ok) break;
-      if (prev_ok) {
-        const GemmArgs& a = w.p[prev.pi];
-#pragma unroll
-        for (int p = 0; p < PER; ++p) {
-          const int r = u / 32 + 8 * p, c = (u % 32) * 4;
-          const long long off = (long long)prev.g * a.sC +
-                                (long long)(prev.m0 + r) * a.ldc + prev.n0 + c;
-          const float4 gr = *(const float4*)&Gs[r * CP + c];
-          float4 wq = wv[p], uq = uv[p];
-          sgd_step(wq.x, uq.x, gr.x, a);
-          sgd_step(wq.y, uq.y, gr.y, a);
-          sgd_step(wq.z, uq.z, gr.z, a);
-          sgd_step(wq.w, uq.w, gr.w, a);
-          *(float4*)(a.W + off) = wq;
-          *(float4*)(a.U + off) = uq;
-          if (a.Wb) {
-            const uint32_t lo = f32_to_bf16(wq.x) | ((uint32_t)f32_to_bf16(wq.y) << 16);
-            const uint32_t hi = f32_to_bf16(wq.z) | ((uint32_t)f32_to_bf16(wq.w) << 16);
-            *(uint2*)(a.Wb + off) = make_uint2(lo, hi);
-          }
-        }
-      }
-      if (ok) {
-        const GemmArgs& a = w.p[cur.pi];
-#pragma unroll
-        for (int p = 0; p < PER; ++p) {
-          const int r = u / 32 + 8 * p, c = (u % 32) * 4;
-          const long long in = (long long)(cur.m0 + r) * a.ldc + cur.n0 + c;
-          const long long off = (long long)cur.g * a.sC + in;
-          wv[p] = *(const float4*)(a.Wsrc ? a.Wsrc + (long long)cur.g * a.sWsrc + in
-                                          : a.W + off);
-          uv[p] = *(const float4*)(a.U + off);
-        }
-      }
-      __syncthreads();  // gradient tile j-1 consumed
-      __syncthreads();  // gradient tile j is in LDS
-      prev = cur;
-      prev_ok = ok;
-    }
-  }
-}
-
-// Shape and alignment rules of the specialised kernel for one problem.
-// fp32 operands are read as float2, bf16 operands as pairs in one 32-bit word.
-bool ws_eligible(int dtype, const GemmArgs& a) {
-  auto al = [](const void* p, uintptr_t m) { return ((uintptr_t)p & m) == 0; };
-  const uintptr_t pair = dtype == 0 ? 7 : 3;
-  return (dtype == 0 || dtype == 1) && a.splits <= 1 && a.G > 0 && a.M > 0 &&
-         a.N > 0 && a.Kd > 0 && a.M % 128 == 0 && a.N % 128 == 0 &&
-         (a.rowmap == nullptr || a.Kd <= kWsMaxRows) &&
-         a.lda % 2 == 0 && a.sA % 2 == 0 && al(a.A, pair) &&
-         a.ldb % 2 == 0 && a.sB % 2 == 0 && al(a.B, pair) &&
-         a.ldc % 4 == 0 && a.sC % 4 == 0 && al(a.W, 15) && al(a.U, 15) &&
-         (a.Wb == nullptr || al(a.Wb, 7)) &&
-         (a.Wsrc == nullptr || (al(a.Wsrc, 15) && a.sWsrc % 4 == 0));
-}
-
 
 // ------------------------------------------------------------------ split-K
 // C[g][m][n] = epilogue(sum_{s=0}^{S-1} part[s][g][m][n]), s ascending. S is
@@ -959,78 +659,6 @@ hipError_t launch_reduce(const GemmArgs& a, hipStream_t s) {
   }
   return hipGetLastError();
 }
-
-// Compute units and resident specialised-update workgroups per CU on the
-// current device, queried once per device.
-template <bool BF>
-hipError_t ws_grid(long long tiles, int& grid) {
-  struct Shape {
-    int cus = 0, per_cu = 0;
-  };
-  static Shape cache[64];
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  if (cache[dev].cus == 0) {
-    Shape sh;
-    e = hipDeviceGetAttribute(&sh.cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &sh.per_cu, reinterpret_cast<const void*>(gemm_f32_sgd_ws<BF, kWsDepth>),
-        kWsThreads, 0);
-    if (e != hipSuccess) return e;
-    if (sh.per_cu < 1) sh.per_cu = 1;
-    cache[dev] = sh;
-  }
-  long long g = (long long)cache[dev].cus * cache[dev].per_cu;
-  if (g > tiles) g = tiles;
-  if (g >= kXcds) g -= g % kXcds;
-  grid = (int)g;
-  return hipSuccess;
-}
-
-}  // namespace
-
-int gemm_sgd_multi_tiles(int dtype, const GemmArgs* list, int n) {
-  if (n < 1 || n > kWsMaxProblems) return -1;
-  long long total = 0;
-  for (int i = 0; i < n; ++i) {
-    if (!ws_eligible(dtype, list[i])) return -1;
-    total += (long long)(list[i].M / 128) * (list[i].N / 128) * list[i].G;
-  }
-  return total < (1LL << 30) ? (int)total : -1;
-}
-
-hipError_t launch_gemm_sgd_multi(int dtype, const GemmArgs* list, int n,
-                                 hipStream_t s) {
-  const int total = gemm_sgd_multi_tiles(dtype, list, n);
-  if (total < 0) return hipErrorInvalidValue;
-  if (total == 0) return hipSuccess;
-  WsArgs w{};
-  w.np = n;
-  w.start[0] = 0;
-  for (int i = 0; i < n; ++i) {
-    w.p[i] = list[i];
-    w.p[i].splits = 1;
-    w.start[i + 1] = w.start[i] + (list[i].M / 128) * (list[i].N / 128) * list[i].G;
-    if (i > 0 && (list[i].lr != list[0].lr || list[i].mom != list[0].mom ||
-                  list[i].wd != list[0].wd || list[i].nesterov != list[0].nesterov))
-      return hipErrorInvalidValue;
-  }
-  int grid = 0;
-  hipError_t e = dtype == 1 ? ws_grid<true>(total, grid) : ws_grid<false>(total, grid);
-  if (e != hipSuccess) return e;
-  if (dtype == 1)
-    hipLaunchKernelGGL((gemm_f32_sgd_ws<true, kWsDepth>), dim3(grid), dim3(kWsThreads),
-                       0, s, w);
-  else
-    hipLaunchKernelGGL((gemm_f32_sgd_ws<false, kWsDepth>), dim3(grid), dim3(kWsThreads),
-                       0, s, w);
-  return hipGetLastError();
-}
-
-namespace {
 
 // Tile of a forward, input-gradient or plain product. Larger tiles read less
 // from LDS per MFMA, but a launch should have a workgroup for each of the 256
@@ -1074,38 +702,28 @@ hipError_t run_tile(const GemmArgs& a, hipStream_t s) {
 
 template <bool BF, bool AT, bool BT, int EPI, bool GATHER>
 hipError_t run_type(const GemmArgs& a, hipStream_t s) {
-  if constexpr (EPI == EPI_SGD) {
-    return run_tile<BF, AT, BT, EPI, GATHER, 64, 64, 32, 2>(a, s);
-  } else {
-    const Shape sh = tile_shape(BF, a.M, a.N, a.G, a.Kd);
-    hipError_t e;
-    if (sh.BM == 64)
-      e = run_tile<BF, AT, BT, EPI, GATHER, 64, 64, BF ? 64 : 32, 2>(a, s);
-    else if (BF || sh.BN == 64)
-      e = run_tile<BF, AT, BT, EPI, GATHER, 128, 64, BF ? 32 : 16, 2>(a, s);
-    else
-      e = run_tile<BF, AT, BT, EPI, GATHER, 128, BF ? 64 : 128, BF ? 32 : 16, 2>(a, s);
-    if (e != hipSuccess || a.splits == 1) return e;
-    constexpr bool OUTBF = BF && (EPI == EPI_BIAS_RELU || EPI == EPI_RELU_MASK);
-    return launch_reduce<EPI, OUTBF>(a, s);
-  }
+  const Shape sh = tile_shape(BF, a.M, a.N, a.G, a.Kd);
+  hipError_t e;
+  if (sh.BM == 64)
+    e = run_tile<BF, AT, BT, EPI, GATHER, 64, 64, BF ? 64 : 32, 2>(a, s);
+  else if (BF || sh.BN == 64)
+    e = run_tile<BF, AT, BT, EPI, GATHER, 128, 64, BF ? 32 : 16, 2>(a, s);
+  else
+    e = run_tile<BF, AT, BT, EPI, GATHER, 128, BF ? 64 : 128, BF ? 32 : 16, 2>(a, s);
+  if (e != hipSuccess || a.splits == 1) return e;
+  constexpr bool OUTBF = BF && (EPI == EPI_BIAS_RELU || EPI == EPI_RELU_MASK);
+  return launch_reduce<EPI, OUTBF>(a, s);
 }
 
 template <bool AT, bool BT, int EPI, bool GATHER>
 hipError_t run(int dtype, const GemmArgs& a, hipStream_t s) {
-  if constexpr (AT && !BT && EPI == EPI_SGD) {
-    // one large layer: the specialised update kernel with a one-item list
-    if (ws_eligible(dtype, a) &&
-        (long long)(a.M / 128) * (a.N / 128) * a.G >= kWsMinTiles)
-      return launch_gemm_sgd_multi(dtype, &a, 1, s);
-  }
   return dtype == 1 ? run_type<true, AT, BT, EPI, GATHER>(a, s)
                     : run_type<false, AT, BT, EPI, GATHER>(a, s);
 }
 
 template <bool AT, bool BT, int EPI>
 hipError_t dispatch(int dtype, const GemmArgs& a, hipStream_t s) {
-  if (a.rowmap) {  // gathered rows: the first layer's forward and update
+  if (a.rowmap) {  // gathered rows: the first layer's forward
     if constexpr (EPI == EPI_STORE || EPI == EPI_RELU_MASK)
       return hipErrorInvalidValue;
     else
@@ -1116,8 +734,37 @@ hipError_t dispatch(int dtype, const GemmArgs& a, hipStream_t s) {
 
 }  // namespace
 
+hipError_t launch_gemm_update(int dtype, const GemmArgs* list, int n, hipStream_t s) {
+  if (n < 1 || n > kUpdMaxProblems) return hipErrorInvalidValue;
+  UpdArgs w{};
+  w.np = n;
+  bool whole = true;
+  long long total = 0;
+  for (int i = 0; i < n; ++i) {
+    GemmArgs& a = w.p[i];
+    a = list[i];
+    if (a.G <= 0 || a.M <= 0 || a.N <= 0 || a.Kd <= 0) return hipErrorInvalidValue;
+    a.splits = 1;
+    a.kchunk = (a.Kd + 31) / 32 * 32;
+    whole = whole && full(a, 64, 64, 32);
+    w.start[i] = (int)total;
+    total += (long long)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.G;
+    if (total > 0x7fffffffLL) return hipErrorInvalidValue;
+  }
+  w.start[n] = (int)total;
+  const dim3 grid((unsigned)total), block(kThreads);
+  if (dtype == 1 && whole)
+    hipLaunchKernelGGL((gemm_update<true, 32, 2, true>), grid, block, 0, s, w);
+  else if (dtype == 1)
+    hipLaunchKernelGGL((gemm_update<true, 32, 2, false>), grid, block, 0, s, w);
+  else if (whole)
+    hipLaunchKernelGGL((gemm_update<false, 16, 4, true>), grid, block, 0, s, w);
+  else
+    hipLaunchKernelGGL((gemm_update<false, 16, 2, false>), grid, block, 0, s, w);
+  return hipGetLastError();
+}
+
 int gemm_splits(int dtype, int M, int N, int Kd, int G, int epi) {
-  if (epi == EPI_SGD) return 1;
   const Shape sh = tile_shape(dtype == 1, M, N, G, Kd);
   const long long tiles = (long long)((N + sh.BN - 1) / sh.BN) * ((M + sh.BM - 1) / sh.BM) * G;
   const int want = sh.BM * sh.BN == 128 * 64 ? 512 : 256;
@@ -1133,7 +780,7 @@ hipError_t launch_gemm(int dtype, int trans_a, int trans_b, int epi,
   if (args.G <= 0 || args.M <= 0 || args.N <= 0 || args.Kd <= 0) return hipSuccess;
   GemmArgs a = args;
   if (a.splits < 1) a.splits = 1;
-  if (a.splits > 1 && (a.part == nullptr || epi == EPI_SGD)) return hipErrorInvalidValue;
+  if (a.splits > 1 && a.part == nullptr) return hipErrorInvalidValue;
   a.kchunk = (a.Kd + a.splits - 1) / a.splits;
   a.kchunk = (a.kchunk + 31) / 32 * 32;
   // activations are bf16 exactly when the operands are
@@ -1156,9 +803,6 @@ hipError_t launch_gemm(int dtype, int trans_a, int trans_b, int epi,
       break;
     case EPI_RELU_MASK:
       if (key == 1) return dispatch<false, true, EPI_RELU_MASK>(dtype, a, s);
-      break;
-    case EPI_SGD:
-      if (key == 2) return dispatch<true, false, EPI_SGD>(dtype, a, s);
       break;
     default:
       break;

@@ -37,6 +37,7 @@ enum Epilogue : int {
   EPI_BIAS_RELU = 2,   // C = relu(acc + bias[n]) (activation dtype)
   EPI_RELU_MASK = 3,   // C = acc * (mask[m][n] > 0) (activation dtype)
   EPI_SGD = 4          // fused parameter update of W[m][n] with acc as grad
+                       //   (launch_gemm_update)
 };
 
 struct GemmArgs {
@@ -88,15 +89,11 @@ int gemm_splits(int dtype, int M, int N, int Kd, int G, int epi);
 hipError_t launch_gemm(int dtype, int trans_a, int trans_b, int epi,
                        int out_bf16, const GemmArgs& a, hipStream_t s);
 
-// Fused weight gradient + update (trans_a = 1, trans_b = 0, EPI_SGD) of up to
-// kWsMaxProblems layers in one persistent launch, their tiles concatenated.
-// gemm_sgd_multi_tiles: the list's total 128 x 128 tile count, or -1 when a
-// problem does not fit the kernel (fp32, M and N multiples of 128, aligned
-// rows, at most 512 gathered rows).
-constexpr int kWsMaxProblems = 8;
-int gemm_sgd_multi_tiles(int dtype, const GemmArgs* list, int n);
-hipError_t launch_gemm_sgd_multi(int dtype, const GemmArgs* list, int n,
-                                 hipStream_t s);
+// Fused weight gradient + update (trans_a = 1, trans_b = 0, EPI_SGD; a null
+// row map: A's rows in order) of up to kUpdMaxProblems layers in one launch,
+// their tiles concatenated.
+constexpr int kUpdMaxProblems = 8;
+hipError_t launch_gemm_update(int dtype, const GemmArgs* list, int n, hipStream_t s);
 
 // ---------------------------------------------------------------- head
 // Output layer with few classes, fused around the loss (head.hip).
