@@ -180,8 +180,9 @@ struct Quad<true> {
 // FULL: whole tiles and whole slabs (checked at launch). Otherwise rows past
 // the end are clamped, and slabs or tiles that reach past K or past the
 // columns of a k-slow operand take element loads (a uniform branch).
+// NT: the update's W and U pass by the caches (see gemm_update).
 template <bool BF, bool AT, bool BT, int EPI, bool GATHER, int BM, int BN, int BK, int D,
-          bool FULL>
+          bool FULL, bool NT = false>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t) {
   using Q = Quad<BF>;
   using E = typename Q::E;
@@ -240,8 +241,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t) {
         for (int j = 0; j < FN; ++j)
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
-            wv[i][j][v] = Wr[tile_off(i, j, v)];
-            uv[i][j][v] = Ur[tile_off(i, j, v)];
+            const float* wp = Wr + tile_off(i, j, v);
+            const float* up = Ur + tile_off(i, j, v);
+            wv[i][j][v] = NT ? __builtin_nontemporal_load(wp) : *wp;
+            uv[i][j][v] = NT ? __builtin_nontemporal_load(up) : *up;
           }
     }
   };
@@ -517,8 +520,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t) {
           if (!FULL && (m >= M || n >= N)) continue;
           const unsigned o = tile_off(i, j, v);
           sgd_step(wv[i][j][v], uv[i][j][v], hi[i][j][v], a);
-          Wt[o] = wv[i][j][v];
-          Ut[o] = uv[i][j][v];
+          if constexpr (NT) {
+            __builtin_nontemporal_store(wv[i][j][v], Wt + o);
+            __builtin_nontemporal_store(uv[i][j][v], Ut + o);
+          } else {
+            Wt[o] = wv[i][j][v];
+            Ut[o] = uv[i][j][v];
+          }
           if (a.Wb) Wbt[o] = f32_to_bf16(wv[i][j][v]);
         }
     if (do_bias) {
@@ -601,15 +609,18 @@ __global__ __launch_bounds__(kThreads, BM * BN > 128 * 64 ? 1 : 2) void gemm_mm(
 // form of eight waves (four computing 128 x 128 tiles, four updating the tile
 // before) 105 on the fp32 instruction. Ragged tiles (FULL false) need the
 // registers of two slabs for their addresses: D = 2 (12 x 1537 x 771 from 90
-// rows: 69 us, D = 4 77, spilling).
+// rows: 69 us, D = 4 77, spilling). NT: a state beyond the 256 MB Infinity
+// Cache is streamed past the caches (64 x 3072 x 2048: fp32 1292 -> 1190 us,
+// bf16 1427 -> 1347 us, 5.4 TB/s; a state that fits loses the lines the next
+// step reads: 86 -> 92 us).
 struct UpdArgs {
   GemmArgs p[kUpdMaxProblems];
   int start[kUpdMaxProblems + 1];  // first tile of each problem; [np] = total
   int np;
 };
 
-template <bool BF, int BK, int D, bool FULL>
-__global__ __launch_bounds__(kThreads, 4) void gemm_update(UpdArgs w) {
+template <bool BF, int BK, int D, bool FULL, bool NT>
+__global__ __launch_bounds__(kThreads, BK == 64 ? 3 : 4) void gemm_update(UpdArgs w) {
   const int total = w.start[w.np], p = blockIdx.x;
   int l = (total % kXcds == 0) ? (p % kXcds) * (total / kXcds) + p / kXcds : p;
   int pi = 0;
@@ -623,7 +634,7 @@ __global__ __launch_bounds__(kThreads, 4) void gemm_update(UpdArgs w) {
   l -= t.g * per_g;
   t.m0 = (l / tn) * 64;
   t.n0 = (l % tn) * 64;
-  gemm_tile<BF, true, false, EPI_SGD, true, 64, 64, BK, D, FULL>(a, t);
+  gemm_tile<BF, true, false, EPI_SGD, true, 64, 64, BK, D, FULL, NT>(a, t);
 }
 
 // ------------------------------------------------------------------ split-K
@@ -734,12 +745,15 @@ hipError_t dispatch(int dtype, const GemmArgs& a, hipStream_t s) {
 
 }  // namespace
 
+// State from which the update streams past the caches.
+constexpr long long kNtBytes = 240LL << 20;
+
 hipError_t launch_gemm_update(int dtype, const GemmArgs* list, int n, hipStream_t s) {
   if (n < 1 || n > kUpdMaxProblems) return hipErrorInvalidValue;
   UpdArgs w{};
   w.np = n;
   bool whole = true;
-  long long total = 0;
+  long long total = 0, state = 0;  // tiles; bytes of W, U and the bf16 copy
   for (int i = 0; i < n; ++i) {
     GemmArgs& a = w.p[i];
     a = list[i];
@@ -747,20 +761,31 @@ hipError_t launch_gemm_update(int dtype, const GemmArgs* list, int n, hipStream_
     a.splits = 1;
     a.kchunk = (a.Kd + 31) / 32 * 32;
     whole = whole && full(a, 64, 64, 32);
+    state += (long long)a.G * a.M * a.N * (a.Wb ? 10 : 8);
     w.start[i] = (int)total;
     total += (long long)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.G;
     if (total > 0x7fffffffLL) return hipErrorInvalidValue;
   }
   w.start[n] = (int)total;
+  // bf16 takes whole tiles in slabs of 64 (16 x 3072 x 512: 94 against 95 us)
+  for (int i = 0; dtype == 1 && i < n; ++i) whole = whole && w.p[i].Kd % 64 == 0;
+  const bool nt = state >= kNtBytes;
   const dim3 grid((unsigned)total), block(kThreads);
-  if (dtype == 1 && whole)
-    hipLaunchKernelGGL((gemm_update<true, 32, 2, true>), grid, block, 0, s, w);
-  else if (dtype == 1)
-    hipLaunchKernelGGL((gemm_update<true, 32, 2, false>), grid, block, 0, s, w);
-  else if (whole)
-    hipLaunchKernelGGL((gemm_update<false, 16, 4, true>), grid, block, 0, s, w);
-  else
-    hipLaunchKernelGGL((gemm_update<false, 16, 2, false>), grid, block, 0, s, w);
+#define LSGD_UPD(BF, BK, D, FULL)                                                        \
+  if (nt)                                                                                \
+    hipLaunchKernelGGL((gemm_update<BF, BK, D, FULL, true>), grid, block, 0, s, w);      \
+  else                                                                                   \
+    hipLaunchKernelGGL((gemm_update<BF, BK, D, FULL, false>), grid, block, 0, s, w)
+  if (dtype == 1 && whole) {
+    LSGD_UPD(true, 64, 2, true);
+  } else if (dtype == 1) {
+    LSGD_UPD(true, 32, 2, false);
+  } else if (whole) {
+    LSGD_UPD(false, 16, 4, true);
+  } else {
+    LSGD_UPD(false, 16, 2, false);
+  }
+#undef LSGD_UPD
   return hipGetLastError();
 }
 
