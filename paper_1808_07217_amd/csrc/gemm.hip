@@ -133,6 +133,16 @@ struct Quad<false> {
   __device__ __forceinline__ void load(const E* p) { v = *(const v4f_any*)p; }
   __device__ __forceinline__ void set(int e, const E* p, bool ok) { v[e] = ok ? *p : 0.f; }
   __device__ __forceinline__ void zero() { v = v4f{0.f, 0.f, 0.f, 0.f}; }
+  // elements s .. s + 3 of the quad and whatever follows (s >= 4: none of it)
+  __device__ __forceinline__ void shift(int s) {
+    if (s & 1) v = v4f{v[1], v[2], v[3], v[3]};
+    if (s & 2) v = v4f{v[2], v[3], v[3], v[3]};
+  }
+  // the first n elements, zeros behind them
+  __device__ __forceinline__ void keep(int n) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = e < n ? v[e] : 0.f;
+  }
   __device__ __forceinline__ void planes(u32x2 (&q)[3]) const {
     uint32_t a[3], b[3];
     split3(v[0], v[1], a);
@@ -158,6 +168,14 @@ struct Quad<true> {
       v.y = w;
   }
   __device__ __forceinline__ void zero() { v = u32x2{0u, 0u}; }
+  __device__ __forceinline__ void shift(int s) {
+    if (s & 1) v = u32x2{(v.x >> 16) | (v.y << 16), v.y >> 16};
+    if (s & 2) v = u32x2{v.y, v.y};
+  }
+  __device__ __forceinline__ void keep(int n) {
+    v.x = n > 1 ? v.x : n > 0 ? v.x & 0xffffu : 0u;
+    v.y = n > 3 ? v.y : n > 2 ? v.y & 0xffffu : 0u;
+  }
   __device__ __forceinline__ void planes(u32x2 (&q)[1]) const { q[0] = v; }
   __device__ __forceinline__ v4f f32() const {
     return v4f{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
@@ -177,28 +195,35 @@ struct Quad<true> {
 // -- no transposition on the way in -- and is read with ds_read_b64_tr_b16,
 // which gives each lane of 16 its column's four k from a 4 x 16 block (pitch
 // + 64 bytes: four rows of a block in disjoint banks).
-// FULL: whole tiles and whole slabs (checked at launch). Otherwise rows past
-// the end are clamped, and slabs or tiles that reach past K or past the
-// columns of a k-slow operand take element loads (a uniform branch).
+// FULL: whole tiles and whole slabs (checked at launch). Otherwise every load
+// still is one vector load at a clamped address, and what a ragged edge needs
+// (a shift, zeros) is done as the quad goes to LDS: loads behind a branch would
+// each be waited for.
 // NT: the update's W and U pass by the caches (see gemm_update).
+// LDS: one plane of an operand of R rows (columns) and its pitch, in elements;
+// two buffers of an operand's planes.
+constexpr int kMapRows = 512;
+constexpr int plane_pitch(bool kc, int R, int BK) { return kc ? BK + 8 : R + 32; }
+constexpr int plane_size(bool kc, int R, int BK) { return (kc ? R : BK) * plane_pitch(kc, R, BK); }
+constexpr int ring_size(bool bf, bool kc, int R, int BK) {
+  return 2 * (bf ? 1 : 3) * plane_size(kc, R, BK);
+}
 template <bool BF, bool AT, bool BT, int EPI, bool GATHER, int BM, int BN, int BK, int D,
           bool FULL, bool NT = false>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t) {
+__device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t, bf16_t* sA,
+                                          bf16_t* sB, int32_t* srmap) {
   using Q = Quad<BF>;
   using E = typename Q::E;
   constexpr int NPL = Q::kPlanes;
   constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 32, FN = WN / 32;
   constexpr bool AK = !AT, BKc = BT;  // k contiguous in storage
-  constexpr int PA = AK ? BK + 8 : BM + 32, PB = BKc ? BK + 8 : BN + 32;
-  constexpr int SA = (AK ? BM : BK) * PA, SB = (BKc ? BN : BK) * PB;  // one plane
+  constexpr int PA = plane_pitch(AK, BM, BK), PB = plane_pitch(BKc, BN, BK);
+  constexpr int SA = plane_size(AK, BM, BK), SB = plane_size(BKc, BN, BK);
   constexpr int NA = BM * BK / 4 / kThreads, NB = BN * BK / 4 / kThreads;
   static_assert(NA >= 1 && NB >= 1 && D % 2 == 0, "tile too small");
-  __shared__ __attribute__((aligned(16))) bf16_t sA[2 * NPL * SA];
-  __shared__ __attribute__((aligned(16))) bf16_t sB[2 * NPL * SB];
   // the k rows of A come from a row map (an update's may have none: its rows
-  // in order)
+  // in order), the first kMapRows of it in LDS
   constexpr bool kRows = AT && GATHER;
-  __shared__ int32_t srmap[kRows ? 512 : 1];  // beyond: read the map itself
 
   const int g = t.g, m0 = t.m0, n0 = t.n0;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -250,97 +275,123 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t) {
   };
 
   if constexpr (kRows) {
-    for (int i = tid; i < 512 && kbeg + i < kend; i += kThreads)
+    for (int i = tid; i < kMapRows && kbeg + i < kend; i += kThreads)
       srmap[i] = rmap ? rmap[kbeg + i] : kbeg + i;
     __syncthreads();
   }
   // per quad of this thread: the storage offset that does not depend on k
+  // (ragged tiles: rows clamped; a quad that reaches past the columns of a
+  // k-slow operand is read four before their end and shifted into place)
   long long offA[NA], offB[NB];
+  int shA[NA], shB[NB];
 #pragma unroll
   for (int i = 0; i < NA; ++i) {
     const int q = tid + i * kThreads;
+    shA[i] = 0;
     if constexpr (AK) {
       int r = m0 + q / (BK / 4);
       if constexpr (!FULL) r = min(r, M - 1);
-      offA[i] = (GATHER ? (long long)rmap[r] : (long long)r) * a.lda + (q % (BK / 4)) * 4;
+      offA[i] = (GATHER ? (long long)rmap[r] : (long long)r) * a.lda;
     } else {
-      offA[i] = m0 + (q % (BM / 4)) * 4;
+      const int c = m0 + (q % (BM / 4)) * 4, cc = FULL ? c : max(min(c, M - 4), 0);
+      offA[i] = cc;
+      shA[i] = c - cc;
     }
   }
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
     const int q = tid + i * kThreads;
+    shB[i] = 0;
     if constexpr (BKc) {
       int r = n0 + q / (BK / 4);
       if constexpr (!FULL) r = min(r, N - 1);
-      offB[i] = (long long)r * a.ldb + (q % (BK / 4)) * 4;
+      offB[i] = (long long)r * a.ldb;
     } else {
-      offB[i] = n0 + (q % (BN / 4)) * 4;
+      const int c = n0 + (q % (BN / 4)) * 4, cc = FULL ? c : max(min(c, N - 4), 0);
+      offB[i] = cc;
+      shB[i] = c - cc;
     }
   }
   auto arow = [&](int k) __attribute__((always_inline)) {  // storage row of A's k
     if constexpr (kRows)
-      return (long long)(k - kbeg < 512 ? srmap[k - kbeg] : rmap ? rmap[k] : k);
+      return (long long)(k - kbeg < kMapRows ? srmap[k - kbeg] : rmap ? rmap[k] : k);
     return (long long)k;
   };
+  // fewer than four elements along the contiguous axis: element loads
+  const bool thin = !FULL && ((AK || BKc ? a.Kd < 4 : false) || (!AK && M < 4) || (!BKc && N < 4));
   auto gload = [&](int k0, Q(&xa)[NA], Q(&xb)[NB]) __attribute__((always_inline)) {
-    const bool ktail = !FULL && k0 + BK > kend;
-    if (ktail || (!FULL && !AK && m0 + BM > M)) {
+    if (!FULL && __builtin_expect(thin, 0)) {
 #pragma unroll
       for (int i = 0; i < NA; ++i) {
         const int q = tid + i * kThreads;
+        const int k = AK ? k0 + (q % (BK / 4)) * 4 : k0 + q / (BM / 4);
+        const int c = AK ? 0 : (int)offA[i] + shA[i];
         xa[i].zero();
-        if constexpr (AK) {
-          const int k = k0 + (q % (BK / 4)) * 4;
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (k + e < kend) xa[i].set(e, A + offA[i] + k0 + e, true);
-        } else {
-          const int k = k0 + q / (BM / 4);
-          if (k < kend) {
-            const E* p = A + arow(k) * a.lda;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              xa[i].set(e, p + min((int)offA[i] + e, M - 1), true);
-          }
+        for (int e = 0; e < 4; ++e) {
+          const int ke = AK ? k + e : k;
+          if (ke < kend && (AK || c + e < M))
+            xa[i].set(e, AK ? A + offA[i] + ke : A + arow(ke) * a.lda + c + e, true);
         }
       }
-    } else {
-#pragma unroll
-      for (int i = 0; i < NA; ++i) {
-        if constexpr (AK)
-          xa[i].load(A + offA[i] + k0);
-        else
-          xa[i].load(A + arow(k0 + (tid + i * kThreads) / (BM / 4)) * a.lda + offA[i]);
-      }
-    }
-    if (ktail || (!FULL && !BKc && n0 + BN > N)) {
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         const int q = tid + i * kThreads;
+        const int k = BKc ? k0 + (q % (BK / 4)) * 4 : k0 + q / (BN / 4);
+        const int c = BKc ? 0 : (int)offB[i] + shB[i];
         xb[i].zero();
-        if constexpr (BKc) {
-          const int k = k0 + (q % (BK / 4)) * 4;
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (k + e < kend) xb[i].set(e, B + offB[i] + k0 + e, true);
-        } else {
-          const int k = k0 + q / (BN / 4);
-          if (k < kend) {
-            const E* p = B + (long long)k * a.ldb;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              xb[i].set(e, p + min((int)offB[i] + e, N - 1), true);
-          }
+        for (int e = 0; e < 4; ++e) {
+          const int ke = BKc ? k + e : k;
+          if (ke < kend && (BKc || c + e < N))
+            xb[i].set(e, BKc ? B + offB[i] + ke : B + (long long)ke * a.ldb + c + e, true);
         }
       }
-    } else {
+      return;
+    }
 #pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        if constexpr (BKc)
-          xb[i].load(B + offB[i] + k0);
-        else
-          xb[i].load(B + (long long)(k0 + (tid + i * kThreads) / (BN / 4)) * a.ldb + offB[i]);
+    for (int i = 0; i < NA; ++i) {
+      const int q = tid + i * kThreads;
+      int k = AK ? k0 + (q % (BK / 4)) * 4 : k0 + q / (BM / 4);
+      if constexpr (!FULL) k = min(k, kend - (AK ? 4 : 1));
+      xa[i].load(AK ? A + offA[i] + k : A + arow(k) * a.lda + offA[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int q = tid + i * kThreads;
+      int k = BKc ? k0 + (q % (BK / 4)) * 4 : k0 + q / (BN / 4);
+      if constexpr (!FULL) k = min(k, kend - (BKc ? 4 : 1));
+      xb[i].load(BKc ? B + offB[i] + k : B + (long long)k * a.ldb + offB[i]);
+    }
+  };
+  // ragged tiles: shifted quads into place, zeros past the last k
+  const bool edge_m = !FULL && !AK && m0 + BM > M, edge_n = !FULL && !BKc && n0 + BN > N;
+  auto fix = [&](int k0, Q(&xa)[NA], Q(&xb)[NB]) __attribute__((always_inline)) {
+    if constexpr (!FULL) {
+      if (thin) return;
+      if (edge_m) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) xa[i].shift(shA[i]);
+      }
+      if (edge_n) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) xb[i].shift(shB[i]);
+      }
+      if (k0 + BK > kend) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+          const int q = tid + i * kThreads;
+          const int k = AK ? k0 + (q % (BK / 4)) * 4 : k0 + q / (BM / 4);
+          if constexpr (AK) xa[i].shift(max(k - (kend - 4), 0));
+          xa[i].keep(AK ? kend - k : (k < kend ? 4 : 0));
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+          const int q = tid + i * kThreads;
+          const int k = BKc ? k0 + (q % (BK / 4)) * 4 : k0 + q / (BN / 4);
+          if constexpr (BKc) xb[i].shift(max(k - (kend - 4), 0));
+          xb[i].keep(BKc ? kend - k : (k < kend ? 4 : 0));
+        }
       }
     }
   };
@@ -440,8 +491,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t) {
     auto slab = [&](int s) __attribute__((always_inline)) { return kbeg + min(s, nk - 1) * BK; };
 #pragma unroll
     for (int d = 0; d < D; ++d) gload(slab(d), ra[d], rb[d]);
-    colsums(rb[0]);
-    lstore(0, ra[0], rb[0]);
+    auto put = [&](int sl, int buf, Q(&xa)[NA], Q(&xb)[NB]) __attribute__((always_inline)) {
+      fix(slab(sl), xa, xb);
+      colsums(xb);
+      lstore(buf, xa, xb);
+    };
+    put(0, 0, ra[0], rb[0]);
     __syncthreads();
     int it = 0;
     for (; it + D < nk; it += D) {
@@ -450,8 +505,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t) {
         gload(slab(it + d + D), ra[d], rb[d]);
         __builtin_amdgcn_sched_barrier(0);
         compute(d & 1);
-        colsums(rb[(d + 1) % D]);
-        lstore((d + 1) & 1, ra[(d + 1) % D], rb[(d + 1) % D]);
+        put(it + d + 1, (d + 1) & 1, ra[(d + 1) % D], rb[(d + 1) % D]);
         __syncthreads();
       }
     }
@@ -460,10 +514,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t) {
     for (int d = 0; d < D; ++d) {
       if (it + d >= nk) break;
       compute(d & 1);
-      if (it + d + 1 < nk) {
-        colsums(rb[(d + 1) % D]);
-        lstore((d + 1) & 1, ra[(d + 1) % D], rb[(d + 1) % D]);
-      }
+      if (it + d + 1 < nk) put(it + d + 1, (d + 1) & 1, ra[(d + 1) % D], rb[(d + 1) % D]);
       __syncthreads();
     }
   }
@@ -596,7 +647,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t) {
 template <bool BF, bool AT, bool BT, int EPI, bool GATHER, int BM, int BN, int BK, int D,
           bool FULL>
 __global__ __launch_bounds__(kThreads, BM * BN > 128 * 64 ? 1 : 2) void gemm_mm(GemmArgs a) {
-  gemm_tile<BF, AT, BT, EPI, GATHER, BM, BN, BK, D, FULL>(a, decode_tile(a, BM, BN));
+  __shared__ __attribute__((aligned(16))) bf16_t sA[ring_size(BF, !AT, BM, BK)];
+  __shared__ __attribute__((aligned(16))) bf16_t sB[ring_size(BF, BT, BN, BK)];
+  gemm_tile<BF, AT, BT, EPI, GATHER, BM, BN, BK, D, FULL>(a, decode_tile(a, BM, BN), sA, sB,
+                                                          nullptr);
 }
 
 // Weight gradients fused with their momentum-SGD step, of one or several
@@ -634,7 +688,10 @@ __global__ __launch_bounds__(kThreads, BK == 64 ? 3 : 4) void gemm_update(UpdArg
   l -= t.g * per_g;
   t.m0 = (l / tn) * 64;
   t.n0 = (l % tn) * 64;
-  gemm_tile<BF, true, false, EPI_SGD, true, 64, 64, BK, D, FULL, NT>(a, t);
+  __shared__ __attribute__((aligned(16))) bf16_t sA[ring_size(BF, false, 64, BK)];
+  __shared__ __attribute__((aligned(16))) bf16_t sB[ring_size(BF, false, 64, BK)];
+  __shared__ int32_t srmap[kMapRows];
+  gemm_tile<BF, true, false, EPI_SGD, true, 64, 64, BK, D, FULL, NT>(a, t, sA, sB, srmap);
 }
 
 // ------------------------------------------------------------------ split-K
