@@ -107,9 +107,8 @@ def kernel_cost(tag: str, w) -> tuple:
         # batch rows + labels per step, replicas and buffers read and written
         # once, the losses
         return flops, H * K * B * (D * 4 + 4) + 16 * K * P + 4 * H * K
-    if tag == "wgrad_update":   # one launch over every generic layer
-        Lg = L - 1 if d[L] <= 32 else L   # the top layer has its own kernels
-        costs = [kernel_cost(f"wgrad_update{l}", w) for l in range(1, Lg + 1)]
+    if tag == "wgrad_update":   # one launch over every layer
+        costs = [kernel_cost(f"wgrad_update{l}", w) for l in range(1, L + 1)]
         return sum(c[0] for c in costs), sum(c[1] for c in costs)
     if w.model != "mlp" or not tag[-1:].isdigit():
         return None, None        # no per-kernel accounting for this kernel
@@ -245,7 +244,7 @@ def traffic_for(tag: str, w):
 
 
 # Kernels (as rocprofv3 names them, by name prefix) behind a launch tag: the
-# MLP's persistent fused weight-gradient + update kernel, the ResNet's
+# MLP's fused weight-gradient + update kernel, the ResNet's
 # convolution families, and the K-way average, the copy-like kernel used to
 # scale the counters.
 TAG_KERNELS = {

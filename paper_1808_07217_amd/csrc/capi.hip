@@ -315,10 +315,10 @@ struct Profiler {
 struct lsgd_ctx {
   lsgd_config cfg;
   Profiler prof;
-  // side streams for weight updates that do not feed the rest of the step
-  // (default priority), with fork/join events; created at init
-  hipStream_t side[2] = {nullptr, nullptr};
-  hipEvent_t fork[2] = {nullptr, nullptr}, join[2] = {nullptr, nullptr};
+  // ResNet: a side stream (default priority) with fork/join events, created at
+  // init
+  hipStream_t side = nullptr;
+  hipEvent_t fork = nullptr, join = nullptr;
   // ResNet: completion of a step's side-stream work (its weight gradients)
   hipEvent_t done = nullptr;
   bool use_side = false;
@@ -355,9 +355,9 @@ struct lsgd_ctx {
   float* E() const { return ef() ? (float*)(ws + lay.E) : nullptr; }
   bf16_t* Wb() const { return bf16() ? (bf16_t*)(ws + lay.Wb) : nullptr; }
   bf16_t* Xb() const { return (bf16_t*)(ws + lay.Xb); }
-  // Sampled rows of the current step. The MLP step samples the next step's
-  // rows on side stream 0 into the other buffer (idx_next); `presampled` is
-  // the step they belong to (-1: none), and the buffers swap when it starts.
+  // Sampled rows of the current step. The MLP step's update launch samples the
+  // next step's rows into the other buffer (idx_next); `presampled` is the
+  // step they belong to (-1: none), and the buffers swap when it starts.
   int idx_alt = 0;
   int64_t presampled = -1;
   int32_t* idx() const { return (int32_t*)(ws + (idx_alt ? lay.idx2 : lay.idx)); }
@@ -370,14 +370,12 @@ struct lsgd_ctx {
   bool bf16() const { return cfg.gemm_dtype == LSGD_BF16; }
 
   ~lsgd_ctx() {
-    for (int i = 0; i < 2; ++i) {
-      if (side[i]) {
-        (void)hipStreamSynchronize(side[i]);
-        (void)hipStreamDestroy(side[i]);
-      }
-      if (fork[i]) (void)hipEventDestroy(fork[i]);
-      if (join[i]) (void)hipEventDestroy(join[i]);
+    if (side) {
+      (void)hipStreamSynchronize(side);
+      (void)hipStreamDestroy(side);
     }
+    if (fork) (void)hipEventDestroy(fork);
+    if (join) (void)hipEventDestroy(join);
     if (done) (void)hipEventDestroy(done);
   }
 
@@ -493,14 +491,12 @@ lsgd_status do_local_step(lsgd_ctx* c, float lr, float* d_loss) {
   const bf16_t* Wbr = c->pending ? c->Wbarb() : Wb;
   const long long sWr = c->pending ? 0 : ly.Ps;
 
-  // this step's rows: sampled by the step before on the side stream, or now
-  if (c->presampled == c->step && c->lay.idx2 != 0)
+  // this step's rows: sampled with the step before's update, or now
+  if (c->presampled == c->step)
     c->idx_alt ^= 1;
   else
     LSGD_LAUNCH(c, "sample", sample(c, c->step, c->idx(), s));
   c->presampled = -1;
-  bool presample = false;
-  bool side0 = false;  // work forked onto side stream 0
 
   // forward: Z_l = A_{l-1} W_l + b_l, A_l = relu(Z_l) below the top layer
   const int Lg = ly.head ? L - 1 : L;  // layers through the generic GEMMs
@@ -576,33 +572,23 @@ lsgd_status do_local_step(lsgd_ctx* c, float lr, float* d_loss) {
     h.nesterov = upd_mode(cf);
     // logits, loss, dZ_L and the masked input gradient of the top layer
     LSGD_LAUNCH(c, "head_fwd", lsgd::launch_head_fwd(dt, h, s));
-    // the top layer's weight gradient feeds nothing else in this step: it
-    // runs on side stream 0 while the backward pass continues
-    if (c->use_side) {
-      LSGD_CK(c, hipEventRecord(c->fork[0], s));
-      LSGD_CK(c, hipStreamWaitEvent(c->side[0], c->fork[0], 0));
-      LSGD_LAUNCH_ON(c, c->side[0], "head_wgrad",
-                     lsgd::launch_head_wgrad(dt, h, c->side[0]));
-      // the next step's rows, off the critical path, into the buffer this
-      // step does not read (its previous rows' readers, the step before,
-      // precede head_fwd, after which this stream runs)
-      if (c->lay.idx2 != 0) {
-        LSGD_LAUNCH_ON(c, c->side[0], "sample",
-                       sample(c, c->step + 1, c->idx_next(), c->side[0]));
-        presample = true;
-      }
-      LSGD_CK(c, hipEventRecord(c->join[0], c->side[0]));
-      side0 = true;
-    } else {
-      LSGD_LAUNCH(c, "head_wgrad", lsgd::launch_head_wgrad(dt, h, s));
-    }
   } else {
     LSGD_LAUNCH(c, "xent", lsgd::launch_xent(c->Z(), c->y, c->idx(), K, B, w[L],
                                                c->dZ(L), dt, d_loss, c->flag(), s));
   }
 
+  // softmax regression: its one layer through the head's own update (3072 x 10
+  // weights of 16 replicas: 12 us, as 64 x 64 tiles of the launch below 17)
+  if (ly.head && L == 1) {
+    LSGD_LAUNCH(c, "head_wgrad", lsgd::launch_head_wgrad(dt, h, s));
+    c->step += 1;
+    c->pending = false;
+    return LSGD_OK;
+  }
+
   // backward, top layer first: the input gradients (they read the pre-update
-  // weights), then one launch that updates every layer below the head
+  // weights), then one launch that updates every layer, forms the losses and
+  // draws the next step's rows
   for (int l = Lg; l >= 2; --l) {
     const int din = w[l - 1], dout = w[l];
     GemmArgs a{};
@@ -625,18 +611,25 @@ lsgd_status do_local_step(lsgd_ctx* c, float lr, float* d_loss) {
     LSGD_LAUNCH(c, "dgrad" + std::to_string(l),
                 lsgd::launch_gemm(dt, 0, 1, lsgd::EPI_RELU_MASK, dt, a, s));
   }
-  if (Lg >= 1) {
-    GemmArgs upd[lsgd::kUpdMaxProblems];
-    static_assert(LSGD_MAX_LAYERS <= lsgd::kUpdMaxProblems, "every layer in one launch");
-    for (int l = 1; l <= Lg; ++l) upd[l - 1] = wgrad_args(c, l, lr);
-    LSGD_LAUNCH(c, "wgrad_update", lsgd::launch_gemm_update(dt, upd, Lg, s));
+  GemmArgs upd[lsgd::kUpdMaxProblems];
+  static_assert(LSGD_MAX_LAYERS <= lsgd::kUpdMaxProblems, "every layer in one launch");
+  for (int l = 1; l <= L; ++l) upd[l - 1] = wgrad_args(c, l, lr);
+  lsgd::StepTail tail{};
+  tail.K = K;
+  tail.B = B;
+  if (ly.head) {
+    tail.rowloss = c->rowloss();
+    tail.loss = d_loss;
+    tail.nonfinite = c->flag();
   }
-  // join: the step ends when all of its updates have; without side-stream
-  // work there is nothing to wait for (a wait costs the stream some µs)
-  if (side0) LSGD_CK(c, hipStreamWaitEvent(s, c->join[0], 0));
+  // the next step's rows into the buffer this step does not read (its previous
+  // rows' readers, the step before, precede this launch on the stream)
+  lsgd::step_tail_sample(tail, cf.sampler == LSGD_SAMPLER_EPOCH, cf.seed, c->step + 1, cf.N,
+                         c->idx_next());
+  LSGD_LAUNCH(c, "wgrad_update", lsgd::launch_gemm_update(dt, upd, L, tail, s));
   c->step += 1;
   c->pending = false;  // every replica now holds its own stepped model
-  if (presample) c->presampled = c->step;
+  c->presampled = c->step;
   return LSGD_OK;
 }
 
@@ -813,18 +806,18 @@ lsgd_status do_local_step_resnet(lsgd_ctx* c, float lr, float* d_loss) {
   // first measured no different).
   if (c->use_side && K % 2 == 0) {
     const int Kh = K / 2;
-    hipStream_t s2 = c->side[1];
+    hipStream_t s2 = c->side;
     double* part2 = (double*)(c->ws + r.bnpart2);
-    LSGD_CK(c, hipEventRecord(c->fork[1], s));
-    LSGD_CK(c, hipStreamWaitEvent(s2, c->fork[1], 0));
+    LSGD_CK(c, hipEventRecord(c->fork, s));
+    LSGD_CK(c, hipStreamWaitEvent(s2, c->fork, 0));
     for (int i = 0; i < kResConvs; ++i) {
       if (lsgd_status st = fwd_layer(i, 0, Kh, s, bnpart)) return st;
       if (lsgd_status st = fwd_layer(i, Kh, Kh, s2, part2)) return st;
     }
     if (lsgd_status st = fwd_head(0, Kh, s)) return st;
     if (lsgd_status st = fwd_head(Kh, Kh, s2)) return st;
-    LSGD_CK(c, hipEventRecord(c->join[1], s2));
-    LSGD_CK(c, hipStreamWaitEvent(s, c->join[1], 0));
+    LSGD_CK(c, hipEventRecord(c->join, s2));
+    LSGD_CK(c, hipStreamWaitEvent(s, c->join, 0));
   } else {
     for (int i = 0; i < kResConvs; ++i)
       if (lsgd_status st = fwd_layer(i, 0, K, s, bnpart)) return st;
@@ -891,7 +884,7 @@ lsgd_status do_local_step_resnet(lsgd_ctx* c, float lr, float* d_loss) {
   // stem's weight gradient, on the main stream, has its own). Without side
   // streams everything runs in order on the main stream.
   const bool sidew = c->use_side;
-  hipStream_t ws = sidew ? c->side[1] : s;
+  hipStream_t ws = sidew ? c->side : s;
   bool pend = false;
   auto join_side = [&]() -> lsgd_status {  // the main stream waits for event done
     if (pend) LSGD_CK(c, hipStreamWaitEvent(s, c->done, 0));
@@ -905,8 +898,8 @@ lsgd_status do_local_step_resnet(lsgd_ctx* c, float lr, float* d_loss) {
   auto fork = [&](int ib, int ia, bool last, const float* g1, const float* g2,
                   const float* h_in) -> lsgd_status {
     if (sidew) {
-      LSGD_CK(c, hipEventRecord(c->fork[1], s));
-      LSGD_CK(c, hipStreamWaitEvent(ws, c->fork[1], 0));
+      LSGD_CK(c, hipEventRecord(c->fork, s));
+      LSGD_CK(c, hipStreamWaitEvent(ws, c->fork, 0));
     }
     if (lsgd_status st = wgrad(ib, F(r.cv[ia].y), g1, ia, ws, wpart)) return st;
     if (lsgd_status st = wgrad(ia, h_in, g2, -1, ws, wpart)) return st;
@@ -1239,17 +1232,13 @@ lsgd_status lsgd_init_replicas(const lsgd_config* cfg, const float* d_X,
       check(lsgd::launch_copy_rows(c->RS() + r.Rs, r.Rs, c->RS(), 0, r.Rs, K - 1,
                                    c->stream), "running statistics to every replica");
   }
-  // side streams pay off once there is a hidden layer (an update that can
-  // overlap the rest of the backward pass), and for ResNet-20 (its weight
-  // gradients overlap the BN backward passes)
-  const bool resnet = c->cfg.model == LSGD_MODEL_RESNET20;
-  if (st == LSGD_OK && ((ly.head && ly.L >= 2) || resnet)) {
-    for (int i = 0; i < 2; ++i) {
-      check(hipStreamCreateWithFlags(&c->side[i], hipStreamNonBlocking), "side stream");
-      check(hipEventCreateWithFlags(&c->fork[i], hipEventDisableTiming), "fork event");
-      check(hipEventCreateWithFlags(&c->join[i], hipEventDisableTiming), "join event");
-    }
-    if (resnet) check(hipEventCreateWithFlags(&c->done, hipEventDisableTiming), "done event");
+  // ResNet-20's two forward halves, and its weight gradients beside the BN
+  // backward passes, run on a side stream
+  if (st == LSGD_OK && c->cfg.model == LSGD_MODEL_RESNET20) {
+    check(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking), "side stream");
+    check(hipEventCreateWithFlags(&c->fork, hipEventDisableTiming), "fork event");
+    check(hipEventCreateWithFlags(&c->join, hipEventDisableTiming), "join event");
+    check(hipEventCreateWithFlags(&c->done, hipEventDisableTiming), "done event");
     c->use_side = st == LSGD_OK;
   }
   if (st != LSGD_OK) {

@@ -60,6 +60,21 @@ inline __device__ int32_t epoch_row(uint32_t q, long long N, int m, uint32_t k0,
   return (int32_t)(y < (uint64_t)N ? y : q);
 }
 
+// Slots 4 q .. 4 q + 3 (below B) of worker k's i.i.d. draws at a local step:
+// a Philox block's four words, scaled to the worker's slice.
+inline __device__ void sample_iid4(uint32_t key0, uint32_t key1, uint32_t s_lo, uint32_t s_hi,
+                                   int k, int K, long long N, int B, int q, int32_t* idx) {
+  const long long lo = (long long)k * N / K;
+  const uint64_t n = (uint64_t)((long long)(k + 1) * N / K - lo);
+  const uint4 r = philox4x32_10(make_uint4((uint32_t)q, s_lo, (uint32_t)k, s_hi), key0, key1);
+  const uint32_t w[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int j = 4 * q + e;
+    if (j < B) idx[(long long)k * B + j] = (int32_t)(lo + (long long)(((uint64_t)w[e] * n) >> 32));
+  }
+}
+
 // Sum of p[0], p[stride], ..., p[(K-1) stride] in the replica-average order:
 // split at the largest power of two below the count, left part first
 // (a binary counter of power-of-two partial sums).

@@ -13,19 +13,7 @@ __global__ void k_sample(uint32_t key0, uint32_t key1, uint32_t s_lo,
                          uint32_t s_hi, int K, long long N, int B,
                          int32_t* idx) {
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  const int k = blockIdx.y;
-  if (4 * q >= B) return;
-  const long long lo = (long long)k * N / K;
-  const long long hi = (long long)(k + 1) * N / K;
-  const uint64_t n = (uint64_t)(hi - lo);
-  const uint4 r = philox4x32_10(make_uint4((uint32_t)q, s_lo, (uint32_t)k, s_hi),
-                                key0, key1);
-  const uint32_t w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int j = 4 * q + e;
-    if (j < B) idx[(long long)k * B + j] = (int32_t)(lo + (long long)(((uint64_t)w[e] * n) >> 32));
-  }
+  if (4 * q < B) sample_iid4(key0, key1, s_lo, s_hi, blockIdx.y, K, N, B, q, idx);
 }
 
 // One thread per (worker k = blockIdx.y, slot b): row pi_e(lo_k + jB + b).

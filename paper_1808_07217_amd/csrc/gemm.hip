@@ -31,6 +31,7 @@
 // the S partials in ascending s and applies the epilogue.
 #include <type_traits>
 
+#include "device_common.h"
 #include "kernels.h"
 
 namespace lsgd {
@@ -671,11 +672,63 @@ struct UpdArgs {
   GemmArgs p[kUpdMaxProblems];
   int start[kUpdMaxProblems + 1];  // first tile of each problem; [np] = total
   int np;
+  unsigned whole;  // bit i: problem i has whole tiles and slabs only
+  StepTail tail;
+  int nloss, ntail;  // workgroups of the losses; of the tail (a multiple of 8)
 };
 
-template <bool BF, int BK, int D, bool FULL, bool NT>
-__global__ __launch_bounds__(kThreads, BK == 64 ? 3 : 4) void gemm_update(UpdArgs w) {
-  const int total = w.start[w.np], p = blockIdx.x;
+// The tail's workgroup p: a replica's loss, or 256 threads of the sampler. They
+// come first in the grid, so they end long before the tiles do. (As launches of
+// their own on a side stream, behind an event each way, they cost the step
+// about 16 us.)
+__device__ __forceinline__ void step_tail(const UpdArgs& w, int p, float* red) {
+  const StepTail& t = w.tail;
+  const int tid = threadIdx.x;
+  if (p < w.nloss) {
+    float part = 0.f;  // strided partial sums, then a fixed tree
+    for (int b = tid; b < t.B; b += kThreads) part += t.rowloss[(long long)p * t.B + b];
+    red[tid] = part;
+    __syncthreads();
+    for (int n = kThreads / 2; n > 0; n >>= 1) {
+      if (tid < n) red[tid] += red[tid + n];
+      __syncthreads();
+    }
+    if (tid == 0) {
+      const float mean = red[0] / (float)t.B;
+      if (t.loss) t.loss[p] = mean;
+      // a plain store: every writer stores the same value
+      if (t.nonfinite && !isfinite(mean)) *t.nonfinite = 1;
+    }
+    return;
+  }
+  if (!t.idx) return;
+  const long long i = (long long)(p - w.nloss) * kThreads + tid;
+  if (t.epoch) {
+    if (i >= (long long)t.K * t.B) return;
+    const int k = (int)(i / t.B), b = (int)(i - (long long)k * t.B);
+    const uint32_t q = (uint32_t)((long long)k * t.N / t.K + t.j * t.B + b);
+    t.idx[i] = epoch_row(q, t.N, t.m, t.key0, t.key1, t.e);
+  } else {
+    const int quads = (t.B + 3) / 4;
+    if (i >= (long long)t.K * quads) return;
+    const int k = (int)(i / quads);
+    sample_iid4(t.key0, t.key1, t.s_lo, t.s_hi, k, t.K, t.N, t.B, (int)(i - (long long)k * quads),
+                t.idx);
+  }
+}
+
+// (bf16: whole tiles in slabs of 64, 94 against 95 us for 16 x 3072 x 512)
+template <bool BF, bool NT>
+__global__ __launch_bounds__(kThreads, BF ? 3 : 4) void gemm_update(UpdArgs w) {
+  constexpr int BK = BF ? 64 : 16;
+  __shared__ __attribute__((aligned(16))) bf16_t sA[ring_size(BF, false, 64, BK)];
+  __shared__ __attribute__((aligned(16))) bf16_t sB[ring_size(BF, false, 64, BK)];
+  __shared__ int32_t srmap[kMapRows];
+  if ((int)blockIdx.x < w.ntail) {
+    step_tail(w, blockIdx.x, (float*)sA);
+    return;
+  }
+  const int total = w.start[w.np], p = blockIdx.x - w.ntail;
   int l = (total % kXcds == 0) ? (p % kXcds) * (total / kXcds) + p / kXcds : p;
   int pi = 0;
   while (pi + 1 < w.np && l >= w.start[pi + 1]) ++pi;
@@ -688,10 +741,11 @@ __global__ __launch_bounds__(kThreads, BK == 64 ? 3 : 4) void gemm_update(UpdArg
   l -= t.g * per_g;
   t.m0 = (l / tn) * 64;
   t.n0 = (l % tn) * 64;
-  __shared__ __attribute__((aligned(16))) bf16_t sA[ring_size(BF, false, 64, BK)];
-  __shared__ __attribute__((aligned(16))) bf16_t sB[ring_size(BF, false, 64, BK)];
-  __shared__ int32_t srmap[kMapRows];
-  gemm_tile<BF, true, false, EPI_SGD, true, 64, 64, BK, D, FULL, NT>(a, t, sA, sB, srmap);
+  if (w.whole >> pi & 1u)  // uniform
+    gemm_tile<BF, true, false, EPI_SGD, true, 64, 64, BK, BF ? 2 : 4, true, NT>(a, t, sA, sB, srmap);
+  else
+    gemm_tile<BF, true, false, EPI_SGD, true, 64, 64, BF ? 32 : 16, 2, false, NT>(a, t, sA, sB,
+                                                                                  srmap);
 }
 
 // ------------------------------------------------------------------ split-K
@@ -805,11 +859,34 @@ hipError_t dispatch(int dtype, const GemmArgs& a, hipStream_t s) {
 // State from which the update streams past the caches.
 constexpr long long kNtBytes = 240LL << 20;
 
-hipError_t launch_gemm_update(int dtype, const GemmArgs* list, int n, hipStream_t s) {
+void step_tail_sample(StepTail& t, int epoch, uint64_t seed, int64_t step, int64_t N,
+                      int32_t* idx) {
+  t.idx = idx;
+  t.epoch = epoch;
+  t.key0 = (uint32_t)seed;
+  t.key1 = (uint32_t)(seed >> 32);
+  t.s_lo = (uint32_t)step;
+  t.s_hi = (uint32_t)((uint64_t)step >> 32);
+  t.N = N;
+  if (epoch) {
+    const long long S = (N / t.K) / t.B;  // batches per worker and epoch, >= 1
+    t.e = (uint32_t)(step / S);
+    t.j = step % S;
+    t.m = 1;
+    while ((1LL << (2 * t.m)) < N) ++t.m;
+  }
+}
+
+hipError_t launch_gemm_update(int dtype, const GemmArgs* list, int n, const StepTail& tail,
+                              hipStream_t s) {
   if (n < 1 || n > kUpdMaxProblems) return hipErrorInvalidValue;
   UpdArgs w{};
   w.np = n;
-  bool whole = true;
+  w.tail = tail;
+  w.nloss = tail.rowloss ? tail.K : 0;
+  const long long slots = !tail.idx ? 0 : (long long)tail.K * (tail.epoch ? tail.B : (tail.B + 3) / 4);
+  const long long extra = w.nloss + (slots + kThreads - 1) / kThreads;
+  w.ntail = (int)((extra + kXcds - 1) / kXcds * kXcds);
   long long total = 0, state = 0;  // tiles; bytes of W, U and the bf16 copy
   for (int i = 0; i < n; ++i) {
     GemmArgs& a = w.p[i];
@@ -817,32 +894,24 @@ hipError_t launch_gemm_update(int dtype, const GemmArgs* list, int n, hipStream_
     if (a.G <= 0 || a.M <= 0 || a.N <= 0 || a.Kd <= 0) return hipErrorInvalidValue;
     a.splits = 1;
     a.kchunk = (a.Kd + 31) / 32 * 32;
-    whole = whole && full(a, 64, 64, 32);
+    if (full(a, 64, 64, dtype == 1 ? 64 : 16)) w.whole |= 1u << i;
     state += (long long)a.G * a.M * a.N * (a.Wb ? 10 : 8);
     w.start[i] = (int)total;
     total += (long long)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.G;
     if (total > 0x7fffffffLL) return hipErrorInvalidValue;
   }
   w.start[n] = (int)total;
-  // bf16 takes whole tiles in slabs of 64 (16 x 3072 x 512: 94 against 95 us)
-  for (int i = 0; dtype == 1 && i < n; ++i) whole = whole && w.p[i].Kd % 64 == 0;
   const bool nt = state >= kNtBytes;
-  const dim3 grid((unsigned)total), block(kThreads);
-#define LSGD_UPD(BF, BK, D, FULL)                                                        \
-  if (nt)                                                                                \
-    hipLaunchKernelGGL((gemm_update<BF, BK, D, FULL, true>), grid, block, 0, s, w);      \
-  else                                                                                   \
-    hipLaunchKernelGGL((gemm_update<BF, BK, D, FULL, false>), grid, block, 0, s, w)
-  if (dtype == 1 && whole) {
-    LSGD_UPD(true, 64, 2, true);
-  } else if (dtype == 1) {
-    LSGD_UPD(true, 32, 2, false);
-  } else if (whole) {
-    LSGD_UPD(false, 16, 4, true);
-  } else {
-    LSGD_UPD(false, 16, 2, false);
-  }
-#undef LSGD_UPD
+  if (total + w.ntail > 0x7fffffffLL) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(total + w.ntail)), block(kThreads);
+  if (dtype == 1 && nt)
+    hipLaunchKernelGGL((gemm_update<true, true>), grid, block, 0, s, w);
+  else if (dtype == 1)
+    hipLaunchKernelGGL((gemm_update<true, false>), grid, block, 0, s, w);
+  else if (nt)
+    hipLaunchKernelGGL((gemm_update<false, true>), grid, block, 0, s, w);
+  else
+    hipLaunchKernelGGL((gemm_update<false, false>), grid, block, 0, s, w);
   return hipGetLastError();
 }
 

@@ -89,11 +89,32 @@ int gemm_splits(int dtype, int M, int N, int Kd, int G, int epi);
 hipError_t launch_gemm(int dtype, int trans_a, int trans_b, int epi,
                        int out_bf16, const GemmArgs& a, hipStream_t s);
 
+// The end of a local step that rides on the update launch, in workgroups of its
+// own: the mean loss of each replica from its per-row losses, and the next
+// step's index sets.
+struct StepTail {
+  int K, B;                // replicas, batch
+  const float* rowloss;    // [K][B] (the loss is formed here), or nullptr
+  float* loss;             // [K] or nullptr
+  int* nonfinite;          // set to 1 on a non-finite mean loss, or nullptr
+  int32_t* idx;            // next step's rows [K][B], or nullptr
+  int epoch;               // 0: i.i.d. draws; 1: the reshuffle sampler
+  uint32_t key0, key1;
+  uint32_t s_lo, s_hi;     // i.i.d.: the step
+  uint32_t e;              // reshuffle: epoch, batch of the epoch, word size
+  long long j;
+  int m;
+  long long N;
+};
 // Fused weight gradient + update (trans_a = 1, trans_b = 0, EPI_SGD; a null
 // row map: A's rows in order) of up to kUpdMaxProblems layers in one launch,
-// their tiles concatenated.
+// their tiles concatenated, and the step's tail.
 constexpr int kUpdMaxProblems = 8;
-hipError_t launch_gemm_update(int dtype, const GemmArgs* list, int n, hipStream_t s);
+hipError_t launch_gemm_update(int dtype, const GemmArgs* list, int n, const StepTail& tail,
+                              hipStream_t s);
+// The sampler fields of a tail: the index sets of local step `step` into idx.
+void step_tail_sample(StepTail& t, int epoch, uint64_t seed, int64_t step, int64_t N,
+                      int32_t* idx);
 
 // ---------------------------------------------------------------- head
 // Output layer with few classes, fused around the loss (head.hip).
