@@ -117,6 +117,40 @@ def test_grouped_gemm_two_k_halves(shape, splits, tb):
     assert np.all(np.abs(C - ref) <= bound), np.max(np.abs(C - ref) / bound)
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("shape,splits", [((2, 3, 2, 3), 1), ((2, 4, 5, 4), 1),      # quads and less
+                                          ((2, 63, 65, 31), 1), ((1, 65, 66, 33), 1),  # 64 x 64 + 1
+                                          ((1, 129, 127, 2049), 2),                    # deep, split
+                                          ((1, 129, 127, 130), 8)])                    # empty splits
+def test_grouped_gemm_ragged_edges(dtype, ta, tb, shape, splits):
+    """Every remainder of a tile, a slab and a quad, and infinities among the
+    operands: the same positions infinite or NaN as in fp64, the others within
+    the fp32 bound."""
+    L = _lsgd()
+    G, M, N, Kd = shape
+    print(f"gemm edges {dtype} ta={ta} tb={tb} {shape} splits={splits}", flush=True)
+    rng = np.random.default_rng(M + 5 * N + 7 * Kd + ta * 2 + tb)
+    A = rng.standard_normal((G, Kd, M) if ta else (G, M, Kd)).astype(np.float32)
+    B = rng.standard_normal((G, N, Kd) if tb else (G, Kd, N)).astype(np.float32)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    for special in (False, True):
+        if special:
+            A[0, -1, -1], A[0, 0, 0], B[0, -1, 0] = np.inf, -np.inf, np.inf
+        Ad, Bd = to_dev(A).to(tdt), to_dev(B).to(tdt)
+        C = L.grouped_gemm(Ad, Bd, bool(ta), bool(tb), splits=splits).cpu().numpy().astype(np.float64)
+        A64 = Ad.to(torch.float64).cpu().numpy()
+        B64 = Bd.to(torch.float64).cpu().numpy()
+        opA = A64.transpose(0, 2, 1) if ta else A64
+        opB = B64.transpose(0, 2, 1) if tb else B64
+        with np.errstate(invalid="ignore"):
+            ref = opA @ opB
+            bound = gamma(Kd + 1) * (np.abs(opA) @ np.abs(opB)) + 1e-30
+        fin = np.isfinite(ref)
+        np.testing.assert_array_equal(C[~fin], ref[~fin])
+        assert np.all(np.abs(C - ref)[fin] <= bound[fin])
+
+
 # ------------------------------------------------------------------ average
 def _tree_f32(rows):
     """The kernel's documented order in fp32: split at the largest power of
@@ -149,6 +183,20 @@ def test_replica_average(K, P):
     depth = int(np.ceil(np.log2(K))) if K > 1 else 0
     bound = gamma(depth) * np.abs(W).astype(np.float64).sum(0) / K + U32 * np.abs(ref)
     assert np.all(np.abs(got[0] - ref) <= bound + 1e-45)
+
+
+@pytest.mark.parametrize("K,P", [(6, 4099), (10, 1026), (12, 1025), (24, 1027),
+                                 (5, (13 << 20) + 3)])  # 273 MB: streamed past the caches
+def test_replica_average_rows_at_any_alignment(K, P):
+    L = _lsgd()
+    print(f"average K={K} P={P}", flush=True)
+    W = np.random.default_rng(K + P).standard_normal((K, P), dtype=np.float32)
+    Wd = to_dev(W)
+    L.replica_average(Wd)
+    got = Wd.cpu().numpy()
+    want = (_tree_f32([W[k] for k in range(K)]) / np.float32(K)).astype(np.float32)
+    for k in range(K):
+        np.testing.assert_array_equal(got[k], want)
 
 
 @pytest.mark.parametrize("K", [1, 2, 4, 16, 64])

@@ -114,6 +114,29 @@ def test_small_mlp_every_step(widths, nesterov, momentum):
     _compare_steps(w, X, y, w0, PARAM_TOL_FP32, 1e-4)
 
 
+@pytest.mark.parametrize("widths,K,B,dtype", [
+    ((1025, 12), 3, 129, "fp32"),         # the head alone, gathered rows, a second pass of one row
+    ((300, 17), 2, 7, "bf16"),
+    ((31, 65, 32), 2, 127, "fp32"),       # 32 classes over 65 inputs, tiles of 64 + 1
+    ((5, 3, 2), 2, 3, "fp32"),            # layers below a quad
+    ((33, 130, 67, 11), 2, 33, "bf16"),   # bf16 rows at odd alignment, a batch of a slab + 1
+    ((1000, 1040, 10), 32, 8, "fp32"),    # 268 MB of state: the update streamed past the caches
+])
+def test_update_and_head_at_tile_edges(widths, K, B, dtype):
+    """Every layer's update, the losses and the next step's rows in one launch,
+    and the head's kernels, at the edges of their tiles, quads and class
+    counts; every replica after every step."""
+    big = K > 3
+    w = _small(widths, dtype=dtype, nesterov=True, K=K, B=B, lr=0.01, H=1 if big else 3,
+               rounds=1 if big else 2)
+    print(f"edges {widths} K={K} B={B} {dtype}", flush=True)
+    X, y, w0 = _small_data(w)
+    if dtype == "bf16":
+        _compare_steps(w, X, y, w0, 2e-3, LOSS_TOL_BF16, nr_ratio=NR_RATIO)
+    else:
+        _compare_steps(w, X, y, w0, PARAM_TOL_FP32, 1e-4)
+
+
 def test_batch_larger_than_the_gathered_row_cache():
     """A local batch of 600 rows (the weight-gradient kernel caches 512
     gathered row indices in LDS and reads the rest from memory)."""
