@@ -869,7 +869,7 @@ lsgd_status do_local_step_resnet(lsgd_ctx* c, float lr, float* d_loss) {
                                              upd_mode(cf), ws));
     return LSGD_OK;
   };
-  // The weight gradients (and updates) of a block run on side stream 1: they
+  // The weight gradients (and updates) of a block run on the side stream: they
   // fork after the block's last input gradient (the last reader of its
   // weights) and overlap the next block's BN backward passes and input
   // gradients on the main stream (memory-bound passes beside the weight
