@@ -9,18 +9,28 @@
 //
 // Every product runs on v_mfma_f32_32x32x16_bf16. bf16 operands feed it as
 // they are. An fp32 operand x is taken as three bf16 pieces, x = x1 + x2 + x3
-// (each the round-to-nearest bf16 of what the ones before leave, so the sum is
-// exact: 3 x 8 significant bits), and x y as the six products x1 y1, x1 y2,
-// x2 y1, x2 y2, x1 y3, x3 y1, each exact in fp32; the three left out are below
-// 2^-26 |x y| together. x1 y1 has an accumulator of its own and the five small
+// (each the round-to-nearest bf16 of what the ones before leave: 3 x 8
+// significant bits), and x y as the six products x1 y1, x1 y2, x2 y1, x2 y2,
+// x1 y3, x3 y1, each exact in fp32. The three left out reach 2^-24 |x y| at
+// worst (|x2| <= 2^-8 |x|, |x3| <= 2^-17 |x|); their rms over normal operands is
+// 2^-27.4 |x y|. x1 y1 has an accumulator of its own and the five small
 // ones share another, added at the end: a k range of 16 then rounds once at the
 // sum's own magnitude where v_mfma_f32_32x32x2f32 rounds 16 times. Measured
-// against fp64 (normwise, normal operands, K = 64 / 512 / 3072): 5.0e-8 /
-// 1.3e-7 / 3.4e-7, the fp32 instruction 1.4e-7 / 4.0e-7 / 1.0e-6; the six
-// products issue at 290 TFLOP/s, the fp32 instruction at 122.
-// Infinities: x1 of an infinity (or of a finite value that rounds to one)
-// leaves NaN pieces, so a wave whose result holds any NaN forms its tile again
-// with the fp32 instruction and keeps that.
+// against fp64 (normwise, normal operands, K = 3 / 64 / 512 / 3072): 2.7e-8 /
+// 5.0e-8 / 1.3e-7 / 3.4e-7, kernels on the fp32 instruction 3.6e-8 / 1.1e-7 /
+// 2.9e-7 / 7.0e-7.
+// An inner range of one or two, where the products left out would show (largest
+// error over |x y| 9.4e-8 against 6.0e-8 at K = 1), takes the fp32 instruction.
+// So does a wave whose result holds an infinity or a NaN: x1 of an infinity, or
+// of a finite value that rounds to one, leaves NaN pieces, and x1 y1 may
+// overflow where x y does not.
+// The pieces of a value below 2^-110 fall under bf16's smallest subnormal, an
+// error of up to 2^-134 |y| of its product. The plain product (EPI_STORE), whose
+// operands may be anything, splits 2^24 x and 2^24 y instead, exact down to the
+// smallest subnormal, and takes 2^-48 of the sum. The products of a local step
+// do not: a step of normal size does not see 1e-40 of an activation or a
+// weight, and the multiplications cost it 2 to 4% (the 512-wide MLP's round of
+// 16 steps 3.24 -> 3.35 ms, 784-300-100-10 at a batch of 50 55 -> 57 us a step).
 //
 // Work distribution: a 1-D grid of G * S * tilesM * tilesN workgroups. The
 // hardware deals consecutive workgroup ids round-robin to the 8 XCDs (each
@@ -113,8 +123,15 @@ __device__ __forceinline__ void bias_update(const GemmArgs& a, int g, int n, flo
 }
 
 // ------------------------------------------------------------ operand pieces
-// Two fp32 values as packed bf16 pairs p[0] + p[1] + p[2] (see the top).
+// Two fp32 values (SCALED: times kSplitScale) as packed bf16 pairs
+// p[0] + p[1] + p[2] (see the top).
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
+template <bool SCALED>
 __device__ __forceinline__ void split3(float x, float y, uint32_t (&p)[3]) {
+  if constexpr (SCALED) {
+    x *= kSplitScale;
+    y *= kSplitScale;
+  }
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     p[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{x, y}, bf16x2));
@@ -144,10 +161,11 @@ struct Quad<false> {
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = e < n ? v[e] : 0.f;
   }
+  template <bool SCALED>
   __device__ __forceinline__ void planes(u32x2 (&q)[3]) const {
     uint32_t a[3], b[3];
-    split3(v[0], v[1], a);
-    split3(v[2], v[3], b);
+    split3<SCALED>(v[0], v[1], a);
+    split3<SCALED>(v[2], v[3], b);
 #pragma unroll
     for (int i = 0; i < 3; ++i) q[i] = u32x2{a[i], b[i]};
   }
@@ -177,6 +195,7 @@ struct Quad<true> {
     v.x = n > 1 ? v.x : n > 0 ? v.x & 0xffffu : 0u;
     v.y = n > 3 ? v.y : n > 2 ? v.y & 0xffffu : 0u;
   }
+  template <bool SCALED>
   __device__ __forceinline__ void planes(u32x2 (&q)[1]) const { q[0] = v; }
   __device__ __forceinline__ v4f f32() const {
     return v4f{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
@@ -225,6 +244,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t, bf16_
   // the k rows of A come from a row map (an update's may have none: its rows
   // in order), the first kMapRows of it in LDS
   constexpr bool kRows = AT && GATHER;
+  constexpr bool kScaled = EPI == EPI_STORE;
 
   const int g = t.g, m0 = t.m0, n0 = t.n0;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -406,7 +426,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t, bf16_
       const int o = AK ? (q / (BK / 4)) * PA + (q % (BK / 4)) * 4
                        : (q / (BM / 4)) * PA + (q % (BM / 4)) * 4;
       u32x2 p[NPL];
-      xa[i].planes(p);
+      xa[i].template planes<kScaled>(p);
 #pragma unroll
       for (int l = 0; l < NPL; ++l) *(u32x2*)&sA[(buf * NPL + l) * SA + o] = p[l];
     }
@@ -416,7 +436,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t, bf16_
       const int o = BKc ? (q / (BK / 4)) * PB + (q % (BK / 4)) * 4
                         : (q / (BN / 4)) * PB + (q % (BN / 4)) * 4;
       u32x2 p[NPL];
-      xb[i].planes(p);
+      xb[i].template planes<kScaled>(p);
 #pragma unroll
       for (int l = 0; l < NPL; ++l) *(u32x2*)&sB[(buf * NPL + l) * SB + o] = p[l];
     }
@@ -520,7 +540,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t, bf16_
     }
   }
   if constexpr (!BF) {
-    bool bad = false;
+    float sum = 0.f;  // an infinity or a NaN among the results shows in it
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -528,11 +548,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t, bf16_
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           hi[i][j][v] += lo[i][j][v];
-          bad |= hi[i][j][v] != hi[i][j][v];
+          sum += hi[i][j][v];
+          if constexpr (kScaled) hi[i][j][v] *= kSplitUnscale;
         }
-    if (__builtin_expect(__any(bad), 0)) {
-      // infinities (or NaN) among the operands: the fp32 instruction, from
-      // memory
+    if (__builtin_expect(__any(!__builtin_isfinite(sum)) || kend - kbeg <= 2, 0)) {
+      // the fp32 instruction, from memory
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll

@@ -148,7 +148,51 @@ def test_grouped_gemm_ragged_edges(dtype, ta, tb, shape, splits):
             bound = gamma(Kd + 1) * (np.abs(opA) @ np.abs(opB)) + 1e-30
         fin = np.isfinite(ref)
         np.testing.assert_array_equal(C[~fin], ref[~fin])
-        assert np.all(np.abs(C - ref)[fin] <= bound[fin])
+        assert np.all(np.abs(C[fin] - ref[fin]) <= bound[fin])
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("shape", [(2, 70, 65, 37), (1, 64, 64, 64), (2, 65, 3, 1), (2, 33, 70, 2),
+                                   (1, 128, 256, 3)])
+def test_grouped_gemm_over_the_range_of_fp32(shape, ta, tb):
+    """Products of fp32 values from subnormal ones to the largest: the fp32 bound
+    (and, where a result is subnormal, its spacing per addition) at every scale;
+    an inner dimension of one gives the correctly rounded product."""
+    L = _lsgd()
+    G, M, N, Kd = shape
+    rng = np.random.default_rng(M + 3 * N + 5 * Kd + 2 * ta + tb)
+    A0 = rng.standard_normal((G, M, Kd)).astype(np.float32)
+    B0 = rng.standard_normal((G, Kd, N)).astype(np.float32)
+    # scales of A and B as powers of two; the last two leave products near 2^125
+    for ea, eb in ((-112, 0), (0, -120), (-133, 0), (-128, 30), (-60, -60), (122, 0), (70, 50)):
+        print(f"gemm range {shape} ta={ta} tb={tb} 2^{ea} 2^{eb}", flush=True)
+        A, B = np.ldexp(A0, ea), np.ldexp(B0, eb)
+        At = A.transpose(0, 2, 1) if ta else A
+        Bt = B.transpose(0, 2, 1) if tb else B
+        C = L.grouped_gemm(to_dev(At), to_dev(Bt), bool(ta), bool(tb)).cpu().numpy().astype(np.float64)
+        A64, B64 = A.astype(np.float64), B.astype(np.float64)
+        ref = A64 @ B64
+        bound = gamma(Kd + 1) * (np.abs(A64) @ np.abs(B64)) + (Kd + 1) * 2.0**-149
+        assert np.all(np.isfinite(C)) and np.all(np.abs(C - ref) <= bound), \
+            np.max(np.abs(C - ref) / bound)
+        if Kd == 1:
+            np.testing.assert_array_equal(C, ref.astype(np.float32))
+
+
+def test_grouped_gemm_products_next_to_the_largest_number():
+    """Finite operands whose leading bf16 pieces round up: to an infinity, or to
+    a product beyond the largest fp32 number where x y itself is below it."""
+    L = _lsgd()
+    root = np.float32(2.0**64 * (1 - 2.0**-24))   # its square: 2^128 (1 - 2^-23)
+    big = np.float32(np.finfo(np.float32).max)
+    for x, y in ((root, root), (big, np.float32(0.5)), (big, np.float32(1)), (-big, np.float32(1))):
+        A = np.zeros((1, 70, 40), np.float32)
+        B = np.zeros((1, 40, 66), np.float32)
+        A[0, :, 17], B[0, 17, :] = x, y
+        C = L.grouped_gemm(to_dev(A), to_dev(B)).cpu().numpy()
+        want = np.float32(np.float64(x) * np.float64(y))
+        assert np.isfinite(want)
+        np.testing.assert_array_equal(C, np.full_like(C, want))
 
 
 # ------------------------------------------------------------------ average

@@ -137,6 +137,33 @@ def test_update_and_head_at_tile_edges(widths, K, B, dtype):
         _compare_steps(w, X, y, w0, PARAM_TOL_FP32, 1e-4)
 
 
+@pytest.mark.parametrize("widths,B", [((64, 64), 64),        # whole tiles
+                                      ((64, 128, 10), 64),
+                                      ((37, 45), 600)])      # ragged; rows past those kept in LDS
+def test_a_value_beyond_the_split_products(widths, B):
+    """One step with the largest fp32 number, which rounds to an infinity in
+    bf16, in a dataset row that replica 0 draws: the wavefronts that meet it (as
+    a gathered row of the forward product and of the update) form their tiles
+    with the fp32 instruction. Every row of every layer, on its own scale."""
+    w = _small(widths, B=B, N=4000, K=2, H=1, rounds=1, lr=0.01)
+    X, y, w0 = _small_data(w)
+    row = int(O.sample_indices(w.sample_seed, 0, 0, w.K, w.N, B)[B - 1])
+    X[row, 5] = np.finfo(np.float32).max
+    w0 *= np.float32(0.05)               # activations and logits below it
+    y[row] = (y[row] + 1) % widths[-1]   # a class this row does not put first
+    reps = make_replicas(w, X, y, w0)
+    reps.local_step(w.lr)
+    st = O.State(w0, w.K)
+    O.local_step(st, w, X, y, w.lr)
+    for k in range(w.K):
+        got = O.unpack(reps.read_params(k).cpu().numpy().astype(np.float64), w.widths)
+        for (gw, gb), (ow, ob) in zip(got, O.unpack(st.W[k], w.widths)):
+            assert (np.abs(ow).max() > 1e28) == (k == 0)
+            err = np.abs(gw - ow).max(axis=1) / np.abs(ow).max(axis=1)
+            assert err.max() <= PARAM_TOL_FP32, (k, err.max())
+            assert normwise(gb, ob) <= PARAM_TOL_FP32
+
+
 def test_batch_larger_than_the_gathered_row_cache():
     """A local batch of 600 rows (the weight-gradient kernel caches 512
     gathered row indices in LDS and reads the rest from memory)."""
