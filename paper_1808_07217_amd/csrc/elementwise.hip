@@ -137,34 +137,50 @@ struct Tree<1> {
   }
 };
 
-// Same tree for a run-time K: a binary counter of power-of-two partial sums.
-template <typename F>
-__device__ auto tree_sum_rt(const F& ld, int K) {
-  decltype(ld(0)) st[24];
-  int sz[24];
-  int top = 0;
-  for (int k = 0; k < K; ++k) {
-    auto v = ld(k);
-    int size = 1;
-    while (top > 0 && sz[top - 1] == size) {
-      v = st[top - 1] + v;
-      size *= 2;
-      --top;
+// Same tree for a run-time K: blocks of eight through a binary counter of
+// power-of-two sums, then the K % 8 left over, folded from the right. The
+// counter's levels are unrolled, so that it stays in registers: LV of them hold
+// 8 (2^LV - 1) + 7 replicas.
+template <int LV, typename F>
+__device__ __forceinline__ auto tree_sum_rt(const F& ld, int K) {
+  using V = decltype(ld(0));
+  const int q = K / 8, r = K % 8;
+  V st[LV];
+  for (int c = 0; c < q; ++c) {
+    V v = Tree<8>::sum(ld, 8 * c);
+    bool carry = true;
+#pragma unroll
+    for (int l = 0; l < LV; ++l) {
+      if (!carry) continue;
+      if (c >> l & 1) {
+        v = st[l] + v;
+      } else {
+        st[l] = v;
+        carry = false;
+      }
     }
-    st[top] = v;
-    sz[top] = size;
-    ++top;
   }
-  auto v = st[top - 1];
-  for (int i = top - 2; i >= 0; --i) v = st[i] + v;
+  V v{};
+  bool any = false;  // (uniform, as K is)
+  auto left = [&](const V& w) __attribute__((always_inline)) {
+    v = any ? w + v : w;
+    any = true;
+  };
+  if (r & 1) left(ld(K - 1));
+  if (r & 2) left(Tree<2>::sum(ld, K - r % 4));
+  if (r & 4) left(Tree<4>::sum(ld, K - r));
+#pragma unroll
+  for (int l = 0; l < LV; ++l)
+    if (q >> l & 1) left(st[l]);
   return v;
 }
+// KT > 0: KT replicas; 0 and -1: any K up to 127, any K.
 template <int KT, typename F>
 __device__ __forceinline__ auto tree_sum(const F& ld, int K) {
   if constexpr (KT > 0)
     return Tree<KT>::sum(ld, 0);
   else
-    return tree_sum_rt(ld, K);
+    return tree_sum_rt<KT == 0 ? 4 : 28>(ld, K);
 }
 
 // Four floats, and four bf16 values, at any element's alignment: the row
@@ -195,10 +211,11 @@ __device__ __forceinline__ void store_bf16x4(bf16_t* p, v4f v) {
 // Working set above which a stream takes the NT form (the cache holds 256 MB).
 constexpr long long kNtBytes = 240LL << 20;
 
-// The replica average: thread i owns elements 4i .. 4i+3 of every replica (the
-// last thread the n % 4 elements left over). The grid's y index picks a block
-// of K consecutive replicas (hierarchical averaging; a single block is the
-// global average).
+// The replica average: item i owns elements 4i .. 4i+3 of every replica; the
+// n % 4 elements left over are an item each (one thread taking them in turn
+// would chain their K loads: 82 us instead of 7 for 24 rows of 100003).
+// The grid's y index picks a block of K consecutive replicas (hierarchical
+// averaging; a single block is the global average).
 // mean_out != nullptr (one block): write the mean there (and its bf16 copy to
 // Wb [n] when given) and leave W untouched.
 // HBM-bound. 16 x 16.8M (2.1 GB read and written): 455 us, with the NT
@@ -209,34 +226,34 @@ __global__ __launch_bounds__(256) void k_average4(float* W, bf16_t* Wb, int K, l
   W += blockIdx.y * (long long)K * ld;
   if (Wb) Wb += blockIdx.y * (long long)K * ld;
   const float Kf = (float)K;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; 4 * i < n;
+  const long long n4 = n / 4, items = n4 + n % 4;
+  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < items;
        i += (long long)gridDim.x * blockDim.x) {
-    const long long e0 = 4 * i;
-    if (e0 + 4 <= n) {
-      const v4f s = tree_sum<KT>([&](int k) { return ld4<NT>(W + k * ld + e0); }, K);
+    if (i < n4) {
+      const long long e = 4 * i;
+      const v4f s = tree_sum<KT>([&](int k) { return ld4<NT>(W + k * ld + e); }, K);
       const v4f mean = v4f{s.x / Kf, s.y / Kf, s.z / Kf, s.w / Kf};
       if (mean_out) {
-        *(v4f_any*)(mean_out + e0) = mean;
-        if (Wb) store_bf16x4(Wb + e0, mean);
+        *(v4f_any*)(mean_out + e) = mean;
+        if (Wb) store_bf16x4(Wb + e, mean);
         continue;
       }
       for (int k = 0; k < K; ++k) {
-        st4<NT>(W + k * ld + e0, mean);
-        if (Wb) store_bf16x4(Wb + k * ld + e0, mean);
+        st4<NT>(W + k * ld + e, mean);
+        if (Wb) store_bf16x4(Wb + k * ld + e, mean);
       }
       continue;
     }
-    for (long long e = e0; e < n; ++e) {
-      const float mean = tree_sum<KT>([&](int k) { return W[k * ld + e]; }, K) / Kf;
-      if (mean_out) {
-        mean_out[e] = mean;
-        if (Wb) Wb[e] = f32_to_bf16(mean);
-        continue;
-      }
-      for (int k = 0; k < K; ++k) {
-        W[k * ld + e] = mean;
-        if (Wb) Wb[k * ld + e] = f32_to_bf16(mean);
-      }
+    const long long e = 3 * n4 + i;
+    const float mean = tree_sum<KT>([&](int k) { return W[k * ld + e]; }, K) / Kf;
+    if (mean_out) {
+      mean_out[e] = mean;
+      if (Wb) Wb[e] = f32_to_bf16(mean);
+      continue;
+    }
+    for (int k = 0; k < K; ++k) {
+      W[k * ld + e] = mean;
+      if (Wb) Wb[k * ld + e] = f32_to_bf16(mean);
     }
   }
 }
@@ -256,37 +273,37 @@ __global__ __launch_bounds__(256) void k_average_gm4(float* W, bf16_t* Wb, int K
                                                      long long ld, float* ws, float* ug,
                                                      float mg, float lr) {
   const float Kf = (float)K;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; 4 * i < n;
+  const long long n4 = n / 4, items = n4 + n % 4;
+  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < items;
        i += (long long)gridDim.x * blockDim.x) {
-    const long long e0 = 4 * i;
-    if (e0 + 4 <= n) {
-      const v4f s = tree_sum<KT>([&](int k) { return ld4<NT>(W + k * ld + e0); }, K);
-      v4f w = *(const v4f_any*)(ws + e0), u = *(const v4f_any*)(ug + e0);
+    if (i < n4) {
+      const long long e = 4 * i;
+      const v4f s = tree_sum<KT>([&](int k) { return ld4<NT>(W + k * ld + e); }, K);
+      v4f w = *(const v4f_any*)(ws + e), u = *(const v4f_any*)(ug + e);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float we = w[e], ue = u[e];
-        gm_step(s[e] / Kf, we, ue, mg, lr);
-        w[e] = we;
-        u[e] = ue;
+      for (int j = 0; j < 4; ++j) {
+        float wj = w[j], uj = u[j];
+        gm_step(s[j] / Kf, wj, uj, mg, lr);
+        w[j] = wj;
+        u[j] = uj;
       }
-      *(v4f_any*)(ws + e0) = w;
-      *(v4f_any*)(ug + e0) = u;
+      *(v4f_any*)(ws + e) = w;
+      *(v4f_any*)(ug + e) = u;
       for (int k = 0; k < K; ++k) {
-        st4<NT>(W + k * ld + e0, w);
-        if (Wb) store_bf16x4(Wb + k * ld + e0, w);
+        st4<NT>(W + k * ld + e, w);
+        if (Wb) store_bf16x4(Wb + k * ld + e, w);
       }
       continue;
     }
-    for (long long e = e0; e < n; ++e) {
-      const float mean = tree_sum<KT>([&](int k) { return W[k * ld + e]; }, K) / Kf;
-      float w = ws[e], u = ug[e];
-      gm_step(mean, w, u, mg, lr);
-      ws[e] = w;
-      ug[e] = u;
-      for (int k = 0; k < K; ++k) {
-        W[k * ld + e] = w;
-        if (Wb) Wb[k * ld + e] = f32_to_bf16(w);
-      }
+    const long long e = 3 * n4 + i;
+    const float mean = tree_sum<KT>([&](int k) { return W[k * ld + e]; }, K) / Kf;
+    float w = ws[e], u = ug[e];
+    gm_step(mean, w, u, mg, lr);
+    ws[e] = w;
+    ug[e] = u;
+    for (int k = 0; k < K; ++k) {
+      W[k * ld + e] = w;
+      if (Wb) Wb[k * ld + e] = f32_to_bf16(w);
     }
   }
 }
@@ -398,6 +415,38 @@ hipError_t launch_sgd_update(float* W, float* U, const float* G, long long n,
   return hipGetLastError();
 }
 
+// The averages' instances: up to 16 replicas, and 32 and 64, with every load of
+// an item in flight at once; other counts by blocks of eight, each waiting for
+// the one before (32 rows of 100003: 6.6 us, by blocks 8.1; 64 of 1841162: 203
+// against 216; 24 of 100003: 6.6 by blocks).
+#define LSGD_FOR_REPLICAS(K, LAUNCH) \
+  switch (K) {                       \
+    case 1: LAUNCH(1); break;        \
+    case 2: LAUNCH(2); break;        \
+    case 3: LAUNCH(3); break;        \
+    case 4: LAUNCH(4); break;        \
+    case 5: LAUNCH(5); break;        \
+    case 6: LAUNCH(6); break;        \
+    case 7: LAUNCH(7); break;        \
+    case 8: LAUNCH(8); break;        \
+    case 9: LAUNCH(9); break;        \
+    case 10: LAUNCH(10); break;      \
+    case 11: LAUNCH(11); break;      \
+    case 12: LAUNCH(12); break;      \
+    case 13: LAUNCH(13); break;      \
+    case 14: LAUNCH(14); break;      \
+    case 15: LAUNCH(15); break;      \
+    case 16: LAUNCH(16); break;      \
+    case 32: LAUNCH(32); break;      \
+    case 64: LAUNCH(64); break;      \
+    default:                         \
+      if (K < 128) {                 \
+        LAUNCH(0);                   \
+      } else {                       \
+        LAUNCH(-1);                  \
+      }                              \
+  }
+
 hipError_t launch_average_blocks(float* W, bf16_t* Wb, int Kb, int blocks,
                                  long long n, long long ld, float* mean_out,
                                  hipStream_t s) {
@@ -405,36 +454,15 @@ hipError_t launch_average_blocks(float* W, bf16_t* Wb, int Kb, int blocks,
   if (blocks > 65535 || (mean_out && blocks != 1)) return hipErrorInvalidValue;
   const int K = Kb;
   const bool nt = 4LL * K * blocks * n >= kNtBytes;
-  const dim3 grid(grid_for((n + 3) / 4, 256), blocks), block(256);
-#define LSGD_AVG(KK)                                                            \
-  if (nt)                                                                       \
+  const dim3 grid(grid_for(n / 4 + n % 4, 256), blocks), block(256);
+#define LSGD_AVG(KK)                                                               \
+  if (nt)                                                                          \
     hipLaunchKernelGGL((k_average4<KK, true>), grid, block, 0, s, W, Wb, K, n, ld, \
-                       mean_out);                                               \
-  else                                                                          \
+                       mean_out);                                                  \
+  else                                                                             \
     hipLaunchKernelGGL((k_average4<KK, false>), grid, block, 0, s, W, Wb, K, n, ld, \
                        mean_out)
-#define LSGD_AVG_CASE(KK) \
-  case KK:                \
-    LSGD_AVG(KK);         \
-    break;
-  switch (K) {
-    LSGD_AVG_CASE(1)
-    LSGD_AVG_CASE(2)
-    LSGD_AVG_CASE(3)
-    LSGD_AVG_CASE(4)
-    LSGD_AVG_CASE(5)
-    LSGD_AVG_CASE(6)
-    LSGD_AVG_CASE(8)
-    LSGD_AVG_CASE(10)
-    LSGD_AVG_CASE(12)
-    LSGD_AVG_CASE(16)
-    LSGD_AVG_CASE(24)
-    LSGD_AVG_CASE(32)
-    LSGD_AVG_CASE(64)
-    default:
-      LSGD_AVG(0);
-  }
-#undef LSGD_AVG_CASE
+  LSGD_FOR_REPLICAS(K, LSGD_AVG)
 #undef LSGD_AVG
   return hipGetLastError();
 }
@@ -449,30 +477,15 @@ hipError_t launch_average_gm(float* W, bf16_t* Wb, int K, long long n,
                              float lr, hipStream_t s) {
   if (n <= 0 || K <= 0) return hipSuccess;
   const bool nt = 4LL * K * n >= kNtBytes;
-  const dim3 grid(grid_for((n + 3) / 4, 256)), block(256);
-#define LSGD_AVG_GM(KK)                                                             \
-  if (nt)                                                                           \
-    hipLaunchKernelGGL((k_average_gm4<KK, true>), grid, block, 0, s, W, Wb, K, n, ld, \
-                       ws, ug, mg, lr);                                             \
-  else                                                                              \
+  const dim3 grid(grid_for(n / 4 + n % 4, 256)), block(256);
+#define LSGD_AVG_GM(KK)                                                                \
+  if (nt)                                                                              \
+    hipLaunchKernelGGL((k_average_gm4<KK, true>), grid, block, 0, s, W, Wb, K, n, ld,  \
+                       ws, ug, mg, lr);                                                \
+  else                                                                                 \
     hipLaunchKernelGGL((k_average_gm4<KK, false>), grid, block, 0, s, W, Wb, K, n, ld, \
                        ws, ug, mg, lr)
-#define LSGD_AVG_GM_CASE(KK) \
-  case KK:                   \
-    LSGD_AVG_GM(KK);         \
-    break;
-  switch (K) {
-    LSGD_AVG_GM_CASE(1)
-    LSGD_AVG_GM_CASE(2)
-    LSGD_AVG_GM_CASE(4)
-    LSGD_AVG_GM_CASE(8)
-    LSGD_AVG_GM_CASE(16)
-    LSGD_AVG_GM_CASE(32)
-    LSGD_AVG_GM_CASE(64)
-    default:
-      LSGD_AVG_GM(0);
-  }
-#undef LSGD_AVG_GM_CASE
+  LSGD_FOR_REPLICAS(K, LSGD_AVG_GM)
 #undef LSGD_AVG_GM
   return hipGetLastError();
 }

@@ -243,6 +243,26 @@ def test_replica_average_rows_at_any_alignment(K, P):
         np.testing.assert_array_equal(got[k], want)
 
 
+@pytest.mark.parametrize("K", [3, 5, 7, 9, 13, 15, 17, 20, 22, 31, 48, 63, 65, 100, 127, 128, 131, 300])
+def test_averages_of_any_count(K):
+    """Both averages in the documented order, bit for bit, for counts with an
+    instance of their own, made of blocks of eight, and beyond 127; the rows'
+    last elements no whole vector. (With m = 0, a step size of 1, w_s = 0 and
+    u = 0 the global-momentum form leaves the mean.)"""
+    L = _lsgd()
+    for P in (1, 3, 1026, 2051):
+        print(f"average K={K} P={P}", flush=True)
+        W = np.random.default_rng(K + P).standard_normal((K, P), dtype=np.float32)
+        want = (_tree_f32([W[k] for k in range(K)]) / np.float32(K)).astype(np.float32)
+        Wd = to_dev(W)
+        L.replica_average(Wd)
+        np.testing.assert_array_equal(Wd.cpu().numpy(), np.broadcast_to(want, (K, P)))
+        Wd, ws, u = to_dev(W), torch.zeros(P, device=device()), torch.zeros(P, device=device())
+        L.replica_average_global_momentum(Wd, ws, u, 0.0, 1.0)
+        np.testing.assert_array_equal(Wd.cpu().numpy(), np.broadcast_to(want, (K, P)))
+        np.testing.assert_array_equal(u.cpu().numpy(), -want)
+
+
 @pytest.mark.parametrize("K", [1, 2, 4, 16, 64])
 def test_average_of_identical_replicas_is_identity(K):
     L = _lsgd()
