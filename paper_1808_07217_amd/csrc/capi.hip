@@ -996,11 +996,12 @@ lsgd_status average_running_stats(lsgd_ctx* c, int Kb) {
   const long long Rs = c->lay.rp.Rs;
   if (Kb == K)
     LSGD_LAUNCH(c, "average_bn_running",
-                lsgd::launch_average(c->RS(), nullptr, K, Rs, Rs, nullptr, c->stream));
+                lsgd::launch_average(c->RS(), nullptr, K, Rs, Rs, nullptr, lsgd::kNtBytes,
+                                     c->stream));
   else if (Kb > 1)
     LSGD_LAUNCH(c, "average_bn_running",
                 lsgd::launch_average_blocks(c->RS(), nullptr, Kb, K / Kb, Rs, Rs, nullptr,
-                                            c->stream));
+                                            lsgd::kNtBytes, c->stream));
   return LSGD_OK;
 }
 
@@ -1022,13 +1023,13 @@ lsgd_status do_average(lsgd_ctx* c) {
     // replica
     LSGD_LAUNCH(c, "average",
                 lsgd::launch_average(c->W(), c->Wbarb(), c->cfg.K, c->lay.Ps, c->lay.Ps,
-                                     c->Wbar(), c->stream));
+                                     c->Wbar(), lsgd::kNtBytes, c->stream));
     c->pending = true;
     return LSGD_OK;
   }
   LSGD_LAUNCH(c, "average",
               lsgd::launch_average(c->W(), c->Wb(), c->cfg.K, c->lay.Ps,
-                                   c->lay.Ps, nullptr, c->stream));
+                                   c->lay.Ps, nullptr, lsgd::kNtBytes, c->stream));
   return average_running_stats(c, c->cfg.K);
 }
 
@@ -1047,7 +1048,7 @@ lsgd_status do_synchronise(lsgd_ctx* c, float lr) {
   LSGD_LAUNCH(c, "average",
               lsgd::launch_average_gm(c->W(), c->Wb(), c->cfg.K, c->lay.Ps,
                                       c->lay.Ps, c->Wsync(), c->Ug(),
-                                      c->cfg.global_momentum, lr, c->stream));
+                                      c->cfg.global_momentum, lr, lsgd::kNtBytes, c->stream));
   return average_running_stats(c, c->cfg.K);
 }
 
@@ -1058,7 +1059,7 @@ lsgd_status do_average_blocks(lsgd_ctx* c, int Kb) {
   LSGD_LAUNCH(c, "average_blocks",
               lsgd::launch_average_blocks(c->W(), c->Wb(), Kb, c->cfg.K / Kb,
                                           c->lay.Ps, c->lay.Ps, nullptr,
-                                          c->stream));
+                                          lsgd::kNtBytes, c->stream));
   return average_running_stats(c, Kb);
 }
 
@@ -1331,7 +1332,7 @@ lsgd_status lsgd_read_params(lsgd_ctx* ctx, int32_t replica, float* d_dst) {
                                 hipMemcpyDeviceToDevice, ctx->stream));
   } else {
     LSGD_CK(ctx, lsgd::launch_average(ctx->W(), nullptr, ctx->cfg.K, ctx->lay.P,
-                                      ctx->lay.Ps, d_dst, ctx->stream));
+                                      ctx->lay.Ps, d_dst, lsgd::kNtBytes, ctx->stream));
   }
   return LSGD_OK;
 }
@@ -1649,7 +1650,7 @@ lsgd_status lsgd_grouped_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b,
 
 lsgd_status lsgd_replica_average(float* d_W, int32_t K, int64_t P, void* stream) {
   if (!d_W || K < 1 || P < 0) return LSGD_E_INVALID;
-  hipError_t e = lsgd::launch_average(d_W, nullptr, K, P, P, nullptr,
+  hipError_t e = lsgd::launch_average(d_W, nullptr, K, P, P, nullptr, lsgd::kNtBytesCaller,
                                       (hipStream_t)stream);
   return e == hipSuccess ? LSGD_OK : LSGD_E_HIP;
 }
@@ -1658,7 +1659,7 @@ lsgd_status lsgd_replica_average_blocks(float* d_W, int32_t K, int32_t Kb,
                                        int64_t P, void* stream) {
   if (!d_W || K < 1 || Kb < 1 || K % Kb || P < 0) return LSGD_E_INVALID;
   hipError_t e = lsgd::launch_average_blocks(d_W, nullptr, Kb, K / Kb, P, P,
-                                             nullptr, (hipStream_t)stream);
+                                             nullptr, lsgd::kNtBytesCaller, (hipStream_t)stream);
   return e == hipSuccess ? LSGD_OK : LSGD_E_HIP;
 }
 
@@ -1670,7 +1671,7 @@ lsgd_status lsgd_replica_average_global_momentum(float* d_W, int32_t K,
       m_global < 0.f || m_global >= 1.f || !std::isfinite(lr) || lr == 0.f)
     return LSGD_E_INVALID;
   hipError_t e = lsgd::launch_average_gm(d_W, nullptr, K, P, P, d_wsync, d_ug,
-                                         m_global, lr, (hipStream_t)stream);
+                                         m_global, lr, lsgd::kNtBytesCaller, (hipStream_t)stream);
   return e == hipSuccess ? LSGD_OK : LSGD_E_HIP;
 }
 

@@ -208,8 +208,6 @@ __device__ __forceinline__ void store_bf16x4(bf16_t* p, v4f v) {
   const uint32_t b = f32_to_bf16(v.z) | ((uint32_t)f32_to_bf16(v.w) << 16);
   *(u32x2_any*)p = u32x2_any{a, b};
 }
-// Working set above which a stream takes the NT form (the cache holds 256 MB).
-constexpr long long kNtBytes = 240LL << 20;
 
 // The replica average: item i owns elements 4i .. 4i+3 of every replica; the
 // n % 4 elements left over are an item each (one thread taking them in turn
@@ -449,11 +447,11 @@ hipError_t launch_sgd_update(float* W, float* U, const float* G, long long n,
 
 hipError_t launch_average_blocks(float* W, bf16_t* Wb, int Kb, int blocks,
                                  long long n, long long ld, float* mean_out,
-                                 hipStream_t s) {
+                                 long long nt_bytes, hipStream_t s) {
   if (n <= 0 || Kb <= 0 || blocks <= 0) return hipSuccess;
   if (blocks > 65535 || (mean_out && blocks != 1)) return hipErrorInvalidValue;
   const int K = Kb;
-  const bool nt = 4LL * K * blocks * n >= kNtBytes;
+  const bool nt = 4LL * K * blocks * n >= nt_bytes;
   const dim3 grid(grid_for(n / 4 + n % 4, 256), blocks), block(256);
 #define LSGD_AVG(KK)                                                               \
   if (nt)                                                                          \
@@ -468,15 +466,15 @@ hipError_t launch_average_blocks(float* W, bf16_t* Wb, int Kb, int blocks,
 }
 
 hipError_t launch_average(float* W, bf16_t* Wb, int K, long long n,
-                          long long ld, float* mean_out, hipStream_t s) {
-  return launch_average_blocks(W, Wb, K, 1, n, ld, mean_out, s);
+                          long long ld, float* mean_out, long long nt_bytes, hipStream_t s) {
+  return launch_average_blocks(W, Wb, K, 1, n, ld, mean_out, nt_bytes, s);
 }
 
 hipError_t launch_average_gm(float* W, bf16_t* Wb, int K, long long n,
                              long long ld, float* ws, float* ug, float mg,
-                             float lr, hipStream_t s) {
+                             float lr, long long nt_bytes, hipStream_t s) {
   if (n <= 0 || K <= 0) return hipSuccess;
-  const bool nt = 4LL * K * n >= kNtBytes;
+  const bool nt = 4LL * K * n >= nt_bytes;
   const dim3 grid(grid_for(n / 4 + n % 4, 256)), block(256);
 #define LSGD_AVG_GM(KK)                                                                \
   if (nt)                                                                              \

@@ -876,9 +876,6 @@ hipError_t dispatch(int dtype, const GemmArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// State from which the update streams past the caches.
-constexpr long long kNtBytes = 240LL << 20;
-
 void step_tail_sample(StepTail& t, int epoch, uint64_t seed, int64_t step, int64_t N,
                       int32_t* idx) {
   t.idx = idx;

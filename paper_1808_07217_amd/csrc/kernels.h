@@ -18,6 +18,19 @@ __device__ __forceinline__ float step_dir(float u, float g, float mom, int mode)
 }
 
 
+// Bytes from which a kernel streams past the caches (nontemporal loads and
+// stores; the Infinity Cache holds 256 MB). kNtBytes: updates, state copies and
+// a context's averages, whose data the step before has left in HBM (16 rows of
+// 272 MB in all not in the cache: 103 us, 115 with it; a round of one step of 40
+// replicas of 1.84M weights 645 us, 671; below the bound the next kernel
+// finds the lines it reads: an update of 225 MB 86 us, streamed 92).
+// kNtBytesCaller: averages of a caller's array, which may have just been
+// written. In the cache, 16 rows of 272 MB take 84 us and streamed 99, of 300 MB
+// 98 and 110, of 340 MB 125 and 129, of 400 MB 159 and 156; out of it streaming
+// gains 8 to 12% at all of them.
+constexpr long long kNtBytes = 240LL << 20;
+constexpr long long kNtBytesCaller = 320LL << 20;
+
 typedef uint16_t bf16_t;  // bfloat16 bit pattern
 
 // fp32 -> bf16, round to nearest even (finite inputs; overflow gives inf).
@@ -280,15 +293,16 @@ hipError_t launch_sgd_update(float* W, float* U, const float* G, long long n,
                              hipStream_t s);
 // K-way average of the first n elements of K rows spaced ld apart: every
 // row (and its bf16 copy in Wb) := the mean; with mean_out, only the mean is
-// written, to mean_out [n] (and its bf16 copy to Wb [n] when given).
+// written, to mean_out [n] (and its bf16 copy to Wb [n] when given). From
+// nt_bytes of rows on it streams past the caches.
 hipError_t launch_average(float* W, bf16_t* Wb, int K, long long n,
-                          long long ld, float* mean_out, hipStream_t s);
+                          long long ld, float* mean_out, long long nt_bytes, hipStream_t s);
 // The K-way average with global momentum: mean of the K rows, then
 // ug = mg ug + (ws - mean) / lr, ws -= lr ug, and every row := ws (ws, ug:
 // [n] fp32, updated in place).
 hipError_t launch_average_gm(float* W, bf16_t* Wb, int K, long long n,
                              long long ld, float* ws, float* ug, float mg,
-                             float lr, hipStream_t s);
+                             float lr, long long nt_bytes, hipStream_t s);
 // Single-launch round for softmax regression (tiny.hip): every replica and
 // its buffer live in LDS for the H steps and the average.
 constexpr int kTinyMaxC = 32, kTinyMaxH = 64;
@@ -332,7 +346,7 @@ hipError_t launch_sign_sync_static(float* W, float* E, float* ws, int K, long lo
 // (mean_out only with blocks == 1).
 hipError_t launch_average_blocks(float* W, bf16_t* Wb, int Kb, int blocks,
                                  long long n, long long ld, float* mean_out,
-                                 hipStream_t s);
+                                 long long nt_bytes, hipStream_t s);
 hipError_t launch_broadcast(const float* src, float* W, bf16_t* Wb, int K,
                             long long n, long long ld, int replica,
                             hipStream_t s);

@@ -208,6 +208,17 @@ def _tree_f32(rows):
     return (_tree_f32(rows[:h]) + _tree_f32(rows[h:])).astype(np.float32)
 
 
+def _tree_rows(W):
+    """The same order on a device tensor's rows."""
+    n = W.shape[0]
+    if n == 1:
+        return W[0]
+    h = 1
+    while 2 * h < n:
+        h *= 2
+    return _tree_rows(W[:h]) + _tree_rows(W[h:])
+
+
 @pytest.mark.parametrize("K,P", [(1, 7), (3, 650), (4, 650), (16, 1841162 + 6),
                                  (64, 10001), (5, 4), (7, 1027)])
 def test_replica_average(K, P):
@@ -261,6 +272,30 @@ def test_averages_of_any_count(K):
         L.replica_average_global_momentum(Wd, ws, u, 0.0, 1.0)
         np.testing.assert_array_equal(Wd.cpu().numpy(), np.broadcast_to(want, (K, P)))
         np.testing.assert_array_equal(u.cpu().numpy(), -want)
+
+
+@pytest.mark.parametrize("K,P", [(5, (17 << 20) + 3), (20, (5 << 20) + 1)])  # 357 and 420 MB
+def test_averages_streamed_past_the_caches(K, P):
+    """Both averages, and the plain one within two blocks, on arrays that take
+    the nontemporal form, bit for bit as in any other size."""
+    L = _lsgd()
+    print(f"streamed averages K={K} P={P}", flush=True)
+    W = to_dev(np.random.default_rng(K).standard_normal((K, P), dtype=np.float32))
+
+    def want(k0, k1):  # the documented order, on the device, in fp32
+        t = _tree_rows(W[k0:k1]) / torch.full((), k1 - k0, dtype=torch.float32, device=device())
+        return t.expand(k1 - k0, P)
+
+    Wd = W.clone()
+    L.replica_average(Wd)
+    assert torch.equal(Wd, want(0, K))
+    Wd, ws, u = W.clone(), torch.zeros(P, device=device()), torch.zeros(P, device=device())
+    L.replica_average_global_momentum(Wd, ws, u, 0.0, 1.0)
+    assert torch.equal(Wd, want(0, K))
+    if K % 2 == 0:
+        Wd = W.clone()
+        L.replica_average_blocks(Wd, K // 2)
+        assert torch.equal(Wd, torch.cat([want(0, K // 2), want(K // 2, K)]))
 
 
 @pytest.mark.parametrize("K", [1, 2, 4, 16, 64])
