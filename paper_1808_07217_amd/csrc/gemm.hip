@@ -219,7 +219,8 @@ struct Quad<true> {
 // still is one vector load at a clamped address, and what a ragged edge needs
 // (a shift, zeros) is done as the quad goes to LDS: loads behind a branch would
 // each be waited for.
-// NT: the update's W and U pass by the caches (see gemm_update).
+// NT: 1, the update's W and U pass by the caches; 2, all but the W it reads (see
+// gemm_update).
 // LDS: one plane of an operand of R rows (columns) and its pitch, in elements;
 // two buffers of an operand's planes.
 constexpr int kMapRows = 512;
@@ -229,7 +230,7 @@ constexpr int ring_size(bool bf, bool kc, int R, int BK) {
   return 2 * (bf ? 1 : 3) * plane_size(kc, R, BK);
 }
 template <bool BF, bool AT, bool BT, int EPI, bool GATHER, int BM, int BN, int BK, int D,
-          bool FULL, bool NT = false>
+          bool FULL, int NT = 0>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t, bf16_t* sA,
                                           bf16_t* sB, int32_t* srmap) {
   using Q = Quad<BF>;
@@ -289,8 +290,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t, bf16_
           for (int v = 0; v < 16; ++v) {
             const float* wp = Wr + tile_off(i, j, v);
             const float* up = Ur + tile_off(i, j, v);
-            wv[i][j][v] = NT ? __builtin_nontemporal_load(wp) : *wp;
-            uv[i][j][v] = NT ? __builtin_nontemporal_load(up) : *up;
+            wv[i][j][v] = NT == 1 ? __builtin_nontemporal_load(wp) : *wp;
+            uv[i][j][v] = NT != 0 ? __builtin_nontemporal_load(up) : *up;
           }
     }
   };
@@ -592,7 +593,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t, bf16_
           if (!FULL && (m >= M || n >= N)) continue;
           const unsigned o = tile_off(i, j, v);
           sgd_step(wv[i][j][v], uv[i][j][v], hi[i][j][v], a);
-          if constexpr (NT) {
+          if constexpr (NT != 0) {
             __builtin_nontemporal_store(wv[i][j][v], Wt + o);
             __builtin_nontemporal_store(uv[i][j][v], Ut + o);
           } else {
@@ -687,7 +688,9 @@ __global__ __launch_bounds__(kThreads, BM * BN > 128 * 64 ? 1 : 2) void gemm_mm(
 // rows: 69 us, D = 4 77, spilling). NT: a state beyond the 256 MB Infinity
 // Cache is streamed past the caches (64 x 3072 x 2048: fp32 1292 -> 1190 us,
 // bf16 1427 -> 1347 us, 5.4 TB/s; a state that fits loses the lines the next
-// step reads: 86 -> 92 us).
+// step reads: 86 -> 92 us); the one mean that all replicas read while a lazy
+// average is pending stays in the caches (NT 2: 64 x 3072-2048-2048-10, all
+// layers, bf16 2229 -> 1979 us, fp32 1956 -> 1812).
 struct UpdArgs {
   GemmArgs p[kUpdMaxProblems];
   int start[kUpdMaxProblems + 1];  // first tile of each problem; [np] = total
@@ -738,7 +741,7 @@ __device__ __forceinline__ void step_tail(const UpdArgs& w, int p, float* red) {
 }
 
 // (bf16: whole tiles in slabs of 64, 94 against 95 us for 16 x 3072 x 512)
-template <bool BF, bool NT>
+template <bool BF, int NT>
 __global__ __launch_bounds__(kThreads, BF ? 3 : 4) void gemm_update(UpdArgs w) {
   constexpr int BK = BF ? 64 : 16;
   __shared__ __attribute__((aligned(16))) bf16_t sA[ring_size(BF, false, 64, BK)];
@@ -905,6 +908,7 @@ hipError_t launch_gemm_update(int dtype, const GemmArgs* list, int n, const Step
   const long long extra = w.nloss + (slots + kThreads - 1) / kThreads;
   w.ntail = (int)((extra + kXcds - 1) / kXcds * kXcds);
   long long total = 0, state = 0;  // tiles; bytes of W, U and the bf16 copy
+  bool shared = false;             // W is read from one model for all replicas
   for (int i = 0; i < n; ++i) {
     GemmArgs& a = w.p[i];
     a = list[i];
@@ -913,22 +917,27 @@ hipError_t launch_gemm_update(int dtype, const GemmArgs* list, int n, const Step
     a.kchunk = (a.Kd + 31) / 32 * 32;
     if (full(a, 64, 64, dtype == 1 ? 64 : 16)) w.whole |= 1u << i;
     state += (long long)a.G * a.M * a.N * (a.Wb ? 10 : 8);
+    shared |= a.Wsrc && a.sWsrc == 0;
     w.start[i] = (int)total;
     total += (long long)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.G;
     if (total > 0x7fffffffLL) return hipErrorInvalidValue;
   }
   w.start[n] = (int)total;
-  const bool nt = state >= kNtBytes;
+  const int nt = state < kNtBytes ? 0 : shared ? 2 : 1;
   if (total + w.ntail > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(total + w.ntail)), block(kThreads);
-  if (dtype == 1 && nt)
-    hipLaunchKernelGGL((gemm_update<true, true>), grid, block, 0, s, w);
-  else if (dtype == 1)
-    hipLaunchKernelGGL((gemm_update<true, false>), grid, block, 0, s, w);
-  else if (nt)
-    hipLaunchKernelGGL((gemm_update<false, true>), grid, block, 0, s, w);
-  else
-    hipLaunchKernelGGL((gemm_update<false, false>), grid, block, 0, s, w);
+#define LSGD_UPDATE(BF, NT) \
+  hipLaunchKernelGGL((gemm_update<BF, NT>), grid, block, 0, s, w)
+  if (dtype == 1) {
+    if (nt == 0) LSGD_UPDATE(true, 0);
+    if (nt == 1) LSGD_UPDATE(true, 1);
+    if (nt == 2) LSGD_UPDATE(true, 2);
+  } else {
+    if (nt == 0) LSGD_UPDATE(false, 0);
+    if (nt == 1) LSGD_UPDATE(false, 1);
+    if (nt == 2) LSGD_UPDATE(false, 2);
+  }
+#undef LSGD_UPDATE
   return hipGetLastError();
 }
 

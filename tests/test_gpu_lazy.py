@@ -93,6 +93,25 @@ def test_lazy_average_is_bit_identical(widths, dtype, K, B, nesterov):
     _same(a, b, w)
 
 
+@pytest.mark.parametrize("widths,dtype,K,B", [
+    ((1024, 1024, 10), "fp32", 32, 32),    # 270 MB of state in whole tiles
+    ((1000, 1040, 10), "fp32", 32, 8),     # and in ragged ones
+    ((1024, 960, 10), "bf16", 32, 64),     # 317 MB with the bf16 copy
+])
+def test_lazy_average_of_a_state_streamed_past_the_caches(widths, dtype, K, B):
+    """The update reads the shared mean through the caches and streams the rest:
+    bit for bit the default form."""
+    w = _small(widths, dtype, K=K, B=B, N=4 * K, nesterov=True)
+    X, y, w0 = _data(w)
+    print(f"lazy average, streamed state {widths} {dtype} K={K}", flush=True)
+    a, b = make_replicas(w, X, y, w0), make_replicas(w, X, y, w0)
+    b.set_lazy_average(True)
+    for r in (a, b):
+        r.run_round([0.02, 0.01])
+        r.run_round([0.01])
+    assert torch.equal(a.read_state(), b.read_state())
+
+
 def test_lazy_average_with_the_single_launch_round():
     """Softmax regression: rounds run as one launch (which averages by
     itself), mixed with lazily averaged step-by-step rounds."""
