@@ -66,11 +66,25 @@ struct Tile {
   int g, s, m0, n0;
 };
 
+// A launch of n workgroups in order: on the grid's x axis, and past 2^23 of them
+// in rows of that (an axis holds fewer than 2^32 threads; a longer one is cut
+// short without an error).
+constexpr int kGridShift = 23;
+dim3 grid_of(long long n) {
+  if (n <= 1LL << kGridShift) return dim3((unsigned)n);
+  return dim3(1u << kGridShift, (unsigned)((n + (1LL << kGridShift) - 1) >> kGridShift));
+}
+__device__ __forceinline__ unsigned workgroup_id() {
+  return (blockIdx.y << kGridShift) + blockIdx.x;
+}
+
+// (g < 0: past the last tile)
 __device__ __forceinline__ Tile decode_tile(const GemmArgs& a, int BM, int BN) {
   const int tn = (a.N + BN - 1) / BN, tm = (a.M + BM - 1) / BM;
   const int per_split = tn * tm, per_g = per_split * a.splits;
   const int total = per_g * a.G;
-  const int p = blockIdx.x;
+  if (workgroup_id() >= (unsigned)total) return Tile{-1, 0, 0, 0};
+  const int p = workgroup_id();
   int l = (total % kXcds == 0) ? (p % kXcds) * (total / kXcds) + p / kXcds : p;
   Tile t;
   t.g = l / per_g;
@@ -671,8 +685,9 @@ template <bool BF, bool AT, bool BT, int EPI, bool GATHER, int BM, int BN, int B
 __global__ __launch_bounds__(kThreads, BM * BN > 128 * 64 ? 1 : 2) void gemm_mm(GemmArgs a) {
   __shared__ __attribute__((aligned(16))) bf16_t sA[ring_size(BF, !AT, BM, BK)];
   __shared__ __attribute__((aligned(16))) bf16_t sB[ring_size(BF, BT, BN, BK)];
-  gemm_tile<BF, AT, BT, EPI, GATHER, BM, BN, BK, D, FULL>(a, decode_tile(a, BM, BN), sA, sB,
-                                                          nullptr);
+  const Tile t = decode_tile(a, BM, BN);
+  if (t.g < 0) return;
+  gemm_tile<BF, AT, BT, EPI, GATHER, BM, BN, BK, D, FULL>(a, t, sA, sB, nullptr);
 }
 
 // Weight gradients fused with their momentum-SGD step, of one or several
@@ -747,11 +762,14 @@ __global__ __launch_bounds__(kThreads, BF ? 3 : 4) void gemm_update(UpdArgs w) {
   __shared__ __attribute__((aligned(16))) bf16_t sA[ring_size(BF, false, 64, BK)];
   __shared__ __attribute__((aligned(16))) bf16_t sB[ring_size(BF, false, 64, BK)];
   __shared__ int32_t srmap[kMapRows];
-  if ((int)blockIdx.x < w.ntail) {
-    step_tail(w, blockIdx.x, (float*)sA);
+  const unsigned id = workgroup_id();
+  if (id < (unsigned)w.ntail) {
+    step_tail(w, id, (float*)sA);
     return;
   }
-  const int total = w.start[w.np], p = blockIdx.x - w.ntail;
+  const int total = w.start[w.np];
+  if (id - w.ntail >= (unsigned)total) return;
+  const int p = id - w.ntail;
   int l = (total % kXcds == 0) ? (p % kXcds) * (total / kXcds) + p / kXcds : p;
   int pi = 0;
   while (pi + 1 < w.np && l >= w.start[pi + 1]) ++pi;
@@ -837,10 +855,10 @@ hipError_t run_tile(const GemmArgs& a, hipStream_t s) {
       (long long)((a.N + BN - 1) / BN) * ((a.M + BM - 1) / BM) * a.G * a.splits;
   if (total > 0x7fffffffLL) return hipErrorInvalidValue;
   if (full(a, BM, BN, BK))
-    hipLaunchKernelGGL((gemm_mm<BF, AT, BT, EPI, GATHER, BM, BN, BK, D, true>), dim3(total),
+    hipLaunchKernelGGL((gemm_mm<BF, AT, BT, EPI, GATHER, BM, BN, BK, D, true>), grid_of(total),
                        dim3(kThreads), 0, s, a);
   else
-    hipLaunchKernelGGL((gemm_mm<BF, AT, BT, EPI, GATHER, BM, BN, BK, D, false>), dim3(total),
+    hipLaunchKernelGGL((gemm_mm<BF, AT, BT, EPI, GATHER, BM, BN, BK, D, false>), grid_of(total),
                        dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
@@ -906,6 +924,7 @@ hipError_t launch_gemm_update(int dtype, const GemmArgs* list, int n, const Step
   w.nloss = tail.rowloss ? tail.K : 0;
   const long long slots = !tail.idx ? 0 : (long long)tail.K * (tail.epoch ? tail.B : (tail.B + 3) / 4);
   const long long extra = w.nloss + (slots + kThreads - 1) / kThreads;
+  if (extra > 0x7fffffffLL - kXcds) return hipErrorInvalidValue;
   w.ntail = (int)((extra + kXcds - 1) / kXcds * kXcds);
   long long total = 0, state = 0;  // tiles; bytes of W, U and the bf16 copy
   bool shared = false;             // W is read from one model for all replicas
@@ -925,7 +944,7 @@ hipError_t launch_gemm_update(int dtype, const GemmArgs* list, int n, const Step
   w.start[n] = (int)total;
   const int nt = state < kNtBytes ? 0 : shared ? 2 : 1;
   if (total + w.ntail > 0x7fffffffLL) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(total + w.ntail)), block(kThreads);
+  const dim3 grid = grid_of(total + w.ntail), block(kThreads);
 #define LSGD_UPDATE(BF, NT) \
   hipLaunchKernelGGL((gemm_update<BF, NT>), grid, block, 0, s, w)
   if (dtype == 1) {

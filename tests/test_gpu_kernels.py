@@ -179,6 +179,16 @@ def test_grouped_gemm_over_the_range_of_fp32(shape, ta, tb):
             np.testing.assert_array_equal(C, ref.astype(np.float32))
 
 
+def test_grouped_gemm_of_more_tiles_than_an_axis_of_the_grid():
+    """65535 outer products of 1 x 16448, 257 tiles each: every result."""
+    L = _lsgd()
+    G, N = 65535, 16448
+    A = torch.arange(1, G + 1, dtype=torch.float32, device=device()).view(G, 1, 1)
+    B = torch.arange(1, N + 1, dtype=torch.float32, device=device()).expand(G, 1, N).contiguous()
+    C = L.grouped_gemm(A, B, out=torch.full((G, 1, N), -1.0, device=device()))
+    assert torch.equal(C, A * B)   # whole numbers: each product rounded once
+
+
 def test_grouped_gemm_products_next_to_the_largest_number():
     """Finite operands whose leading bf16 pieces round up: to an infinity, or to
     a product beyond the largest fp32 number where x y itself is below it."""

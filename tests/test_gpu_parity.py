@@ -164,6 +164,33 @@ def test_a_value_beyond_the_split_products(widths, B):
             assert normwise(gb, ob) <= PARAM_TOL_FP32
 
 
+def test_update_of_more_tiles_than_an_axis_of_the_grid():
+    """33000 replicas of a 1-16384-2 network: 512 nearly empty tiles each, more
+    workgroups together than an axis of a launch holds threads; replicas on both
+    sides of every row of the grid, two steps (the second on rows that the first
+    one drew)."""
+    K, lr = 33000, 0.05
+    w = _small((1, 16384, 2), K=K, B=1, N=K, H=2, rounds=1, lr=lr)
+    X, y, w0 = _small_data(w)
+    reps = make_replicas(w, X, y, w0)
+    loss = torch.empty(2, K, device=device())
+    for h in range(2):
+        reps.local_step(lr, loss[h])
+    loss = loss.cpu().numpy()
+    # workgroups 2^23 and 2^24, behind 33136 of the losses and the sampler: tiles
+    # of layer 1 of replica 32638 and of layer 2 of replica 32406
+    for k in (0, 1, 32405, 32406, 32407, 32637, 32638, 32639, K - 1):
+        m, u = w0.astype(np.float64), np.zeros(w0.size)
+        for h in range(2):
+            idx = O.sample_indices(w.sample_seed, h, k, K, w.N, 1)
+            want, g = O.loss_and_grad(m, w.widths, X[idx], y[idx])
+            m, u = O.sgd_update(m, u, g, lr, w.momentum, w.weight_decay, False)
+            assert rel(loss[h, k], want) <= 1e-4, (k, h)
+        assert normwise(reps.read_params(k).cpu().numpy(), m) <= PARAM_TOL_FP32, k
+        assert normwise(reps.read_momentum(k).cpu().numpy(), u) <= 1e-4, k
+    reps.close()
+
+
 def test_batch_larger_than_the_gathered_row_cache():
     """A local batch of 600 rows (the weight-gradient kernel caches 512
     gathered row indices in LDS and reads the rest from memory)."""
