@@ -333,7 +333,8 @@ __global__ void k_to_bf16(const float* x, bf16_t* y, long long n) {
 template <bool NT>
 __global__ __launch_bounds__(256) void k_copy_rows(float* dst, long long dpitch, const float* src,
                                                    long long spitch, long long n) {
-  const long long e0 = 4 * (blockIdx.x * 256LL + threadIdx.x);
+  // (parts of 2^23 workgroups on the grid's z axis)
+  const long long e0 = 4 * ((((long long)blockIdx.z << 23) + blockIdx.x) * 256 + threadIdx.x);
   float* d = dst + blockIdx.y * dpitch;
   const float* q = src + blockIdx.y * spitch;
   if (e0 + 4 <= n) {
@@ -355,12 +356,12 @@ __global__ void k_fill(float* x, float v, long long n) {
 
 // One element (or float4) per thread over the whole range: measured on the
 // fused update at 1 GB, a full grid streams 15% faster than a grid capped at
-// 16384 workgroups with grid-stride loops. Ranges beyond 2^31 - 1 workgroups
-// fall back to the grid-stride loop the kernels keep.
+// 16384 workgroups with grid-stride loops. An axis of the grid holds fewer than
+// 2^32 threads (a longer one is cut short without an error): longer ranges fall
+// back to the grid-stride loop the kernels keep.
 int grid_for(long long n, int threads) {
-  long long b = (n + threads - 1) / threads;
-  if (b > 0x7fffffffLL) b = 0x7fffffffLL;
-  return b < 1 ? 1 : (int)b;
+  const long long b = (n + threads - 1) / threads, most = 0xffffffffLL / threads;
+  return (int)(b < 1 ? 1 : b < most ? b : most);
 }
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
@@ -507,13 +508,14 @@ hipError_t launch_copy_rows(float* dst, long long dpitch, const float* src,
                             long long spitch, long long n, int rows,
                             hipStream_t s) {
   if (rows <= 0 || n <= 0) return hipSuccess;
-  const long long b = (n + 1023) / 1024;
-  if (b > 0x7fffffffLL || rows > 65535) return hipErrorInvalidValue;
+  if (rows > 65535) return hipErrorInvalidValue;
+  const long long b = (n + 1023) / 1024, part = 1LL << 23;
+  const dim3 grid((unsigned)(b < part ? b : part), rows, (unsigned)((b + part - 1) / part));
   if (8LL * rows * n >= kNtBytes)
-    hipLaunchKernelGGL(k_copy_rows<true>, dim3((unsigned)b, rows), dim3(256), 0, s, dst,
+    hipLaunchKernelGGL(k_copy_rows<true>, grid, dim3(256), 0, s, dst,
                        dpitch, src, spitch, n);
   else
-    hipLaunchKernelGGL(k_copy_rows<false>, dim3((unsigned)b, rows), dim3(256), 0, s, dst,
+    hipLaunchKernelGGL(k_copy_rows<false>, grid, dim3(256), 0, s, dst,
                        dpitch, src, spitch, n);
   return hipGetLastError();
 }

@@ -389,6 +389,16 @@ def test_replica_average_global_momentum(K, P, mg, lr):
     assert np.all(a(ws_got - ws_ref) <= e_w), np.max(a(ws_got - ws_ref) / e_w)
 
 
+def test_update_of_more_elements_than_an_axis_of_the_grid_holds_threads():
+    """2^32 + 5 elements, one a thread (no whole vectors): every one updated."""
+    L = _lsgd()
+    n = 2**32 + 5
+    W, U = torch.zeros(n, device=device()), torch.zeros(n, device=device())
+    L.sgd_update(W, U, torch.ones(n, device=device()), 0.5, 0.0, 0.0)
+    for t, v in ((W, -0.5), (U, 1.0)):
+        assert all(bool((t[i:i + 2**28] == v).all()) for i in range(0, n, 2**28))
+
+
 # ------------------------------------------------- sign-compressed sync
 @pytest.mark.parametrize("K,P,ef", [(16, 1841168, False), (16, 1841168, True),
                                     (4, 8192 + 4, False), (3, 260, True),

@@ -89,6 +89,27 @@ def test_state_blob_resumes_bit_exactly(case):
     c.sync()
 
 
+def test_state_blob_streamed_past_the_caches():
+    """265 MB of replicas and buffers whose rows are no whole number of vectors:
+    the blob holds every one of them, and a context restored from it reads back
+    the same blob."""
+    from paper_1808_07217_amd import lsgd as L
+    w = _small((1024, 1001, 10), K=32, B=8)
+    X, y, w0 = _small_data(w)
+    a = make_replicas(w, X, y, w0)
+    a.run_round([w.lr])
+    a.local_step(w.lr)
+    blob = a.read_state()
+    s = L.parse_state(blob)
+    for k in range(w.K):
+        assert torch.equal(s["W"][k], a.read_params(k))
+        assert torch.equal(s["U"][k], a.read_momentum(k))
+    assert not torch.equal(s["W"][0], s["W"][1])
+    c = make_replicas(w, X, y, w0)
+    c.write_state(blob)
+    assert torch.equal(c.read_state(), blob)
+
+
 def test_write_state_refuses_a_foreign_blob():
     """A blob of another configuration (different K, or damaged magic) is
     refused with LSGD_E_INVALID and changes nothing."""
