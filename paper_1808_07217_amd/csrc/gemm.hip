@@ -58,6 +58,7 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 // four elements at any element's alignment (one global load)
 typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
 
 constexpr int kThreads = 256;
 constexpr int kXcds = 8;
@@ -160,7 +161,6 @@ struct Quad;
 template <>
 struct Quad<false> {
   using E = float;
-  static constexpr int kPlanes = 3;
   v4f v;
   __device__ __forceinline__ void load(const E* p) { v = *(const v4f_any*)p; }
   __device__ __forceinline__ void set(int e, const E* p, bool ok) { v[e] = ok ? *p : 0.f; }
@@ -188,7 +188,6 @@ struct Quad<false> {
 template <>
 struct Quad<true> {
   using E = bf16_t;
-  static constexpr int kPlanes = 1;
   u32x2 v;
   __device__ __forceinline__ void load(const E* p) { v = *(const u32x2_any*)p; }
   __device__ __forceinline__ void set(int e, const E* p, bool ok) {
@@ -215,6 +214,16 @@ struct Quad<true> {
     return v4f{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
                __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u)};
   }
+};
+
+// Eight bf16 elements: one load and one LDS store of 16 bytes (products in whole
+// tiles: 8192 x 512 x 8192 123 us in quads, 101; 64 x 64 x 65536 389, 281).
+struct Oct {
+  using E = bf16_t;
+  u32x4 v;
+  __device__ __forceinline__ void load(const E* p) { v = *(const u32x4_any*)p; }
+  template <bool SCALED>
+  __device__ __forceinline__ void planes(u32x4 (&q)[1]) const { q[0] = v; }
 };
 
 // ------------------------------------------------------------------ the GEMM
@@ -247,14 +256,17 @@ template <bool BF, bool AT, bool BT, int EPI, bool GATHER, int BM, int BN, int B
           bool FULL, int NT = 0>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t, bf16_t* sA,
                                           bf16_t* sB, int32_t* srmap) {
-  using Q = Quad<BF>;
+  constexpr bool kOct = BF && FULL && EPI != EPI_SGD;
+  constexpr int VE = kOct ? 8 : 4;  // elements of a vector load
+  using Q = std::conditional_t<kOct, Oct, Quad<BF>>;
   using E = typename Q::E;
-  constexpr int NPL = Q::kPlanes;
+  using P = std::conditional_t<kOct, u32x4, u32x2>;
+  constexpr int NPL = BF ? 1 : 3;
   constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 32, FN = WN / 32;
   constexpr bool AK = !AT, BKc = BT;  // k contiguous in storage
   constexpr int PA = plane_pitch(AK, BM, BK), PB = plane_pitch(BKc, BN, BK);
   constexpr int SA = plane_size(AK, BM, BK), SB = plane_size(BKc, BN, BK);
-  constexpr int NA = BM * BK / 4 / kThreads, NB = BN * BK / 4 / kThreads;
+  constexpr int NA = BM * BK / VE / kThreads, NB = BN * BK / VE / kThreads;
   static_assert(NA >= 1 && NB >= 1 && D % 2 == 0, "tile too small");
   // the k rows of A come from a row map (an update's may have none: its rows
   // in order), the first kMapRows of it in LDS
@@ -325,11 +337,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t, bf16_
     const int q = tid + i * kThreads;
     shA[i] = 0;
     if constexpr (AK) {
-      int r = m0 + q / (BK / 4);
+      int r = m0 + q / (BK / VE);
       if constexpr (!FULL) r = min(r, M - 1);
       offA[i] = (GATHER ? (long long)rmap[r] : (long long)r) * a.lda;
     } else {
-      const int c = m0 + (q % (BM / 4)) * 4, cc = FULL ? c : max(min(c, M - 4), 0);
+      const int c = m0 + (q % (BM / VE)) * VE, cc = FULL ? c : max(min(c, M - 4), 0);
       offA[i] = cc;
       shA[i] = c - cc;
     }
@@ -339,11 +351,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t, bf16_
     const int q = tid + i * kThreads;
     shB[i] = 0;
     if constexpr (BKc) {
-      int r = n0 + q / (BK / 4);
+      int r = n0 + q / (BK / VE);
       if constexpr (!FULL) r = min(r, N - 1);
       offB[i] = (long long)r * a.ldb;
     } else {
-      const int c = n0 + (q % (BN / 4)) * 4, cc = FULL ? c : max(min(c, N - 4), 0);
+      const int c = n0 + (q % (BN / VE)) * VE, cc = FULL ? c : max(min(c, N - 4), 0);
       offB[i] = cc;
       shB[i] = c - cc;
     }
@@ -356,46 +368,48 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t, bf16_
   // fewer than four elements along the contiguous axis: element loads
   const bool thin = !FULL && ((AK || BKc ? a.Kd < 4 : false) || (!AK && M < 4) || (!BKc && N < 4));
   auto gload = [&](int k0, Q(&xa)[NA], Q(&xb)[NB]) __attribute__((always_inline)) {
-    if (!FULL && __builtin_expect(thin, 0)) {
+    if constexpr (!FULL) {
+      if (__builtin_expect(thin, 0)) {
 #pragma unroll
-      for (int i = 0; i < NA; ++i) {
-        const int q = tid + i * kThreads;
-        const int k = AK ? k0 + (q % (BK / 4)) * 4 : k0 + q / (BM / 4);
-        const int c = AK ? 0 : (int)offA[i] + shA[i];
-        xa[i].zero();
+        for (int i = 0; i < NA; ++i) {
+          const int q = tid + i * kThreads;
+          const int k = AK ? k0 + (q % (BK / VE)) * VE : k0 + q / (BM / VE);
+          const int c = AK ? 0 : (int)offA[i] + shA[i];
+          xa[i].zero();
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int ke = AK ? k + e : k;
-          if (ke < kend && (AK || c + e < M))
-            xa[i].set(e, AK ? A + offA[i] + ke : A + arow(ke) * a.lda + c + e, true);
+          for (int e = 0; e < 4; ++e) {
+            const int ke = AK ? k + e : k;
+            if (ke < kend && (AK || c + e < M))
+              xa[i].set(e, AK ? A + offA[i] + ke : A + arow(ke) * a.lda + c + e, true);
+          }
         }
-      }
 #pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        const int q = tid + i * kThreads;
-        const int k = BKc ? k0 + (q % (BK / 4)) * 4 : k0 + q / (BN / 4);
-        const int c = BKc ? 0 : (int)offB[i] + shB[i];
-        xb[i].zero();
+        for (int i = 0; i < NB; ++i) {
+          const int q = tid + i * kThreads;
+          const int k = BKc ? k0 + (q % (BK / VE)) * VE : k0 + q / (BN / VE);
+          const int c = BKc ? 0 : (int)offB[i] + shB[i];
+          xb[i].zero();
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int ke = BKc ? k + e : k;
-          if (ke < kend && (BKc || c + e < N))
-            xb[i].set(e, BKc ? B + offB[i] + ke : B + (long long)ke * a.ldb + c + e, true);
+          for (int e = 0; e < 4; ++e) {
+            const int ke = BKc ? k + e : k;
+            if (ke < kend && (BKc || c + e < N))
+              xb[i].set(e, BKc ? B + offB[i] + ke : B + (long long)ke * a.ldb + c + e, true);
+          }
         }
+        return;
       }
-      return;
     }
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
       const int q = tid + i * kThreads;
-      int k = AK ? k0 + (q % (BK / 4)) * 4 : k0 + q / (BM / 4);
+      int k = AK ? k0 + (q % (BK / VE)) * VE : k0 + q / (BM / VE);
       if constexpr (!FULL) k = min(k, kend - (AK ? 4 : 1));
       xa[i].load(AK ? A + offA[i] + k : A + arow(k) * a.lda + offA[i]);
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       const int q = tid + i * kThreads;
-      int k = BKc ? k0 + (q % (BK / 4)) * 4 : k0 + q / (BN / 4);
+      int k = BKc ? k0 + (q % (BK / VE)) * VE : k0 + q / (BN / VE);
       if constexpr (!FULL) k = min(k, kend - (BKc ? 4 : 1));
       xb[i].load(BKc ? B + offB[i] + k : B + (long long)k * a.ldb + offB[i]);
     }
@@ -417,14 +431,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t, bf16_
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
           const int q = tid + i * kThreads;
-          const int k = AK ? k0 + (q % (BK / 4)) * 4 : k0 + q / (BM / 4);
+          const int k = AK ? k0 + (q % (BK / VE)) * VE : k0 + q / (BM / VE);
           if constexpr (AK) xa[i].shift(max(k - (kend - 4), 0));
           xa[i].keep(AK ? kend - k : (k < kend ? 4 : 0));
         }
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
           const int q = tid + i * kThreads;
-          const int k = BKc ? k0 + (q % (BK / 4)) * 4 : k0 + q / (BN / 4);
+          const int k = BKc ? k0 + (q % (BK / VE)) * VE : k0 + q / (BN / VE);
           if constexpr (BKc) xb[i].shift(max(k - (kend - 4), 0));
           xb[i].keep(BKc ? kend - k : (k < kend ? 4 : 0));
         }
@@ -438,22 +452,22 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t, bf16_
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
       const int q = tid + i * kThreads;
-      const int o = AK ? (q / (BK / 4)) * PA + (q % (BK / 4)) * 4
-                       : (q / (BM / 4)) * PA + (q % (BM / 4)) * 4;
-      u32x2 p[NPL];
+      const int o = AK ? (q / (BK / VE)) * PA + (q % (BK / VE)) * VE
+                       : (q / (BM / VE)) * PA + (q % (BM / VE)) * VE;
+      P p[NPL];
       xa[i].template planes<kScaled>(p);
 #pragma unroll
-      for (int l = 0; l < NPL; ++l) *(u32x2*)&sA[(buf * NPL + l) * SA + o] = p[l];
+      for (int l = 0; l < NPL; ++l) *(P*)&sA[(buf * NPL + l) * SA + o] = p[l];
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       const int q = tid + i * kThreads;
-      const int o = BKc ? (q / (BK / 4)) * PB + (q % (BK / 4)) * 4
-                        : (q / (BN / 4)) * PB + (q % (BN / 4)) * 4;
-      u32x2 p[NPL];
+      const int o = BKc ? (q / (BK / VE)) * PB + (q % (BK / VE)) * VE
+                        : (q / (BN / VE)) * PB + (q % (BN / VE)) * VE;
+      P p[NPL];
       xb[i].template planes<kScaled>(p);
 #pragma unroll
-      for (int l = 0; l < NPL; ++l) *(u32x2*)&sB[(buf * NPL + l) * SB + o] = p[l];
+      for (int l = 0; l < NPL; ++l) *(P*)&sB[(buf * NPL + l) * SB + o] = p[l];
     }
   };
   auto colsums = [&](const Q(&xb)[NB]) __attribute__((always_inline)) {
@@ -830,12 +844,14 @@ hipError_t launch_reduce(const GemmArgs& a, hipStream_t s) {
 // split-K to get there; else 64 x 64. Measured, 16 replicas of 128 x 512 x
 // 3072, fp32 with the partials' sum: 128 x 128 split 4 46 us, 128 x 64 split 4
 // 51-58, 64 x 64 split 2 53; 128 x 512 x 512: 64 x 64 12 us, 128 x 64 18.
+// A caller's product without split-K takes larger tiles only where they fill the
+// chip by themselves (16 x 128 x 512 x 3072 in bf16: 31 us as 128 x 64, 16 as 64 x 64).
 struct Shape {
   int BM, BN;
 };
-Shape tile_shape(bool bf, int M, int N, int G, int Kd) {
+Shape tile_shape(bool bf, int M, int N, int G, int Kd, bool split = true) {
   if (M <= 64 || N <= 64) return {64, 64};
-  const bool deep = Kd >= 2048;
+  const bool deep = split && Kd >= 2048;
   const long long t128 = (long long)((M + 127) / 128) * ((N + 127) / 128) * G;
   if (!bf && (t128 >= 256 || (deep && t128 >= 32))) return {128, 128};
   const long long t64 = (long long)((M + 127) / 128) * ((N + 63) / 64) * G;
@@ -865,7 +881,7 @@ hipError_t run_tile(const GemmArgs& a, hipStream_t s) {
 
 template <bool BF, bool AT, bool BT, int EPI, bool GATHER>
 hipError_t run_type(const GemmArgs& a, hipStream_t s) {
-  const Shape sh = tile_shape(BF, a.M, a.N, a.G, a.Kd);
+  const Shape sh = tile_shape(BF, a.M, a.N, a.G, a.Kd, a.splits > 1);
   hipError_t e;
   if (sh.BM == 64)
     e = run_tile<BF, AT, BT, EPI, GATHER, 64, 64, BF ? 64 : 32, 2>(a, s);
