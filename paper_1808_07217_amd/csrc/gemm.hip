@@ -844,6 +844,10 @@ hipError_t launch_reduce(const GemmArgs& a, hipStream_t s) {
 // split-K to get there; else 64 x 64. Measured, 16 replicas of 128 x 512 x
 // 3072, fp32 with the partials' sum: 128 x 128 split 4 46 us, 128 x 64 split 4
 // 51-58, 64 x 64 split 2 53; 128 x 512 x 512: 64 x 64 12 us, 128 x 64 18.
+// Between one and nearly two rounds of 128 x 128 tiles (one a CU) 64 x 64 ones
+// leave less of the chip idle at the end: fp32 5 x 700 x 1100 x 784 (270 tiles)
+// 96 us, 59 as 64 x 64; 28 x 128 x 2048 x 256 (448) 35.7, 35.4; 31 x 256 x 1024
+// x 512 (496) 61, 68.
 // A caller's product without split-K takes larger tiles only where they fill the
 // chip by themselves (16 x 128 x 512 x 3072 in bf16: 31 us as 128 x 64, 16 as 64 x 64).
 struct Shape {
@@ -853,6 +857,7 @@ Shape tile_shape(bool bf, int M, int N, int G, int Kd, bool split = true) {
   if (M <= 64 || N <= 64) return {64, 64};
   const bool deep = split && Kd >= 2048;
   const long long t128 = (long long)((M + 127) / 128) * ((N + 127) / 128) * G;
+  if (!bf && !deep && t128 > 256 && t128 < 480) return {64, 64};
   if (!bf && (t128 >= 256 || (deep && t128 >= 32))) return {128, 128};
   const long long t64 = (long long)((M + 127) / 128) * ((N + 63) / 64) * G;
   if (t64 >= 512 || deep) return {128, 64};
