@@ -263,10 +263,10 @@ Layout make_layout(const lsgd_config* c) {
   for (int i = 1; i <= l.L; ++i) {
     const int din = c->widths[i - 1], dout = c->widths[i];
     const int dt = c->gemm_dtype;
-    const size_t f = lsgd::gemm_splits(dt, c->B_loc, dout, din, c->K, lsgd::EPI_BIAS);
+    const size_t f = lsgd::gemm_splits(dt, c->B_loc, dout, din, c->K);
     if (f > 1) part = std::max(part, f * K * B * dout);
     if (i > 1) {
-      const size_t d = lsgd::gemm_splits(dt, c->B_loc, din, dout, c->K, lsgd::EPI_RELU_MASK);
+      const size_t d = lsgd::gemm_splits(dt, c->B_loc, din, dout, c->K);
       if (d > 1) part = std::max(part, d * K * B * din);
     }
   }
@@ -524,7 +524,7 @@ lsgd_status do_local_step(lsgd_ctx* c, float lr, float* d_loss) {
     a.sBias = sWr;
     a.ldc = dout;
     a.sC = (long long)B * dout;
-    a.splits = lsgd::gemm_splits(dt, B, dout, din, K, lsgd::EPI_BIAS);
+    a.splits = lsgd::gemm_splits(dt, B, dout, din, K);
     a.part = c->part();
     if (l < L) {
       a.C = c->act(l);
@@ -606,7 +606,7 @@ lsgd_status do_local_step(lsgd_ctx* c, float lr, float* d_loss) {
     a.ldc = din;
     a.sC = (long long)B * din;
     a.mask = c->act(l - 1);
-    a.splits = lsgd::gemm_splits(dt, B, din, dout, K, lsgd::EPI_RELU_MASK);
+    a.splits = lsgd::gemm_splits(dt, B, din, dout, K);
     a.part = c->part();
     LSGD_LAUNCH(c, "dgrad" + std::to_string(l),
                 lsgd::launch_gemm(dt, 0, 1, lsgd::EPI_RELU_MASK, dt, a, s));

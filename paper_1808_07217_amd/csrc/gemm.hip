@@ -981,7 +981,7 @@ hipError_t launch_gemm_update(int dtype, const GemmArgs* list, int n, const Step
   return hipGetLastError();
 }
 
-int gemm_splits(int dtype, int M, int N, int Kd, int G, int epi) {
+int gemm_splits(int dtype, int M, int N, int Kd, int G) {
   const Shape sh = tile_shape(dtype == 1, M, N, G, Kd);
   const long long tiles = (long long)((N + sh.BN - 1) / sh.BN) * ((M + sh.BM - 1) / sh.BM) * G;
   const int want = sh.BM * sh.BN == 128 * 64 ? 512 : 256;

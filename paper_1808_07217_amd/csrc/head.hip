@@ -10,6 +10,8 @@
 //   sum_b A[b][d] dZ[b][c], fused with the momentum-SGD update; workgroup 0 of
 //   each replica also updates the bias (sum_b dZ[b][c]) and reduces the
 //   per-row losses.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace lsgd {
@@ -78,7 +80,7 @@ __device__ __forceinline__ void load_row(const bf16_t* p, float (&w)[CM]) {
 // Sums of v[0 .. N) over a wavefront (N / 32 whole): five exchanges that each
 // halve what a lane keeps (lanes with the exchanged bit set keep the upper
 // half), then one plain exchange; v[0 .. N/32) of lane l are the sums from
-// index first(l) on. 63 N / 64 + N / 32 exchanges instead of the 6 N of a
+// index first(l) on. 31 N / 32 + N / 32 = N exchanges instead of the 6 N of a
 // butterfly per value.
 template <int N, int OFF>
 __device__ __forceinline__ void scatter_sum(float* v, int lane, int& first) {
@@ -616,11 +618,15 @@ hipError_t launch_pair(const HeadArgs& h, hipStream_t s, int which) {
     else
       hipLaunchKernelGGL((k_head_fwd<T, CM, false>), grid, dim3(256), 0, s, h);
   } else {
+    // (behind hidden layers gemm_update has this layer with the others; only
+    // ResNet-20's, in fp32, comes here)
     dim3 grid((h.D + 63) / 64, h.K);
     if (gather)
       hipLaunchKernelGGL((k_head_wgrad<T, CM, true>), grid, dim3(256), 0, s, h);
-    else
+    else if constexpr (std::is_same_v<T, float>)
       hipLaunchKernelGGL((k_head_wgrad<T, CM, false>), grid, dim3(256), 0, s, h);
+    else
+      return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }

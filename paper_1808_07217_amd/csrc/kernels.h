@@ -97,7 +97,7 @@ struct GemmArgs {
 };
 
 // Split count launch_gemm would like for a problem (1 = no split-K).
-int gemm_splits(int dtype, int M, int N, int Kd, int G, int epi);
+int gemm_splits(int dtype, int M, int N, int Kd, int G);
 
 hipError_t launch_gemm(int dtype, int trans_a, int trans_b, int epi,
                        int out_bf16, const GemmArgs& a, hipStream_t s);
