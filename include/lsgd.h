@@ -340,9 +340,9 @@ const char* lsgd_last_error(const lsgd_ctx* ctx);
 
 /* Per-launch timing (a measurement aid, off by default): while enabled,
  * every kernel the context launches is bracketed by two HIP events on its
- * stream, tagged by launch site (sample, fwd<l>, xent, dgrad<l>,
- * wgrad_update<l>, average; a split-K GEMM's tag covers both of its
- * kernels). */
+ * stream, tagged by launch site (sample, fwd<l>, head_fwd, xent, dgrad<l>,
+ * wgrad_update for every layer's update, head_wgrad, average ...; a split-K
+ * GEMM's tag covers both of its kernels). */
 lsgd_status lsgd_profile_enable(lsgd_ctx* ctx, int32_t enable);
 
 /* Restrict the bracketing to launches tagged `tag` (host string, at most 64

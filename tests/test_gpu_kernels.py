@@ -94,18 +94,17 @@ def test_grouped_gemm_error_bound(dtype, ta, tb, shape, splits):
     assert np.all(np.abs(C - ref) <= bound), np.max(np.abs(C - ref) / bound)
 
 
-# whole-tile fp32 shapes with an even number of k slabs per split: the
-# kernel with two k halves per workgroup (64 x 64 tiles with 32-deep slabs,
-# or 128 x 128 tiles with 16-deep slabs once the inner dimension reaches
-# 2048), including an odd slab count per half (192 = 2 x 3 x 32)
+# whole-tile fp32 shapes, in one range of k and in splits: 64 x 64 tiles in slabs
+# of 32 (192 = 6 of them), 128 x 128 ones in slabs of 16 where there are 256 of
+# them or (with a split) the inner dimension reaches 2048
 @pytest.mark.parametrize("tb", [0, 1])
 @pytest.mark.parametrize("shape,splits", [((16, 128, 512, 512), 1), ((16, 128, 512, 512), 2),
                                           ((2, 64, 128, 192), 1), ((2, 256, 256, 3072), 1),
                                           ((2, 128, 256, 2048), 4)])
-def test_grouped_gemm_two_k_halves(shape, splits, tb):
+def test_grouped_gemm_whole_tiles(shape, splits, tb):
     L = _lsgd()
     G, M, N, Kd = shape
-    print(f"gemm two k halves {shape} splits={splits} tb={tb}", flush=True)
+    print(f"gemm whole tiles {shape} splits={splits} tb={tb}", flush=True)
     rng = np.random.default_rng(G + M + N + Kd + splits + tb)
     A = rng.standard_normal((G, M, Kd)).astype(np.float32)
     B = rng.standard_normal((G, N, Kd) if tb else (G, Kd, N)).astype(np.float32)

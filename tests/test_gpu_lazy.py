@@ -41,10 +41,10 @@ def _same(a, b, w):
 
 
 CASES = [
-    ((70, 48, 36, 10), "fp32", 4, 16, False),     # fused head, side streams
+    ((70, 48, 36, 10), "fp32", 4, 16, False),     # fused head
     ((64, 128, 64, 10), "bf16", 4, 16, True),     # bf16 operand copies of the mean
     ((40, 33, 45), "fp32", 3, 20, True),          # > 32 classes: generic top layer
-    ((256, 2048, 10), "fp32", 32, 21, False),     # persistent update kernel
+    ((256, 2048, 10), "fp32", 32, 21, False),     # thousands of update tiles
     ((512, 1024, 512, 10), "bf16", 16, 64, False),
 ]
 

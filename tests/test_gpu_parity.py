@@ -100,12 +100,12 @@ def _compare_steps(w, X, y, w0, param_tol, loss_tol, rounds=None, nr_ratio=None)
     ((64, 128, 64, 10), False, 0.0),
     ((37, 10), False, 0.5),
     ((130, 200, 66, 100, 7), True, 0.9),
-    ((50, 24, 20), False, 0.9),        # 17..32 classes: wider head variant
+    ((50, 24, 20), False, 0.9),        # 17..32 classes: the head of 32
     ((40, 33, 45), True, 0.9),         # > 32 classes: generic GEMM + loss path
     ((100, 256, 10), False, 0.9),      # register-resident head, 256 inputs
     ((48, 512, 512, 10), True, 0.9),   # register-resident head, 512 inputs
-    ((64, 64, 13), True, 0.9),         # one-pass head weight gradient, 13 classes
-    ((128, 16), False, 0.9),           # the same, gathered rows, 16 classes
+    ((64, 64, 13), True, 0.9),         # 13 classes: the head of 16
+    ((128, 16), False, 0.9),           # the same, gathered rows, its own update
 ])
 def test_small_mlp_every_step(widths, nesterov, momentum):
     w = _small(widths, nesterov=nesterov, momentum=momentum)
@@ -121,6 +121,8 @@ def test_small_mlp_every_step(widths, nesterov, momentum):
     ((5, 3, 2), 2, 3, "fp32"),            # layers below a quad
     ((33, 130, 67, 11), 2, 33, "bf16"),   # bf16 rows at odd alignment, a batch of a slab + 1
     ((1000, 1040, 10), 32, 8, "fp32"),    # 268 MB of state: the update streamed past the caches
+    ((1024, 1024, 10), 32, 80, "fp32"),   # and in whole tiles, five slabs
+    ((1024, 1024, 10), 32, 64, "bf16"),
 ])
 def test_update_and_head_at_tile_edges(widths, K, B, dtype):
     """Every layer's update, the losses and the next step's rows in one launch,
@@ -200,15 +202,14 @@ def test_batch_larger_than_the_gathered_row_cache():
 
 
 @pytest.mark.parametrize("widths,K,B,nesterov,seed", [
-    ((256, 2048, 10), 32, 21, False, 5),       # gathered rows, 1024 tiles
-    ((384, 384, 384, 10), 115, 9, True, 6),    # both layers; 1035 tiles, odd batch
-    ((64, 1024, 1024, 10), 16, 20, False, 5),  # activation rows, 1024 tiles
-    ((512, 1024, 512, 10), 16, 128, True, 5),  # 128-row batch: unrolled k loop
+    ((256, 2048, 10), 32, 21, False, 5),       # gathered rows, slabs that end early
+    ((384, 384, 384, 10), 115, 9, True, 6),    # 8970 tiles, no multiple of the 8 XCDs
+    ((64, 1024, 1024, 10), 16, 20, False, 5),  # layers one tile high, activation rows
+    ((512, 1024, 512, 10), 16, 128, True, 5),  # whole tiles and slabs below the head
 ])
-def test_persistent_update_kernel_shapes(widths, K, B, nesterov, seed):
-    """Layers with 1024 or more 128 x 128 weight tiles take the persistent
-    weight-gradient + update kernel (MFMA and update wavefronts working on
-    consecutive tiles); every replica after every step.
+def test_update_launch_shapes(widths, K, B, nesterov, seed):
+    """The launch that updates every layer in 64 x 64 tiles, thousands of them
+    (several a compute unit): every replica after every step.
 
     The data seeds keep every ReLU pre-activation of these runs clear of
     zero at fp32 resolution: perturbing the oracle's own initial weights by
@@ -218,22 +219,21 @@ def test_persistent_update_kernel_shapes(widths, K, B, nesterov, seed):
     oracle by 2.45e-4 -- an fp32 result can legitimately differ there.)"""
     w = _small(widths, nesterov=nesterov, K=K, B=B, N=max(999, 4 * K), H=2,
                rounds=2, lr=0.01)
-    print(f"persistent update {widths} K={K} B={B}", flush=True)
+    print(f"update launch {widths} K={K} B={B}", flush=True)
     X, y, w0 = _small_data(w, seed=seed)
     _compare_steps(w, X, y, w0, PARAM_TOL_FP32, 1e-4)
 
 
 @pytest.mark.parametrize("widths,K,B", [
-    ((256, 2048, 10), 32, 21),        # gathered bf16 rows, runtime k loop
-    ((512, 1024, 512, 10), 16, 64),   # both layers, unrolled 64-row k loop
+    ((256, 2048, 10), 32, 21),        # gathered bf16 rows, a slab that ends early
+    ((512, 1024, 512, 10), 16, 64),   # whole tiles and slabs of 64
 ])
-def test_persistent_update_kernel_bf16(widths, K, B):
-    """bf16 GEMM operands through the persistent update kernel (bf16 pairs
-    widened to fp32 for the MFMAs; fp32 master weights and momentum, bf16
-    weight copy written by the update), every replica after every step."""
+def test_update_launch_bf16(widths, K, B):
+    """The same launch on bf16 operands (fp32 master weights and momentum, the
+    bf16 weight copy written by the update), every replica after every step."""
     w = _small(widths, dtype="bf16", K=K, B=B, N=max(999, 4 * K), H=2,
                rounds=2, lr=0.01)
-    print(f"persistent update bf16 {widths} K={K} B={B}", flush=True)
+    print(f"update launch bf16 {widths} K={K} B={B}", flush=True)
     X, y, w0 = _small_data(w)
     _compare_steps(w, X, y, w0, 2e-3, LOSS_TOL_BF16, nr_ratio=NR_RATIO)
 
