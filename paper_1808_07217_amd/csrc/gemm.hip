@@ -26,8 +26,10 @@
 // overflow where x y does not.
 // The pieces of a value below 2^-110 fall under bf16's smallest subnormal, an
 // error of up to 2^-134 |y| of its product. The plain product (EPI_STORE), whose
-// operands may be anything, splits 2^24 x and 2^24 y instead, exact down to the
-// smallest subnormal, and takes 2^-48 of the sum. The products of a local step
+// operands may be anything, splits 2^16 x and 2^16 y instead, exact down to the
+// smallest subnormal (2^-149, whose image is bf16's), and takes 2^-32 of the sum;
+// what overflows by that (results of 2^96, operands of 2^112) takes the fp32
+// instruction. The products of a local step
 // do not: a step of normal size does not see 1e-40 of an activation or a
 // weight, and the multiplications cost it 2 to 4% (the 512-wide MLP's round of
 // 16 steps 3.24 -> 3.35 ms, 784-300-100-10 at a batch of 50 55 -> 57 us a step).
@@ -140,7 +142,7 @@ __device__ __forceinline__ void bias_update(const GemmArgs& a, int g, int n, flo
 // ------------------------------------------------------------ operand pieces
 // Two fp32 values (SCALED: times kSplitScale) as packed bf16 pairs
 // p[0] + p[1] + p[2] (see the top).
-constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
+constexpr float kSplitScale = 0x1p16f, kSplitUnscale = 0x1p-32f;
 template <bool SCALED>
 __device__ __forceinline__ void split3(float x, float y, uint32_t (&p)[3]) {
   if constexpr (SCALED) {
@@ -586,20 +588,28 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const Tile t, bf16_
       for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
-          floatx16 acc;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) acc[v] = 0.f;
           const int m = min(m0 + wm0 + i * 32 + lr, M - 1), n = min(n0 + wn0 + j * 32 + lr, N - 1);
-          for (int k = kbeg; k < kend; k += 2) {
-            const int kx = k + lk, kc = min(kx, kend - 1);
-            const long long oa = AT ? arow(kc) * a.lda + m
-                                    : (GATHER ? (long long)rmap[m] : (long long)m) * a.lda + kc;
-            const long long ob = BT ? (long long)n * a.ldb + kc : (long long)kc * a.ldb + n;
-            const float x = kx < kend ? ((const float*)A)[oa] : 0.f;
-            const float y = kx < kend ? ((const float*)B)[ob] : 0.f;
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, acc, 0, 0, 0);
+          const int kmid = kbeg + (kend - kbeg) / 4 * 2;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) hi[i][j][v] = 0.f;
+#pragma unroll 1
+          for (int half = 0; half < 2; ++half) {  // (two sums round less than one)
+            const int ke = half ? kend : kmid;
+            floatx16 acc;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+            for (int k = half ? kmid : kbeg; k < ke; k += 2) {
+              const int kx = k + lk, kc = min(kx, ke - 1);
+              const long long oa = AT ? arow(kc) * a.lda + m
+                                      : (GATHER ? (long long)rmap[m] : (long long)m) * a.lda + kc;
+              const long long ob = BT ? (long long)n * a.ldb + kc : (long long)kc * a.ldb + n;
+              const float x = kx < ke ? ((const float*)A)[oa] : 0.f;
+              const float y = kx < ke ? ((const float*)B)[ob] : 0.f;
+              acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, acc, 0, 0, 0);
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) hi[i][j][v] += acc[v];
           }
-          hi[i][j] = acc;
         }
     }
   }

@@ -162,8 +162,10 @@ def test_grouped_gemm_over_the_range_of_fp32(shape, ta, tb):
     rng = np.random.default_rng(M + 3 * N + 5 * Kd + 2 * ta + tb)
     A0 = rng.standard_normal((G, M, Kd)).astype(np.float32)
     B0 = rng.standard_normal((G, Kd, N)).astype(np.float32)
-    # scales of A and B as powers of two; the last two leave products near 2^125
-    for ea, eb in ((-112, 0), (0, -120), (-133, 0), (-128, 30), (-60, -60), (122, 0), (70, 50)):
+    # scales of A and B as powers of two; some leave products near 2^125, and
+    # sums on both sides of 2^96 and operands of 2^112
+    for ea, eb in ((-112, 0), (0, -120), (-133, 0), (-128, 30), (-60, -60), (122, 0), (70, 50),
+                   (47, 47), (111, -20), (-90, 113)):
         print(f"gemm range {shape} ta={ta} tb={tb} 2^{ea} 2^{eb}", flush=True)
         A, B = np.ldexp(A0, ea), np.ldexp(B0, eb)
         At = A.transpose(0, 2, 1) if ta else A
