@@ -250,8 +250,8 @@ def traffic_for(tag: str, w):
 TAG_KERNELS = {
     "wgrad_update": ("gemm_update<",),
     "average": ("k_average4<",),
-    "conv_fwd": ("k_conv_stem_fwd", "k_conv_halo16<0>", "k_conv_rows<0,"),
-    "conv_dgrad": ("k_conv_halo16<1>", "k_conv_rows<1,", "k_conv_dgrad_s2<"),
+    "conv_fwd": ("k_conv_stem_fwd", "k_conv_halo16<0,", "k_conv_rows<0,"),
+    "conv_dgrad": ("k_conv_halo16<1,", "k_conv_rows<1,", "k_conv_dgrad_s2<"),
     "conv_wgrad": ("k_conv_wgrad_stem", "k_conv_wgrad_halo16", "k_conv_wgrad_band<"),
     "bn_bwd": ("k_bn_partial4", "k_bn_finalize_wg", "k_bn_bwd_apply4"),
     "bn_apply": ("k_bn_apply4<",),
