@@ -217,9 +217,11 @@ __device__ __forceinline__ void store_bf16x4(bf16_t* p, v4f v) {
 // mean_out != nullptr (one block): write the mean there (and its bf16 copy to
 // Wb [n] when given) and leave W untouched.
 // HBM-bound. 16 x 16.8M (2.1 GB read and written): 455 us, with the NT
-// form 366 us (5.9 TB/s).
+// form 366 us (5.9 TB/s). The plain form keeps eight wavefronts a SIMD: with more
+// registers (74 for 16 rows) rows in the cache whose pitch is a power of two lose
+// up to 10% (16 x 1M 21.2 -> 23.4 us, 32 x 1M 41.7 -> 46.5), others 1%.
 template <int KT, bool NT>
-__global__ __launch_bounds__(256) void k_average4(float* W, bf16_t* Wb, int K, long long n,
+__global__ __launch_bounds__(256, !NT && KT > 0 && KT <= 32 ? 8 : 1) void k_average4(float* W, bf16_t* Wb, int K, long long n,
                                                   long long ld, float* mean_out) {
   W += blockIdx.y * (long long)K * ld;
   if (Wb) Wb += blockIdx.y * (long long)K * ld;
